@@ -229,7 +229,7 @@ int fbp_init(const Plan &p, const float *g, float *f, hipStream_t s)
     std::vector<double> ind((size_t)G.Ntheta * Npi, 0.0);
     for (int i = 0; i < G.Ntheta; ++i) ind[(size_t)i * Npi + i / n0] = M_PI / (double)n0;
     rt_plan *ip = nullptr;
-    if ((rc = rt_plan_create(&gm, RT_FORM_PF, RT_PREC_FP32, ind.data(), nullptr, &ip))) return rc;
+    if ((rc = plan_create(&gm, RT_FORM_PF, RT_PREC_FP32, ind.data(), nullptr, gm.Nz, true, &ip))) return rc;
     struct PlanGuard {
         rt_plan *p;
         ~PlanGuard() { rt_plan_destroy(p); }

@@ -45,29 +45,34 @@ struct Tables {
     std::vector<double> ccos, csin;     // [Ntheta0] cos/sin of theta0_a
 };
 
-// Work layout of the ray-driven projector: classes of one walk direction
-// (rows when |cos| >= |sin|, columns otherwise) are grouped A at a time; one
-// workgroup owns (group, slice, channel chunk, bin tile).
-// Staged lines of the plain projector: KC channels of a position in a row of
-// line_stride(KC) floats (an odd number of 16-byte groups, so that 16
-// consecutive positions fall in distinct LDS bank groups), LINE_GUARD zero
-// positions at each end of a line.
-constexpr int LINE_GUARD = 2;
-__host__ __device__ constexpr int line_stride(int kc) { return (kc / 4) % 2 ? kc : kc + 4; }
+// Rays of one workgroup of the plain projector (k_project): bin blocks [bb0,
+// bb0 + bbt) (64 bins each) of the classes [cls0, cls0 + ncls) of the class
+// list, which share one walk direction (0: rows, |cos| >= |sin|; 1: columns)
+// and neighbour each other in angle.  On line l their taps lie in the W
+// positions from floor(wl0 + l sw) on (32.32 fixed point).
+struct RayGroup {
+    int walk, cls0, ncls, bb0, bbt, W;
+    long long wl0, sw;
+};
+// float4 staged per thread and stage, threads and ray blocks of a workgroup
+constexpr int RAY_PF = 4, RAY_NTH = 1024, RAY_BLOCKS = 32;
+constexpr int RAY_PF_SMALL = 8, RAY_NTH_SMALL = 256, RAY_BLOCKS_SMALL = 4;
+// widest window: one line of 4-quad rows per stage
+constexpr int RAY_WMAX = RAY_PF * RAY_NTH / 4, RAY_WMAX_SMALL = RAY_PF_SMALL * RAY_NTH_SMALL / 4;
 
-struct FwdCfg {
-    int A = 1;            // classes per group
-    int ngroups = 0;
-    int KC = 4;           // channels per chunk (4, 8, 16)
-    int nkc = 1;          // channel chunks
-    int BT = 1;           // bins per tile
-    int nbt = 1;          // bin tiles
-    int stride = 4;       // floats per staged position (KC + padding)
-    int nbuf = 2;         // LDS line buffers (1 when two padded lines do not fit)
+// Work split of the plain projector, from the plan's geometry: one workgroup
+// owns NQ channel quads of the list of all slices' quads, one RayGroup, and
+// one of NLP parts of the lines.
+struct RayCfg {
+    int NQ = 4;           // channel quads per workgroup (1, 2, 4)
+    int K4 = 1;           // channel quads per slice
+    int ncg = 1;          // column groups: ceil(Nz K4 / NQ)
+    int group0 = 0, ngroups = 0;   // the plan's groups in use
+    int NLP = 1;          // line parts (> 1: partial sums, added by k_contract)
+    int nth = RAY_NTH;    // threads per workgroup
     bool tl = false;      // two-level ray sums (N > 512)
-    int vec = 1;          // 4: float4 staging loads
-    int pf = 4;           // float4 per thread that hold one staged line (4 or 8)
-    int nth = 512;        // threads per workgroup (1024: 16 waves of 2 rays, KC = 16)
+    bool fused = true;    // contraction in the epilogue
+    unsigned nblocks = 0;
     size_t lds = 0;       // bytes of LDS per workgroup
 };
 
@@ -108,22 +113,26 @@ struct Plan {
     int device = 0;
     int n0 = 1;           // Ntheta0 = Ntheta / Npi
     Tables T;
-    std::vector<uint8_t> lperm;   // host copy of d_lperm
-    FwdCfg fwd;
+    int nz_ref = 0;       // slices the order of the ray sums is planned for (see ray_cfg)
+    bool adjoint_only = false;
+    std::vector<RayGroup> groups;   // full workgroups, then small ones
+    int ngroups = 0;      // full workgroups
     AdjCfg adj;
     SfCfg sf;
     TvCfg tv;
 
+    void *d_tables = nullptr;   // holds the tables below, up to d_gwalk_sf
     float *d_phi = nullptr;     // [Ntheta][K]
     float *d_S = nullptr;       // [Nt][K]
     double *d_ccos = nullptr;   // [Ntheta0]
     double *d_csin = nullptr;
-    int *d_gcls = nullptr;      // [ngroups][A], -1 = empty slot
-    int *d_gwalk = nullptr;     // [ngroups]
-    uint8_t *d_lperm = nullptr; // [Ntheta0][64] forward lane -> bin offset in its block of 64
+    float *d_phip = nullptr;    // [Ntheta][K rounded up to 4], zero padded
+    int *d_wcls = nullptr;      // classes by walk direction and sign of cos
+    RayGroup *d_groups = nullptr;
+    uint8_t *d_lanes = nullptr; // [3][Ntheta0][64] lane -> bin offset in its block of 64, for 1, 2, 4 channel quads
     int *d_gcls_sf = nullptr;   // class groups of the synthesise-first projector
     int *d_gwalk_sf = nullptr;
-    float *d_scr = nullptr;     // [Ntheta0][Nz][Ns][K]: P (forward), g~ (adjoint)
+    float *d_scr = nullptr;     // P (forward) [NLP][Ntheta0][Nz][Ns][K up to 4], g~ (adjoint) [Ntheta0][Nz][Ns][K]
     float *d_frames = nullptr;  // [Nz][Nt][N][N]: time frames for tv_grad / tv_norm
     double *d_part = nullptr;   // FP64 partial sums
     size_t part_cap = 0;        // doubles in d_part
@@ -161,7 +170,15 @@ inline size_t nf_of(const rt_geom &g) { return (size_t)g.Nz * g.N * g.N * g.K; }
 inline size_t ng_of(const rt_geom &g) { return (size_t)g.Ntheta * g.Nz * g.Ns; }
 inline size_t n4_of(const rt_geom &g) { return (size_t)g.Nz * g.N * g.N * g.Nt; }
 size_t job_state_bytes(const rt_geom &g);
-size_t plan_scratch_bytes(const rt_geom &g);
+size_t plan_scratch_bytes(const rt_geom &g, int nz_ref);
+size_t adjoint_scratch_bytes(const rt_geom &g);   // g~ alone
+// plan_create with the order of the ray sums planned for nz_ref slices: plans
+// that differ only in Nz then give every slice the same bits.  adjoint_only:
+// no more than R_T* needs (no projector tables, no scratch for it, for the TV
+// or for reductions)
+int plan_create(const rt_geom *geom, rt_form form, rt_prec prec, const double *phi, const double *S,
+                int nz_ref, bool adjoint_only, rt_plan **out);
+RayCfg ray_cfg(const Plan &p);
 size_t shadow_bytes(const rt_geom &g);   // BF16 shadow of f (synthesise-first plans)
 int sf_line_parts(const rt_geom &g);     // NLP of a synthesise-first plan
 size_t sf_partial_bytes(const rt_geom &g);   // its partial ray sums (0 when NLP = 1)

@@ -58,7 +58,8 @@ struct SlabPlans {
             rt_geom gz = g;
             gz.Nz = nz;
             rt_plan *p = nullptr;
-            int rc = rt_plan_create(&gz, RT_FORM_PF, RT_PREC_FP32, phi, S, &p);
+            // ray sums in the order of the whole volume's plan
+            int rc = plan_create(&gz, RT_FORM_PF, RT_PREC_FP32, phi, S, g.Nz, false, &p);
             if (rc) return rc;
             it = m.emplace(nz, p).first;
         }

@@ -5,6 +5,7 @@
 #include <cstdio>
 #include <cstring>
 #include <new>
+#include <utility>
 
 #include "internal.h"
 
@@ -58,10 +59,192 @@ int check_plan(const rt_plan *p)
     return RT_OK;
 }
 
-size_t plan_scratch_bytes(const rt_geom &g)
+// Time of one projection launch in microseconds, for the choice of the line
+// parts: `rounds` workgroups one after the other on a CU, each walking
+// `lines` lines of N positions for `blocks` ray blocks of 64, and the extra
+// kernel and traffic of partial sums.  Per line: the tap reads at about 5
+// cycles, the stores of the line at 8, a barrier; a fixed 6 us per workgroup.
+static double project_cost(double rounds, double lines, double blocks, int N, int NQ, double parts_bytes)
 {
-    const size_t n0 = (size_t)(g.Ntheta / g.Npi);
-    return n0 * g.Nz * g.Ns * g.K * sizeof(float);
+    const double line = (blocks * 2 * NQ * 5.5 + std::min(N, 300) * NQ / 64.0 * 8 + 400) / 2400.0;
+    return rounds * (lines * line + 6.0) + (parts_bytes > 0 ? 8.0 + parts_bytes / 2.0e6 : 0.0);
+}
+
+// The split of the lines and the workgroup size for nz slices.  The parts
+// fix the order in which a ray's taps are added, so they follow from nz_ref
+// alone: every plan of one volume, whole or a slab, passes the same.  One part
+// and full workgroups (32 ray blocks) where these fill the chip; else the
+// cheaper, by project_cost, of up to 16 parts of full workgroups and, for lines
+// of at most 256 positions, of workgroups of 4 ray blocks (several per CU).
+// Measured: one 512^2 slice of 16 channels over 180 classes, 46 full
+// workgroups, 577 us in one part.
+static int quads_per_row(const rt_geom &g, int nz)
+{
+    const long tq = (long)nz * ((g.K + 3) / 4);   // channel quads of nz slices
+    return tq >= 3 ? 4 : (int)std::max(tq, 1L);
+}
+
+struct LineSplit {
+    int NLP = 1;
+    bool small = false;
+};
+static LineSplit line_split(const rt_geom &g, int nz)
+{
+    LineSplit best;
+    if (nz < 1) return best;
+    const long n0 = g.Ntheta / g.Npi;
+    const long K4 = (g.K + 3) / 4, nbb = (g.Ns + 63) / 64;
+    const int NQ = quads_per_row(g, nz);
+    const long ncg = (nz * K4 + NQ - 1) / NQ;
+    const long half = (n0 + 1) / 2 * nbb;   // ray blocks of a walk, about
+    const bool fusable = g.N <= 512 && K4 <= NQ && NQ % K4 == 0;
+    double cost = 1e300;
+    for (int small = 0; small < (g.N <= 256 ? 2 : 1); ++small) {
+        const long bpw = small ? RAY_BLOCKS_SMALL : RAY_BLOCKS;
+        const long W = ncg * 2 * ((half + bpw - 1) / bpw) * 107 / 100;   // groups fill to about 0.94
+        const long occ = small ? (NQ == 4 ? 2 : 4) : 1;   // workgroups per CU, by their LDS
+        if (!small && W >= 512) return LineSplit{};
+        for (int np = 1; np <= 16 && np * 4 <= std::max(g.N, 4); ++np) {
+            const double rounds = (double)((W * np + 256 * occ - 1) / (256 * occ));
+            const double pb = np > 1 || !fusable ? 2.0 * np * n0 * nz * g.Ns * K4 * 16 : 0.0;
+            // the workgroups that share a CU take turns: their blocks add up
+            const double share = std::min<double>((double)occ, std::max(1.0, (double)(W * np) / 256));
+            const double c = project_cost(rounds, (double)g.N / np, bpw * share, g.N, NQ, pb);
+            if (c < cost * 0.97) {
+                cost = c;
+                best.NLP = np;
+                best.small = small;
+            }
+        }
+    }
+    return best;
+}
+
+size_t adjoint_scratch_bytes(const rt_geom &g)
+{
+    return (size_t)(g.Ntheta / g.Npi) * g.Nz * g.Ns * ((size_t)(g.K + 3) / 4 * 4) * sizeof(float);
+}
+
+size_t plan_scratch_bytes(const rt_geom &g, int nz_ref)
+{
+    const size_t n0 = (size_t)(g.Ntheta / g.Npi), Kp = (size_t)(g.K + 3) / 4 * 4;
+    // partial ray sums of the whole volume, or of the one slice of the power iteration
+    const size_t slices = std::max((size_t)g.Nz * line_split(g, nz_ref).NLP,
+                                   g.Nz > 0 ? (size_t)line_split(g, 1).NLP : 0);
+    return n0 * slices * g.Ns * Kp * sizeof(float);
+}
+
+// The window of a group of rays: n classes of directions d (one walk, one
+// sign of the main direction) and bins [b0, b1].  Relative to the line of the middle
+// slope a class's positions run linearly, so the extremes over the group are
+// at the first or last line.  One position to spare below and two above (the
+// right tap, and fixed-point rounding).  A window wider than the line becomes
+// the whole line with two guard positions at each end.
+struct RayDir {
+    double slope, inv;   // positions per line, per bin
+};
+static void ray_window(int N, int Ns, const RayDir *d, int n, int b0, int b1, RayGroup &G)
+{
+    const double hN = 0.5 * (double)(N - 1), hS = 0.5 * (double)(Ns - 1);
+    double smin = 1e9, smax = -1e9, lo = 1e9, hi = -1e9;
+    for (int i = 0; i < n; ++i) {
+        smin = std::min(smin, d[i].slope);
+        smax = std::max(smax, d[i].slope);
+    }
+    const double sw = 0.5 * (smin + smax);
+    for (int i = 0; i < n; ++i) {
+        const double first = hN - hN * d[i].slope;                    // line 0, the bin at s = 0
+        const double last = hN + hN * d[i].slope - (double)(N - 1) * sw;
+        const double p0 = ((double)b0 - hS) * d[i].inv, p1 = ((double)b1 - hS) * d[i].inv;
+        lo = std::min(lo, std::min(first, last) + std::min(p0, p1));
+        hi = std::max(hi, std::max(first, last) + std::max(p0, p1));
+    }
+    G.W = (int)std::ceil(hi - lo) + 5;
+    if (G.W < N + 4) {
+        G.wl0 = std::llrint((lo - 1.0) * 4294967296.0);
+        G.sw = std::llrint(sw * 4294967296.0);
+    } else {
+        G.W = N + 4;
+        G.wl0 = -2 * (1LL << 32);
+        G.sw = 0;
+    }
+}
+
+// Ray groups of at most `blocks` bin blocks with windows of at most wmax
+// positions.  A group is a tile of bin blocks over neighbouring classes; more
+// classes and fewer bins (or the reverse) widen the window by their fan-out
+// (their spacing).  The tile width is the power of two that costs least: per
+// line the LDS cycles of the taps and of the window's stores and a share of
+// the barrier, as k_project's comment has them.  At 512^2 over 180 classes two
+// blocks of 16 classes: windows of 247 positions on average; whole lines
+// (eight blocks of four classes) took 16% longer there and 2.1x at 1024^2.
+static std::vector<RayGroup> ray_groups(const rt_geom &g, const std::vector<RayDir> (&lists)[3], int blocks, int wmax)
+{
+    const int nbb = (g.Ns + 63) / 64, N = g.N, Ns = g.Ns;
+    std::vector<RayGroup> best;
+    double best_cost = 1e300;
+    for (int tile = 1; tile <= blocks; tile *= 2) {
+        const int nt = (nbb + tile - 1) / tile;   // tiles of nearly equal width
+        std::vector<RayGroup> v;
+        double cost = 0.0;
+        bool fits = true;
+        int cls0 = 0;
+        for (int s = 0; s < 3; ++s) {
+            const std::vector<RayDir> &L = lists[s];
+            for (int t = 0; t < nt; ++t) {
+                RayGroup G{};
+                G.walk = s == 1;
+                G.bb0 = t * (nbb / nt) + std::min(t, nbb % nt);
+                G.bbt = nbb / nt + (t < nbb % nt ? 1 : 0);
+                const int b0 = G.bb0 * 64, b1 = std::min((G.bb0 + G.bbt) * 64, Ns) - 1;
+                for (int i = 0; i < (int)L.size(); i += G.ncls) {
+                    G.cls0 = cls0 + i;
+                    G.ncls = std::min(blocks / G.bbt, (int)L.size() - i);
+                    ray_window(N, Ns, L.data() + i, G.ncls, b0, b1, G);
+                    while (G.W > wmax && G.ncls > 1) ray_window(N, Ns, L.data() + i, --G.ncls, b0, b1, G);
+                    if (G.W > wmax) fits = false;
+                    const int lines = std::max(1, wmax / G.W >= 4 ? 4 : wmax / G.W >= 2 ? 2 : 1);
+                    cost += G.ncls * G.bbt * 40.0 + G.W * 0.5 + 500.0 / lines;
+                    v.push_back(G);
+                }
+            }
+            cls0 += (int)L.size();
+        }
+        if (fits && cost < best_cost) {
+            best_cost = cost;
+            best = v;
+        }
+        if (tile >= nbb) break;
+    }
+    return best;
+}
+
+RayCfg ray_cfg(const Plan &p)
+{
+    const rt_geom &g = p.g;
+    const LineSplit L = line_split(g, p.nz_ref);
+    RayCfg R;
+    R.K4 = (g.K + 3) / 4;
+    const int tq = g.Nz * R.K4;   // channel quads of all slices
+    R.NQ = quads_per_row(g, g.Nz);
+    R.ncg = (tq + R.NQ - 1) / R.NQ;
+    R.tl = g.N > 512;
+    R.NLP = L.NLP;
+    R.nth = L.small ? RAY_NTH_SMALL : RAY_NTH;
+    R.group0 = L.small ? p.ngroups : 0;
+    R.ngroups = L.small ? (int)p.groups.size() - p.ngroups : p.ngroups;
+    R.fused = R.NLP == 1 && !R.tl && R.K4 <= R.NQ && R.NQ % R.K4 == 0;
+    R.nblocks = (unsigned)R.ncg * R.ngroups * R.NLP;
+    // stage buffers: as k_project lays them out
+    const int rpj = R.nth / R.NQ, pf = L.small ? RAY_PF_SMALL : RAY_PF;
+    int rows = 0;
+    for (int i = 0; i < R.ngroups; ++i) {
+        const int W = p.groups[R.group0 + i].W;
+        const int sh = W <= rpj ? 0 : W <= 2 * rpj ? 1 : W <= 4 * rpj ? 2 : 3;
+        rows = std::max(rows, std::min(pf >> sh, (g.N + R.NLP - 1) / R.NLP) * W);
+    }
+    R.lds = (size_t)2 * rows * R.NQ * 16;
+    return R;
 }
 
 size_t shadow_bytes(const rt_geom &g)
@@ -122,91 +305,94 @@ static void build_tables(const rt_geom &g, const double *phi, const double *S, T
     }
 }
 
-static int configure(Plan &p)
+// The plan's tables in one device allocation and one copy.
+struct TableUpload {
+    std::vector<char> host;
+    std::vector<std::pair<void **, size_t>> at;   // pointer to set, offset
+    template <class T>
+    void add(T **dst, const std::vector<T> &src)
+    {
+        at.emplace_back((void **)dst, host.size());
+        const size_t b = (std::max<size_t>(src.size(), 1) * sizeof(T) + 255) / 256 * 256;
+        host.resize(host.size() + b, 0);
+        if (!src.empty()) std::memcpy(host.data() + at.back().second, src.data(), src.size() * sizeof(T));
+    }
+    int upload(void **mem, size_t *bytes)
+    {
+        RT_HIP(hipMalloc(mem, host.size()));
+        RT_HIP(hipMemcpy(*mem, host.data(), host.size(), hipMemcpyHostToDevice));
+        for (const auto &x : at) *x.first = (char *)*mem + x.second;
+        *bytes += host.size();
+        return RT_OK;
+    }
+};
+
+static int configure(Plan &p, TableUpload &up)
 {
     const rt_geom &g = p.g;
     const int n0 = p.n0;
     const size_t budget = 80 * 1024;
 
-    // ---- forward: classes grouped by walk direction
-    std::vector<int> rows, cols;
-    for (int a = 0; a < n0; ++a)
-        (std::fabs(p.T.ccos[a]) >= std::fabs(p.T.csin[a]) ? rows : cols).push_back(a);
-    FwdCfg &F = p.fwd;
-    // 512 threads x 4 rays; for 512 < N <= 1024, 8 rays of 8-channel chunks:
-    // each workgroup streams its whole slice through, so the re-read traffic
-    // per channel-sample is 2N / (rays per workgroup).  (Register budget of
-    // the two-level ray sums: 16 channels only for N <= 512, 8 rays only with
-    // 8 channels and one line of prefetch in 4 float4.)
-    const bool wide = g.N > 512 && g.N <= 1024 && g.K % 4 == 0;
-    const int pairs_max = 512 * (wide ? 8 : 4);
-    F.BT = std::min(g.Ns, pairs_max);
-    F.nbt = (g.Ns + F.BT - 1) / F.BT;
-    F.A = std::max(1, pairs_max / F.BT);
-    F.A = std::min(F.A, (int)std::max(rows.size(), cols.size()));
-    std::vector<int> gcls, gwalk;
-    for (int w = 0; w < 2; ++w) {
-        const std::vector<int> &L = w == 0 ? rows : cols;
-        for (size_t i = 0; i < L.size(); i += F.A) {
-            for (int j = 0; j < F.A; ++j)
-                gcls.push_back(i + j < L.size() ? L[i + j] : -1);
-            gwalk.push_back(w);
-        }
-    }
-    F.ngroups = (int)gwalk.size();
-    // LDS line buffers with an odd number of 16-byte groups per position
-    // (KC = 4: 4 floats, 8: 12, 16: 20), so that 16 consecutive positions
-    // fall in distinct bank groups: two buffers when they fit, else one; one
-    // line must also fit the 512 threads' prefetch registers (N * KC <= 16384)
-    F.KC = 0;
-    const int K4 = (g.K + 3) / 4 * 4;
-    for (int kc : {16, 8, 4}) {
-        const int pfmax = g.K % 4 == 0 && !wide ? 8 : 4;   // float4 of line prefetch per thread
-        const int kcmax = g.K % 4 == 0 && g.N <= 512 ? 16 : 8;
-        if (F.KC || (kc > K4 && kc != 4) || g.N * kc > 4 * pfmax * 512 || kc > kcmax) continue;
-        const int stride = line_stride(kc);
-        for (int nbuf : {2, 1})
-            if (!F.KC && nbuf * (size_t)(g.N + 2 * LINE_GUARD) * stride * sizeof(float) <= 160 * 1024) {
-                F.KC = kc;
-                F.stride = stride;
-                F.nbuf = nbuf;
-            }
-    }
-    if (F.KC == 0)
-        return fail(RT_E_SHAPE, "no staged-line configuration of the projector for N=%d K=%d", g.N, g.K);
-    F.pf = g.N * F.KC <= 4 * 4 * 512 ? 4 : 8;
-    F.tl = g.N > 512;
-    F.nkc = (g.K + F.KC - 1) / F.KC;
-    F.vec = (g.K % 4 == 0) ? 4 : 1;
-    F.lds = (size_t)F.nbuf * (g.N + 2 * LINE_GUARD) * F.stride * sizeof(float);
-    // 16-channel chunks over more than 1024 rays: 1024 threads of 2 rays each.
-    // The group (and so the slice re-read traffic) is the same as with 512
-    // threads of 4 rays, at half the registers per thread, so twice the
-    // waves share the CU's LDS and VALU.
-    F.nth = F.KC == 16 && F.vec == 4 && !F.tl && F.A * F.BT > 1024 && g.N <= 512 ? 1024 : 512;
-
-    // Lane order of the forward waves. A wave's 64 rays are 64 consecutive bins
-    // of one class when BT is a multiple of 64; their positions on a line are
-    // spaced 1/|c| in [1, sqrt 2] apart, and each 16-byte tap read is served 16
-    // lanes at a time over 16 bank groups that repeat every 16 positions (the
-    // padded stride is an odd number of groups). Consecutive bins in a quarter
-    // of the wave span up to 22 positions, so some share a group. Ordering the
-    // 64 rays by (r / c) mod 16 and dealing them out in turn to the four
-    // quarters spreads each quarter's positions evenly over the 16 groups.
-    // The plain form applies the order when BT is a multiple of 64, the
-    // precision form to each class slot's bins.
-    p.lperm.assign((size_t)n0 * 64, 0);
+    // ---- forward: classes by walk direction and sign of the main direction
+    std::vector<int> rows, cols, by_dir[3];
+    std::vector<RayDir> lists[3];
     for (int a = 0; a < n0; ++a) {
-        const double c = std::fabs(p.T.ccos[a]) >= std::fabs(p.T.csin[a]) ? p.T.ccos[a] : p.T.csin[a];
-        double ph[64];
-        int ord[64];
-        for (int r = 0; r < 64; ++r) {
-            ph[r] = std::fmod((double)r / c, 16.0);
-            if (ph[r] < 0) ph[r] += 16.0;
-            ord[r] = r;
+        const double cs = p.T.ccos[a], sn = p.T.csin[a];
+        const bool row = std::fabs(cs) >= std::fabs(sn);
+        (row ? rows : cols).push_back(a);
+        const int d = !row ? 1 : cs > 0 ? 0 : 2;
+        by_dir[d].push_back(a);
+        lists[d].push_back(row ? RayDir{-sn / cs, 1.0 / cs} : RayDir{-cs / sn, 1.0 / sn});
+    }
+    std::vector<int> wcls;
+    for (const std::vector<int> &L : by_dir) wcls.insert(wcls.end(), L.begin(), L.end());
+    if (!p.adjoint_only) p.groups = ray_groups(g, lists, RAY_BLOCKS, RAY_WMAX);
+    p.ngroups = (int)p.groups.size();
+    if (!p.adjoint_only && !p.ngroups) return fail(RT_E_SHAPE, "no ray groups of the projector for N=%d Ns=%d", g.N, g.Ns);
+    if (!p.adjoint_only && (line_split(g, p.nz_ref).small || line_split(g, 1).small)) {
+        const std::vector<RayGroup> v = ray_groups(g, lists, RAY_BLOCKS_SMALL, RAY_WMAX_SMALL);
+        p.groups.insert(p.groups.end(), v.begin(), v.end());
+    }
+
+    // Lane order of the forward waves.  A wave's 64 rays are 64 consecutive
+    // bins of one class; their positions on a line are spaced 1/|c| in [1,
+    // sqrt 2] apart.  A 16-byte LDS read is served 16 lanes at a time, in the
+    // groups of lane quads {0,3,5,6}, {1,2,4,7} and the same + 8 (measured: a
+    // lane on the same 16-byte unit as lane 0 costs a cycle for the lanes of
+    // its group alone).  With NQ quads per staged position the lanes of a
+    // group that read the same quad of a position must differ modulo 16 / NQ
+    // in position; ordering the 64 rays by (r / c) modulo that and dealing
+    // them out in turn spreads each such set evenly.  The precision form's
+    // rows (an odd number of 16-byte units) take the order of NQ = 1.
+    std::vector<uint8_t> lanes((size_t)3 * n0 * 64, 0);
+    static const int set_quads[3][8] = {   // lane quads of the sets, in order, of half a wave
+        {0, 3, 5, 6, 1, 2, 4, 7}, {0, 3, 5, 6, 1, 2, 4, 7}, {0, 1, 2, 3, 4, 5, 6, 7}};
+    for (int v = 0; v < 3 && !p.adjoint_only; ++v) {
+        const int NQ = 1 << v, M = 16 / NQ, nsets = 4 * NQ;   // sets of M lanes
+        // in use: by the volume, by the one slice of the power iteration, by
+        // the precision form
+        if (NQ != quads_per_row(g, p.nz_ref) && NQ != quads_per_row(g, 1) &&
+            NQ != quads_per_row(g, g.Nz) && !(NQ == 1 && p.form == RT_FORM_SF))
+            continue;
+        for (int a = 0; a < n0; ++a) {
+            const double d = 1.0 / std::max(std::fabs(p.T.ccos[a]), std::fabs(p.T.csin[a]));
+            // counting sort of the phases r d mod M in 256 steps
+            uint8_t key[64], ord[64];
+            int at[257] = {0};
+            double ph = 0.0;
+            for (int r = 0; r < 64; ++r, ph += d) {
+                if (ph >= M) ph -= M;
+                key[r] = (uint8_t)std::min(255, (int)(ph * 256.0 / M));
+                ++at[key[r] + 1];
+            }
+            for (int k = 0; k < 256; ++k) at[k + 1] += at[k];
+            for (int r = 0; r < 64; ++r) ord[at[key[r]]++] = (uint8_t)r;
+            for (int i = 0; i < 64; ++i) {
+                const int slot = (i % nsets) * M + i / nsets;   // set, place in it
+                const int lane = 32 * (slot / 32) + 4 * set_quads[v][slot % 32 / 4] + slot % 4;
+                lanes[((size_t)v * n0 + a) * 64 + lane] = ord[i];
+            }
         }
-        std::stable_sort(ord, ord + 64, [&](int x, int y) { return ph[x] < ph[y]; });
-        for (int i = 0; i < 64; ++i) p.lperm[(size_t)a * 64 + (i % 4) * 16 + i / 4] = (uint8_t)ord[i];
     }
 
     // ---- adjoint: 32x32 pixel tiles, CA classes staged per round
@@ -280,62 +466,52 @@ static int configure(Plan &p)
         }
     }
 
-    // device copies of the group tables
-    RT_HIP(hipMalloc(&p.d_gcls, gcls.size() * sizeof(int)));
-    RT_HIP(hipMalloc(&p.d_gwalk, gwalk.size() * sizeof(int)));
-    RT_HIP(hipMemcpy(p.d_gcls, gcls.data(), gcls.size() * sizeof(int), hipMemcpyHostToDevice));
-    RT_HIP(hipMemcpy(p.d_gwalk, gwalk.data(), gwalk.size() * sizeof(int), hipMemcpyHostToDevice));
-    p.bytes += (gcls.size() + gwalk.size()) * sizeof(int);
+    up.add(&p.d_wcls, wcls);
+    up.add(&p.d_groups, p.groups);
+    up.add(&p.d_lanes, lanes);
     if (p.form == RT_FORM_SF) {
-        RT_HIP(hipMalloc(&p.d_gcls_sf, gcls_sf.size() * sizeof(int)));
-        RT_HIP(hipMalloc(&p.d_gwalk_sf, gwalk_sf.size() * sizeof(int)));
-        RT_HIP(hipMemcpy(p.d_gcls_sf, gcls_sf.data(), gcls_sf.size() * sizeof(int), hipMemcpyHostToDevice));
-        RT_HIP(hipMemcpy(p.d_gwalk_sf, gwalk_sf.data(), gwalk_sf.size() * sizeof(int), hipMemcpyHostToDevice));
-        p.bytes += (gcls_sf.size() + gwalk_sf.size()) * sizeof(int);
+        up.add(&p.d_gcls_sf, gcls_sf);
+        up.add(&p.d_gwalk_sf, gwalk_sf);
     }
     return RT_OK;
 }
 
 static void free_plan(Plan &p)
 {
-    for (void *ptr : {(void *)p.d_phi, (void *)p.d_S, (void *)p.d_ccos, (void *)p.d_csin,
-                      (void *)p.d_gcls, (void *)p.d_gwalk, (void *)p.d_lperm, (void *)p.d_gcls_sf, (void *)p.d_gwalk_sf,
-                      (void *)p.d_scr, (void *)p.d_frames, p.d_f16, (void *)p.d_psf,
-                      (void *)p.d_part,
-                      (void *)p.d_red})
+    for (void *ptr : {p.d_tables, (void *)p.d_scr, (void *)p.d_frames, p.d_f16, (void *)p.d_psf,
+                      (void *)p.d_part, (void *)p.d_red})
         if (ptr) (void)hipFree(ptr);
 }
 
-template <class T>
-static int dev_copy(T **dst, const std::vector<T> &src, size_t *bytes)
-{
-    const size_t b = std::max<size_t>(src.size(), 1) * sizeof(T);
-    RT_HIP(hipMalloc(dst, b));
-    if (!src.empty()) RT_HIP(hipMemcpy(*dst, src.data(), src.size() * sizeof(T), hipMemcpyHostToDevice));
-    *bytes += b;
-    return RT_OK;
-}
-
 static int create(const rt_geom *geom, rt_form form, rt_prec prec, const double *phi,
-                  const double *S, Plan &p)
+                  const double *S, int nz_ref, bool adjoint_only, Plan &p)
 {
     p.g = *geom;
+    p.nz_ref = nz_ref;
+    p.adjoint_only = adjoint_only;
     p.form = form;
     p.prec = prec;
     p.n0 = geom->Ntheta / geom->Npi;
     RT_HIP(hipGetDevice(&p.device));
     build_tables(p.g, phi, S, p.T);
-    int rc = configure(p);
+    TableUpload up;
+    int rc = configure(p, up);
     if (rc) return rc;
     std::vector<float> phi32(p.T.phi.begin(), p.T.phi.end()), S32(p.T.S.begin(), p.T.S.end());
-    if ((rc = dev_copy(&p.d_phi, phi32, &p.bytes))) return rc;
-    if ((rc = dev_copy(&p.d_S, S32, &p.bytes))) return rc;
-    if ((rc = dev_copy(&p.d_ccos, p.T.ccos, &p.bytes))) return rc;
-    if ((rc = dev_copy(&p.d_csin, p.T.csin, &p.bytes))) return rc;
-    if ((rc = dev_copy(&p.d_lperm, p.lperm, &p.bytes))) return rc;
-    const size_t scr = std::max<size_t>(plan_scratch_bytes(p.g), 256);
+    const size_t Kp = (size_t)(geom->K + 3) / 4 * 4;
+    std::vector<float> phip((size_t)geom->Ntheta * Kp, 0.f);
+    for (int i = 0; i < geom->Ntheta; ++i)
+        std::copy_n(phi32.begin() + (size_t)i * geom->K, geom->K, phip.begin() + (size_t)i * Kp);
+    up.add(&p.d_phi, phi32);
+    up.add(&p.d_phip, phip);
+    up.add(&p.d_S, S32);
+    up.add(&p.d_ccos, p.T.ccos);
+    up.add(&p.d_csin, p.T.csin);
+    if ((rc = up.upload(&p.d_tables, &p.bytes))) return rc;
+    const size_t scr = std::max<size_t>(adjoint_only ? adjoint_scratch_bytes(p.g) : plan_scratch_bytes(p.g, nz_ref), 256);
     RT_HIP(hipMalloc(&p.d_scr, scr));
     p.bytes += scr;
+    if (adjoint_only) return RT_OK;
     const size_t frb = std::max<size_t>(n4_of(p.g), 1) * sizeof(float);
     RT_HIP(hipMalloc(&p.d_frames, frb));
     p.bytes += frb;
@@ -382,6 +558,31 @@ int pick_form(const rt_geom *geom, rt_form *form, rt_prec *prec)
         return fail(RT_E_ARG, "the synthesise-first form is built with the BF16 contraction only");
     if (*form == RT_FORM_SF && geom->Npi > 32)
         return fail(RT_E_SHAPE, "the synthesise-first form needs Npi <= 32 (got %d)", geom->Npi);
+    return RT_OK;
+}
+
+int plan_create(const rt_geom *geom, rt_form form, rt_prec prec, const double *phi, const double *S,
+                int nz_ref, bool adjoint_only, rt_plan **out)
+{
+    if (!out) return fail(RT_E_ARG, "out is NULL");
+    *out = nullptr;
+    int rc = pick_form(geom, &form, &prec);
+    if (rc) return rc;
+    if (phi)
+        for (size_t e = 0; e < (size_t)geom->Ntheta * geom->K; ++e)
+            if (!std::isfinite(phi[e])) return fail(RT_E_ARG, "phi has a non-finite entry");
+    if (S)
+        for (size_t e = 0; e < (size_t)geom->Nt * geom->K; ++e)
+            if (!std::isfinite(S[e])) return fail(RT_E_ARG, "S has a non-finite entry");
+    rt_plan *p = new (std::nothrow) rt_plan();
+    if (!p) return fail(RT_E_OOM, "host allocation failed");
+    rc = create(geom, form, prec, phi, S, nz_ref, adjoint_only, p->impl);
+    if (rc) {
+        free_plan(p->impl);
+        delete p;
+        return rc;
+    }
+    *out = p;
     return RT_OK;
 }
 
@@ -434,26 +635,7 @@ extern "C" int rt_plan_form(const rt_plan *p, rt_form *form, rt_prec *prec)
 extern "C" int rt_plan_create(const rt_geom *geom, rt_form form, rt_prec prec, const double *phi,
                               const double *S, rt_plan **out)
 {
-    if (!out) return fail(RT_E_ARG, "out is NULL");
-    *out = nullptr;
-    int rc = pick_form(geom, &form, &prec);
-    if (rc) return rc;
-    if (phi)
-        for (size_t e = 0; e < (size_t)geom->Ntheta * geom->K; ++e)
-            if (!std::isfinite(phi[e])) return fail(RT_E_ARG, "phi has a non-finite entry");
-    if (S)
-        for (size_t e = 0; e < (size_t)geom->Nt * geom->K; ++e)
-            if (!std::isfinite(S[e])) return fail(RT_E_ARG, "S has a non-finite entry");
-    rt_plan *p = new (std::nothrow) rt_plan();
-    if (!p) return fail(RT_E_OOM, "host allocation failed");
-    rc = create(geom, form, prec, phi, S, p->impl);
-    if (rc) {
-        free_plan(p->impl);
-        delete p;
-        return rc;
-    }
-    *out = p;
-    return RT_OK;
+    return plan_create(geom, form, prec, phi, S, geom ? geom->Nz : 0, false, out);
 }
 
 extern "C" void rt_plan_destroy(rt_plan *p)

@@ -9,24 +9,21 @@
 //          out_k = static back-projection of g~(.,.,.,k) over theta0_a
 //
 // Kernels
-//   k_project      ray-driven projection of a chunk of KC channels for a
-//                  group of angle classes of one walk direction; each line
-//                  (row or column) of the slice is staged once in LDS and
-//                  shared by all rays of the group.
+//   k_project      ray-driven projection of up to 16 channel columns for the
+//                  rays of several angle classes of one walk direction; each
+//                  line (row or column) of the slice is staged once in LDS and
+//                  shared by all rays of the workgroup.
 //   k_contract     sum over k with the s-flip; optionally fused with the
 //                  h1 prox of Fig. 2 and an FP64 partial of |R f~ - g|^2.
 //   k_fold         the fold-sum g -> g~.
 // The back-projection of g~ is in backproject.hip.
-// Ray positions are computed in FP64 (the rate of FP64 FMA on CDNA4 equals
-// that of unpacked FP32), weights and accumulation in FP32.
+// Ray positions start in FP64 and are stepped in 32.32 fixed point; weights and
+// accumulation in FP32.
 #include "common.h"
 #include "internal.h"
 
 namespace rt {
 namespace {
-
-constexpr int FT = 512;   // threads of a projection workgroup (8 wave64)
-constexpr int G0 = LINE_GUARD;   // zero guard positions at each end of a staged line
 
 // clamp to [0, hi] in one v_med3_i32 (the compiler forms it only for
 // constant bounds); hi is uniform and stays in an SGPR
@@ -37,99 +34,14 @@ __device__ inline int clamp0_i32(int x, int hi)
     return r;
 }
 
-// clamp to [lo, hi] in one v_med3_i32, both bounds in VGPRs
-__device__ inline int clamp_i32(int x, int lo, int hi)
-{
-    int r;
-    asm("v_med3_i32 %0, %1, %2, %3" : "=v"(r) : "v"(x), "v"(lo), "v"(hi));
-    return r;
-}
-
-// Staging of one line (row or column of a slice, KC channels, positions
-// 0..N-1 into LDS slots G0..N+G0-1; slots 0..G0-1 and N+G0..N+2G0-1 stay zero)
-// through registers: the loads of line l+1 are issued before the taps of line
-// l are summed, and written to the other LDS buffer afterwards (or, with one
-// buffer, over line l once its taps are done).  PF float4 per thread cover a
-// whole line (N * KC <= 4 * PF * NTH).  VEC = 4: float4 loads (K % 4 == 0);
-// VEC = 1: scalar loads of the same PF*4 values.  EXACT: the PF float4 of the
-// NTH threads are exactly the line's N * KC values and every channel of the
-// chunk exists (N * KC == 4 * PF * NTH, K % KC == 0), so the loads need no
-// masks; element j of a thread is then at offset off + j * inc of the line
-// (32-bit: at most N * N * K < 2^31 floats) and at LDS float dst + j * dinc.
-template <int KC, int PF, int VEC, int NTH>
-struct LinePrefetch {
-    float4 r[PF];
-    // EXACT: the offsets of element 0 of this thread (line float, LDS float)
-    // and their steps between elements (uniform)
-    struct Exact {
-        int off, inc, dst, dinc;
-    };
-    static __device__ inline Exact exact(size_t pstep)
-    {
-        constexpr int NQ = KC / 4;
-        const int pos = threadIdx.x / NQ, kq = threadIdx.x % NQ;
-        return {pos * (int)pstep + 4 * kq, (NTH / NQ) * (int)pstep,
-                (pos + G0) * line_stride(KC) + 4 * kq, (NTH / NQ) * line_stride(KC)};
-    }
-    __device__ inline void load(const float *__restrict__ src, size_t pstep, int N, int k0, int K,
-                                const Exact &)
-    {
-        if constexpr (VEC == 4) {
-            constexpr int NQ = KC / 4;
-#pragma unroll
-            for (int j = 0; j < PF; ++j) {
-                const int e = threadIdx.x + NTH * j;
-                const int pos = e / NQ, kq = e % NQ;
-                r[j] = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (pos < N && k0 + 4 * kq < K) r[j] = *(const float4 *)(src + (size_t)pos * pstep + 4 * kq);
-            }
-        } else {
-#pragma unroll
-            for (int j = 0; j < PF; ++j) {
-                float v[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int e = threadIdx.x + NTH * (4 * j + i);
-                    const int pos = e / KC, kk = e % KC;
-                    v[i] = (pos < N && k0 + kk < K) ? src[(size_t)pos * pstep + kk] : 0.f;
-                }
-                r[j] = make_float4(v[0], v[1], v[2], v[3]);
-            }
-        }
-    }
-    __device__ inline void store(float *__restrict__ buf, int N, const Exact &) const
-    {
-        constexpr int stride = line_stride(KC);
-        if constexpr (VEC == 4) {
-            constexpr int NQ = KC / 4;
-#pragma unroll
-            for (int j = 0; j < PF; ++j) {
-                const int e = threadIdx.x + NTH * j;
-                const int pos = e / NQ, kq = e % NQ;
-                if (pos < N) *(float4 *)(buf + (pos + G0) * stride + 4 * kq) = r[j];
-            }
-        } else {
-#pragma unroll
-            for (int j = 0; j < PF; ++j) {
-                const float v[4] = {r[j].x, r[j].y, r[j].z, r[j].w};
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int e = threadIdx.x + NTH * (4 * j + i);
-                    const int pos = e / KC, kk = e % KC;
-                    if (pos < N) buf[(pos + G0) * stride + kk] = v[i];
-                }
-            }
-        }
-    }
-};
-
 // What the projection does with its sums P(a,z,b,k): store them (EPI_P), or,
-// when one workgroup holds all K channels, contract them with Phi over the
-// Npi half-turns with the s-flip (Sec. 4, eq. radapr and the pi-periodicity)
-// and store g (EPI_G) or apply the h1 prox of Fig. 2 step 3 (EPI_PROX).
+// when one workgroup holds all K channels of its slices and all lines,
+// contract them with Phi over the Npi half-turns with the s-flip (Sec. 4, eq.
+// radapr and the pi-periodicity) and store g (EPI_G) or apply the h1 prox of
+// Fig. 2 step 3 (EPI_PROX).
 enum { EPI_P = 0, EPI_G = 1, EPI_PROX = 2 };
 struct FwdEpi {
-    const float *phi;     // [Ntheta][K]
+    const float *phi;     // [Ntheta][4 K4], channels K.. zero
     float *out;           // g (EPI_G) or h1 (EPI_PROX)
     const float *gdata;   // measured sinogram (EPI_PROX)
     double *part;         // per-workgroup FP64 sum of (R f~ - g)^2, or NULL
@@ -137,62 +49,112 @@ struct FwdEpi {
     int mode, n0, Npi;
 };
 
-// Joseph's ray-driven projection of KC channels of slice z for the rays
-// (class, bin) of one group; P(a,z,b,k0..k0+KC) = sum over lines of the
-// linear interpolation between the two positions around the ray, times the
-// line spacing along the ray 1/c.
-// The ray a lane takes: its index pr in the tile, with the bin offset within
-// the aligned block of 64 (one wave, one class when BT is a multiple of 64)
-// reordered by the class's lane map when there is one.
-__device__ inline int fwd_ray(int pr, int a, const unsigned char *__restrict__ lperm)
+// Work split of k_project (host: RayCfg).
+struct RayArgs {
+    int N, Nz, Ns, K, K4;      // K4 = channel quads per slice
+    int ngroups, NLP;          // ray groups, parts of the lines
+    unsigned nblocks;
+};
+
+typedef float v4 __attribute__((ext_vector_type(4)));
+
+__device__ inline float dot4(float4 w, v4 x)
 {
-    return lperm && a >= 0 ? (pr & ~63) | (int)lperm[a * 64 + (pr & 63)] : pr;
+    return fmaf(w.w, x[3], fmaf(w.z, x[2], fmaf(w.y, x[1], w.x * x[0])));
 }
 
-template <int KC, int PPT, int PF, int VEC, bool TL, int NTH, bool EXACT>
+// Joseph's ray-driven projection: P(a,z,b,k) = sum over the lines of slice z
+// (rows or columns, whichever the ray crosses once each) of the linear
+// interpolation between the two positions around the ray, times the line
+// spacing along the ray 1/c.
+//
+// Columns.  The Nz * K4 channel quads of all slices form one list; a
+// workgroup takes NQ consecutive ones, so K = 16 is one slice per workgroup
+// and K = 8 two, and a position of a staged line is NQ * 16 bytes in LDS.
+// Rays.  A workgroup takes one RayGroup: a tile of bins (blocks of 64) of
+// neighbouring classes of one walk direction, PPT blocks per wave.  Lines no
+// ray of a block crosses are skipped (a wave-uniform interval per block): 9%
+// of the tap work at Ns = N, more where the detector is wider than the slice.
+// Lines.  Only the window of W positions that the group's rays reach on a
+// line is staged; it moves with the line along the group's middle slope
+// (positions outside the slice are read as zeros by the buffer bounds).
+// Two bin blocks of 16 classes need about 250 of 512 positions, 270 of
+// 1024, 380 of 2048: a line's read and LDS traffic per ray is 8 to 13 bytes
+// per channel quad column instead of 16 to 64 for whole lines, and 4 or 2
+// lines fit a stage.  Stages are double buffered, with the loads a stage
+// further ahead in registers; one barrier per stage.  With NLP > 1 a
+// workgroup walks one of NLP parts of the lines and stores partial sums
+// (EPI_P) that k_contract adds in part order.
+//
+// LDS.  A ds_read_b128 is served in four groups of 16 lanes ({0-3, 12-15,
+// 20-27}, {4-11, 16-19, 28-31}, and the same + 32), each over 16 units of 16
+// bytes, at 4.3 cycles per CU when no two lanes of a group hit different rows
+// of one unit.  Rows are unpadded; lane l reads the quads of a row in the
+// order quad = kappa ^ rho, rho = (l >> 3) & 3 (NQ = 4), so the four lane
+// quads of a group read four different column quads, and the lane tables give
+// every lane quad four rays whose positions are about 0, 1, 2, 3 modulo 4
+// apart.  Sampled over the angles that is 5.1 cycles per read, against 5.9 for
+// rows padded to 80 bytes and lanes ordered modulo 16, and a line takes 20%
+// less LDS.
+//
+// Staging (STG).  STG_LINE: the quads are of one slice; each line is a buffer
+// whose bounds give the zeros outside it, and the loads go to LDS directly.
+// STG_LIST: the quads are of several slices (K4 is no multiple of NQ); one
+// buffer over them, lanes outside get an offset past its end.  STG_REGS: fewer
+// than 4 channels, or offsets of more than 32 bits; masked loads through
+// registers.  Where K is no multiple of 4, a slice's last quad is staged as
+// its last four channels, all of them real; the sums are shifted into place
+// at the end.
+enum { STG_LINE = 0, STG_LIST = 1, STG_REGS = 2 };
+template <int NQ, int PPT, int PF, bool TL, int NTH, int STG>
 __global__ __launch_bounds__(NTH) void k_project(
-    const float *__restrict__ f, float *__restrict__ P, const int *__restrict__ gcls,
-    const int *__restrict__ gwalk, const unsigned char *__restrict__ lperm,
-    const double *__restrict__ ccos, const double *__restrict__ csin, int N, int Nz, int Ns,
-    int K, int A, int ngroups, int BT, int nbt, int nkc, int nbuf, unsigned nblocks, FwdEpi E)
+    const float *__restrict__ f, float *P, const RayGroup *__restrict__ groups,
+    const int *__restrict__ wcls, const unsigned char *__restrict__ rlane, const double *__restrict__ ccos,
+    const double *__restrict__ csin, RayArgs A, FwdEpi E)
 {
-    constexpr int stride = line_stride(KC);
-    extern __shared__ float lines[];   // nbuf buffers x [N + 2 G0 slots][stride], slot = position + G0
-    __shared__ double sh[NTH / 64];
-    unsigned lid = xcd_remap(blockIdx.x, nblocks);
-    const int bt = lid % nbt;
-    lid /= nbt;
-    const int kc = lid % nkc;
-    lid /= nkc;
-    const int grp = lid % ngroups;
-    const int z = lid / ngroups;
-    const int tid = threadIdx.x;
-    const int walk = gwalk[grp];
-    const int k0 = kc * KC;
+    constexpr int NW = NTH / 64;
+    constexpr int SH = NQ == 4 ? 6 : NQ == 2 ? 5 : 4;   // log2 of a row's bytes
+    constexpr int RPJ = NTH / NQ;                       // rows one float4 per thread covers
+    extern __shared__ __align__(64) char smem[];        // [2][NLS][W rows][NQ] float4
+    __shared__ double sh[NW];
+    const int N = A.N, Ns = A.Ns, K = A.K, K4 = A.K4;
+    unsigned lid = xcd_remap(blockIdx.x, A.nblocks);
+    const int grp = lid % A.ngroups;
+    lid /= A.ngroups;
+    const int lp = lid % A.NLP, cg = lid / A.NLP;
+    const int lbeg = (int)((long)lp * N / A.NLP), lend = (int)((long)(lp + 1) * N / A.NLP);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const RayGroup G = groups[grp];
+    const int walk = G.walk, W = G.W;
     const double hN = 0.5 * (double)(N - 1), hS = 0.5 * (double)(Ns - 1);
-    const int bufsz = (N + 2 * G0) * stride;
-    if constexpr (EXACT) nbuf = 2;   // planned so (a 512-position line of 16 channels)
+    // a line takes PPL float4 per thread, a stage NLS = PF / PPL lines (fewer
+    // in a short part)
+    const int sh_l = W <= RPJ ? 0 : W <= 2 * RPJ ? 1 : W <= 4 * RPJ ? 2 : 3;   // log2 PPL
+    const int NLS = min(PF >> sh_l, lend - lbeg);
+    const int lineb = W << SH, bufb = NLS * lineb;
 
-    // Ray positions along the lines in 32.32 fixed point: u(l) = u(0) + l s,
-    // stepped by an exact integer add per line, so u(l) carries the rounding
-    // of u(0) and of l s alone (below 2^-32 (1 + l) positions).  Its integer
-    // part gives the left tap (with EXACT, U holds u + G0, so that part is
-    // the tap's LDS slot itself), its fraction the interpolation weight.  A
-    // ray outside the tile has 1/c = 0; a position before the line or past
-    // it is clamped into the zero guard slots.  The unmasked path measured
-    // faster with the offset inside U, one 64-bit add per line and the
-    // upper bound in an SGPR; the masked path (block sums over 1024
-    // positions) measured 3% slower with them and keeps the plain form.
+    // ---- rays.  Positions along the lines in 32.32 fixed point: u at the
+    // block's first line from FP64, stepped by the slope with an exact
+    // integer add per line, so u(l) carries the rounding of its start and of
+    // l s alone (below 2^-32 (1 + l) positions).  The integer part less the
+    // window's first position is the LDS row of the left tap, the fraction
+    // the weight.  The row is clamped to the window, which only moves lanes
+    // without a ray (1/c = 0), or, where the window is the whole line with
+    // its guard positions, rays off the slice.
     long long U[PPT], S[PPT];
     float invc[PPT], sfr[PPT];
+    int cl[PPT], bin[PPT], jb[PPT], je[PPT];   // class (-1: none), bin, lines [jb, je) of the block
 #pragma unroll
     for (int j = 0; j < PPT; ++j) {
-        const int slot = (tid + NTH * j) / BT;
-        const int a = slot < A ? gcls[grp * A + slot] : -1;
-        const int b = bt * BT + fwd_ray(tid + NTH * j, a, lperm) % BT;
-        double base = -1.0e6, slope = 0.0;
+        const int n = j * NW + wave;
+        const int a = n < G.ncls * G.bbt ? wcls[G.cls0 + n / G.bbt] : -1;
+        const int b = a >= 0 ? (G.bb0 + n % G.bbt) * 64 + (int)rlane[a * 64 + lane] : Ns;
+        cl[j] = a;
+        bin[j] = b;
+        double base = -1.0e6, slope = 0.0, lo = 2.0e6, hi = -2.0e6;
         invc[j] = 0.f;
-        if (a >= 0 && b < Ns) {
+        if (b < Ns) {
             const double cs = ccos[a], sn = csin[a], sb = (double)b - hS;
             if (walk == 0) {   // |cos| >= |sin|: the ray crosses every row once
                 base = sb / cs + hN;
@@ -203,255 +165,268 @@ __global__ __launch_bounds__(NTH) void k_project(
                 slope = -cs / sn;
                 invc[j] = (float)(1.0 / fabs(sn));
             }
+            // lines with -1 <= u < N, a line to spare at each end
+            const double u0 = fma(-hN, slope, base);
+            if (fabs(slope) * (double)N > 1.0e-3) {
+                const double x = (-1.0 - u0) / slope, y = ((double)N - u0) / slope;
+                lo = fmin(x, y) - 1.0;
+                hi = fmax(x, y) + 2.0;
+            } else if (u0 > -2.0 && u0 < (double)N + 1.0) {
+                lo = -1.0;
+                hi = (double)N;
+            }
         }
-        const double u0 = fmin(fmax(fma(-hN, slope, base), -1.0e6), 1.0e6);   // line 0
-        U[j] = (long long)llrint(u0 * 4294967296.0);
-        if constexpr (EXACT) {
-            U[j] += (long long)G0 << 32;
-            asm volatile("" : "+v"(U[j]));   // keeps the offset inside U (else it is re-added per line)
+        int l0 = (int)fmin(fmax(lo, (double)lbeg), (double)lend);
+        int l1 = (int)fmin(fmax(hi, (double)lbeg), (double)lend);
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            l0 = min(l0, __shfl_xor(l0, o, 64));
+            l1 = max(l1, __shfl_xor(l1, o, 64));
         }
+        jb[j] = __builtin_amdgcn_readfirstlane(l0);
+        je[j] = __builtin_amdgcn_readfirstlane(l1);
+        const double u = fmin(fmax(fma((double)jb[j] - hN, slope, base), -1.0e6), 1.0e6);
+        U[j] = (long long)llrint(u * 4294967296.0);
         S[j] = (long long)llrint(slope * 4294967296.0);
         sfr[j] = invc[j] * 2.3283064365386963e-10f;   // fraction bits -> weight: 2^-32 / c
     }
 
-    // TL (two-level sums, planned for N > 512): the taps of LB consecutive
-    // lines go into blk, which is added into acc every LB lines, so that the
-    // FP32 rounding of a long ray grows with sqrt(LB) + sqrt(N / LB)
-    // additions instead of sqrt(N)
-    constexpr int LB = 32;
-    float acc[PPT][KC], blk[TL ? PPT : 1][KC];
+    float acc[PPT][NQ][4];
 #pragma unroll
     for (int j = 0; j < PPT; ++j)
 #pragma unroll
-        for (int k = 0; k < KC; ++k) acc[j][k] = 0.f;
+        for (int q = 0; q < NQ; ++q)
 #pragma unroll
-    for (int j = 0; j < (TL ? PPT : 1); ++j)
+            for (int t = 0; t < 4; ++t) acc[j][q][t] = 0.f;
+
+    // ---- staging: float4 j of a thread is quad tid % NQ of row tid / NQ +
+    // RPJ (j mod PPL) of line j / PPL of the stage
+    const unsigned lstep = (walk == 0 ? N * K : K) * 4u;   // next line (bytes)
+    const unsigned pstep = (walk == 0 ? K : N * K) * 4u;   // next position
+    const int z0 = cg * NQ / K4;
+    const int cq = tid % NQ, p0 = tid / NQ, gq = cg * NQ + cq;
+    const int zq = gq / K4 - z0, kq = gq % K4;
+    const bool qok = gq < A.Nz * K4;             // a quad of the list
+    const int kr = K & 3;                        // channels of a slice's last quad (0: 4)
+    const unsigned coff = min(4 * kq, max(K - 4, 0)) * 4u;   // channel offset of the load
+    const unsigned goff = coff + p0 * pstep + (STG == STG_LIST ? zq * (unsigned)N * N * K * 4u : 0u);
+    const char *fz = (const char *)(f + (size_t)z0 * N * N * K);
+    typedef float v4u __attribute__((ext_vector_type(4), aligned(4)));
+    typedef int i4 __attribute__((ext_vector_type(4)));
+    v4 r[STG == STG_REGS ? PF : 1];
+    const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) char *)smem;
+    auto first_line = [&](int st) { return min(lbeg + st * NLS, lend - NLS); };
+    auto wfirst = [&](int l) { return (int)((G.wl0 + l * G.sw) >> 32); };   // window's first position
+    // stage st into registers (STG_REGS) or into buffer st & 1: global to LDS
+    // copies of 16 bytes per lane to consecutive LDS addresses.  They are
+    // issued from inline assembly, so that the compiler, which cannot tell the
+    // two buffers apart, adds no wait for them before the tap reads; the wait
+    // is the vmcnt(0) before the barrier that ends the stage.
+    auto load = [&](int st) {
+        const int l0 = first_line(st);
+        const unsigned buf = lds0 + (st & 1) * bufb + wave * 1024;
 #pragma unroll
-        for (int k = 0; k < KC; ++k) blk[j][k] = 0.f;
-
-    for (int e = tid; e < nbuf * 2 * G0 * stride; e += NTH) {   // zero the guard slots
-        const int b = e / (2 * G0 * stride), w = e % (2 * G0 * stride);
-        const int row = w / stride;
-        lines[b * bufsz + (row < G0 ? row : N + row) * stride + w % stride] = 0.f;
-    }
-
-    const size_t lstep = walk == 0 ? (size_t)N * K : (size_t)K;   // next line
-    const size_t pstep = walk == 0 ? (size_t)K : (size_t)N * K;   // next position
-    const float *src = f + (size_t)z * N * N * K + k0;
-
-    // staging registers: PF float4 per thread, or with EXACT two named float4
-    // at the offsets of Stage::exact (an indexed array there is placed in
-    // scratch memory by the compiler)
-    using Stage = LinePrefetch<KC, PF, VEC, NTH>;
-    Stage pf;
-    const typename Stage::Exact ex = EXACT ? Stage::exact(pstep) : typename Stage::Exact{0, 0, 0, 0};
-    float4 xa, xb;
-    auto stage_load = [&]() {
-        if constexpr (EXACT) {
-            static_assert(PF == 2, "the unmasked staging is planned with 2 float4 per thread");
-            xa = *(const float4 *)(src + ex.off);
-            xb = *(const float4 *)(src + ex.off + ex.inc);
-        } else {
-            pf.load(src, pstep, N, k0, K, ex);
+        for (int j = 0; j < PF; ++j) {
+            const int ln = j >> sh_l, row = (j & ((1 << sh_l) - 1)) * RPJ;
+            if (ln >= NLS) break;
+            const int l = l0 + ln, w0 = wfirst(l) + row;   // uniform
+            if constexpr (STG == STG_REGS) {
+                const int pos = w0 + p0;
+                const char *src = fz + (qok ? (size_t)zq * N * N * K * 4 : 0) + (size_t)l * lstep +
+                                  (size_t)(unsigned)max(pos, 0) * pstep + coff;
+                r[j] = v4{0.f, 0.f, 0.f, 0.f};
+                if (qok && (unsigned)pos < (unsigned)N) {
+                    if (K > 3) {
+                        r[j] = *(const v4u *)src;
+                    } else {
+#pragma unroll
+                        for (int t = 0; t < 3; ++t)
+                            if (t < K) r[j][t] = ((const float *)src)[t];
+                    }
+                }
+            } else {
+                // STG_LINE: the bytes of the line up to its last position's
+                // end; a position before the line (the offset wraps) or past
+                // it is out of bounds
+                const char *base = fz + (STG == STG_LINE ? (size_t)l * lstep : 0);
+                const unsigned end = STG == STG_LINE ? (N - 1) * pstep + K * 4u
+                                                     : (unsigned)min(A.Nz - z0, NQ) * (unsigned)N * N * K * 4u;
+                const i4 rs{(int)(unsigned)(size_t)base, (int)(((size_t)base >> 32) & 0xffff), (int)end, 0x00020000};
+                unsigned off = goff + (unsigned)w0 * pstep;
+                if constexpr (STG == STG_LIST) {
+                    const bool in = qok && (unsigned)(w0 + p0) < (unsigned)N;
+                    off = in ? off + l * lstep : 0xffffff00u;
+                }
+                if (p0 + row < W)
+                    asm volatile("buffer_load_dwordx4 %0, %1, 0 offen lds"
+                                 :: "v"(off), "s"(rs), "{m0}"(__builtin_amdgcn_readfirstlane(buf + ln * lineb + (row << SH)))
+                                 : "memory");
+            }
         }
     };
-    auto stage_store = [&](float *buf) {
-        if constexpr (EXACT) {
-            *(float4 *)(buf + ex.dst) = xa;
-            *(float4 *)(buf + ex.dst + ex.dinc) = xb;
-        } else {
-            pf.store(buf, N, ex);
+    auto store = [&](int st) {   // STG_REGS
+        char *dst = smem + (st & 1) * bufb + (tid << 4);
+#pragma unroll
+        for (int j = 0; j < PF; ++j) {
+            const int ln = j >> sh_l, row = (j & ((1 << sh_l) - 1)) * RPJ;
+            if (ln >= NLS) break;
+            if (p0 + row < W) *(v4 *)(dst + ln * lineb + (row << SH)) = r[STG == STG_REGS ? j : 0];
         }
     };
-    // the taps of every ray on one staged line
-    auto line_taps = [&](const float *line) {
+
+    typedef __attribute__((address_space(3))) const v4 lds_v4;
+    const unsigned rho = (NQ == 4 ? (lane >> 3) & 3 : NQ == 2 ? (lane >> 4) & 1 : 0) * 16;
+    // block j's rays on the staged line at byte offset lb (its low bits hold rho)
+    auto taps = [&](int j, unsigned lb, int w0l) {
+        const int q0 = (int)(U[j] >> 32);
+        const float fr = (float)(unsigned)U[j];
+        U[j] += S[j];
+        asm volatile("" : "+v"(U[j]));   // one 64-bit add per line, not U(0) + l s rebuilt
+        const float w1 = fr * sfr[j];
+        const float w0 = invc[j] - w1;
+        const unsigned t0 = ((unsigned)clamp0_i32(q0 - w0l, W - 2) << SH) + lb;
+        v4 x[NQ], y[NQ];
+        //ORD-BEGIN
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) x[q] = *(lds_v4 *)(size_t)(t0 ^ (16u * q));
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) y[q] = *(lds_v4 *)(size_t)((t0 ^ (16u * q)) + (1u << SH));
+        __builtin_amdgcn_sched_barrier(0);   // all reads are issued before the first FMA waits
+#pragma unroll
+        for (int q = 0; q < NQ; ++q)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) acc[j][q][t] = fmaf(w0, x[q][t], acc[j][q][t]);
+#pragma unroll
+        for (int q = 0; q < NQ; ++q)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) acc[j][q][t] = fmaf(w1, y[q][t], acc[j][q][t]);
+        //ORD-END
+#pragma unroll
+        for (int q = 0; q < NQ; ++q)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) asm volatile("" : "+v"(acc[j][q][t])::"memory");
+    };
+
+    // acc[j][q] holds column quad q ^ (rho / 16) of block j
+    const int rq = (int)rho / 16, Kp = 4 * K4, nq = A.Nz * K4;
+    // quad q's sums with a ragged last quad's kr channels moved to its front
+    auto sums = [&](int j, int q) {
+        v4 x{acc[j][q][0], acc[j][q][1], acc[j][q][2], acc[j][q][3]};
+        if (kr && K > 4 && (cg * NQ + (q ^ rq)) % K4 == K4 - 1)
+            x = v4{kr == 1 ? x[3] : kr == 2 ? x[2] : x[1], kr == 1 ? 0.f : kr == 2 ? x[3] : x[2],
+                   kr == 3 ? x[3] : 0.f, 0.f};
+        return x;
+    };
+    auto psum = [&](int j, int g) {   // where P keeps column quad g of block j's ray
+        return (v4 *)(P + ((((size_t)lp * E.n0 + cl[j]) * A.Nz + g / K4) * Ns + bin[j]) * Kp + 4 * (g % K4));
+    };
+    // TL (two-level sums, planned for N > 512): the taps of LB consecutive
+    // lines are summed in registers and then added to P, so that the FP32
+    // rounding of a long ray grows with sqrt(LB) + sqrt(N / LB) additions
+    // instead of sqrt(N).  A second set of sums in registers would not fit
+    // 16 waves per CU; P costs 6% of the line traffic.  All reads of P are
+    // issued before the first is used.
+    constexpr int LB = 64;
+    bool first = true;
+    auto flush = [&]() {
 #pragma unroll
         for (int j = 0; j < PPT; ++j) {
-            const int q0 = (int)(U[j] >> 32);
-            const float fr = (float)(unsigned)U[j];
-            U[j] += S[j];
-            if constexpr (EXACT)
-                asm volatile("" : "+v"(U[j]));   // one 64-bit add per line, not U(0) + l s rebuilt
-            const float w1 = fr * sfr[j];
-            const float w0 = invc[j] - w1;
-            const int slot = EXACT ? clamp0_i32(q0, N + G0) : clamp_i32(q0, -G0, N) + G0;
-            const float *t0 = line + __umul24((unsigned)slot, (unsigned)stride);
-            // the taps of this ray into s (the ray's sums or its block sums);
-            // its FMAs finish before the next ray's tap loads are issued:
-            // hoisting the loads of all rays needs 32 VGPRs per ray and spills
-            // The left tap's channels are read (and summed) before the right
-            // tap's: a wave's consecutive LDS reads then stay on one staged
-            // row, which measured 7% faster than alternating the two rows.
-            // Each channel still adds w0 x0, then w1 x1.
-            auto taps = [&](float (&sr)[KC]) {
+            v4 x[NQ];
+            const bool ray = cl[j] >= 0 && bin[j] < Ns;
 #pragma unroll
-                for (int k = 0; k < KC; k += 4) {
-                    const float4 x0 = *(const float4 *)(t0 + k);
-                    sr[k + 0] = fmaf(w0, x0.x, sr[k + 0]);
-                    sr[k + 1] = fmaf(w0, x0.y, sr[k + 1]);
-                    sr[k + 2] = fmaf(w0, x0.z, sr[k + 2]);
-                    sr[k + 3] = fmaf(w0, x0.w, sr[k + 3]);
-                }
+            for (int q = 0; q < NQ; ++q) {
+                x[q] = v4{0.f, 0.f, 0.f, 0.f};
+                if (ray && !first && cg * NQ + (q ^ rq) < nq) x[q] = *psum(j, cg * NQ + (q ^ rq));
+            }
 #pragma unroll
-                for (int k = 0; k < KC; k += 4) {
-                    const float4 x1 = *(const float4 *)(t0 + stride + k);
-                    sr[k + 0] = fmaf(w1, x1.x, sr[k + 0]);
-                    sr[k + 1] = fmaf(w1, x1.y, sr[k + 1]);
-                    sr[k + 2] = fmaf(w1, x1.z, sr[k + 2]);
-                    sr[k + 3] = fmaf(w1, x1.w, sr[k + 3]);
-                }
+            for (int q = 0; q < NQ; ++q) {
+                x[q] += sums(j, q);
+                if (ray && cg * NQ + (q ^ rq) < nq) *psum(j, cg * NQ + (q ^ rq)) = x[q];
 #pragma unroll
-                for (int k = 0; k < KC; ++k) asm volatile("" : "+v"(sr[k])::"memory");
-            };
-            if constexpr (TL) taps(blk[TL ? j : 0]);
-            else taps(acc[j]);
+                for (int t = 0; t < 4; ++t) acc[j][q][t] = 0.f;
+            }
         }
+        first = false;
     };
 
-    if constexpr (EXACT) {
-        // Loads run two lines ahead of the taps (a line's loads have two
-        // lines' taps to arrive; one line was too short at one workgroup per
-        // CU): two register sets, A and B, alternate over line pairs, and the
-        // two LDS buffers alternate as before.  At the taps of line l, line
-        // l+1 waits in registers and line l+2 is being loaded.
-        static_assert(!TL, "the unmasked staging is planned for N = 512, without block sums");
-        constexpr int NL = 512;
-        constexpr int bsz = (NL + 2 * G0) * stride;
-        // Buffer loads over the slice: the thread's two offsets stay in
-        // VGPRs and the line's offset goes in an SGPR, so a load costs no
-        // vector address arithmetic.  Every offset is inside the slice
-        // (line < NL, element offsets as in LinePrefetch::exact).
-        typedef unsigned int v4u __attribute__((ext_vector_type(4)));
-        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-            (void *)src, (short)0, (int)(((size_t)N * N * K - k0) * sizeof(float)), 0x00020000);
-        const int vo0 = ex.off * (int)sizeof(float), vo1 = (ex.off + ex.inc) * (int)sizeof(float);
-        const int lsb = (int)(lstep * sizeof(float));   // bytes per line, < 2^31 / NL
-        v4u ra, rb, rc, rd;
-        auto ldA = [&](int ln) {
-            ra = __builtin_amdgcn_raw_buffer_load_b128(rs, vo0, ln * lsb, 0);
-            rb = __builtin_amdgcn_raw_buffer_load_b128(rs, vo1, ln * lsb, 0);
-        };
-        auto ldB = [&](int ln) {
-            rc = __builtin_amdgcn_raw_buffer_load_b128(rs, vo0, ln * lsb, 0);
-            rd = __builtin_amdgcn_raw_buffer_load_b128(rs, vo1, ln * lsb, 0);
-        };
-        auto stA = [&](float *buf) {
-            *(v4u *)(buf + ex.dst) = ra;
-            *(v4u *)(buf + ex.dst + ex.dinc) = rb;
-        };
-        auto stB = [&](float *buf) {
-            *(v4u *)(buf + ex.dst) = rc;
-            *(v4u *)(buf + ex.dst + ex.dinc) = rd;
-        };
-        ldA(0);
-        stA(lines);
-        ldB(1);
-        __syncthreads();
-        // The loads and stores are unconditional (past the end they repeat
-        // the last line into a buffer no one reads again): a conditional
-        // store would let the compiler sink its loads next to it, and a
-        // conditional load would make it wait for every load in flight.
-        for (int l = 0; l < NL; l += 2) {
-            // line l in buffer 0, line l+1 in B
-            ldA(min(l + 2, NL - 1));
-            line_taps(lines);
-            stB(lines + bsz);
-            __syncthreads();
-            // line l+1 in buffer 1, line l+2 in A
-            ldB(min(l + 3, NL - 1));
-            line_taps(lines + bsz);
-            stA(lines);
-            __syncthreads();
-        }
+    // Stage st + 1 is on its way during stage st, into the buffer that stage
+    // st - 1 has left.  (STG_REGS: at the top of stage st the registers hold
+    // stage st + 1 and are refilled with stage st + 2.)
+    const int nst = (lend - lbeg + NLS - 1) / NLS;
+    load(0);
+    if constexpr (STG == STG_REGS) {
+        store(0);
+        load(min(1, nst - 1));
     } else {
-    stage_load();
-    stage_store(lines);
-    __syncthreads();
-    for (int l = 0; l < N; ++l) {
-        const bool more = l + 1 < N;
-        if (more) {
-            src += lstep;
-            stage_load();
-        }
-        line_taps(lines + (nbuf == 2 ? (l & 1) * bufsz : 0));
-        if constexpr (TL) {
-            if ((l + 1) % LB == 0 || !more) {
-#pragma unroll
-                for (int j = 0; j < PPT; ++j)
-#pragma unroll
-                    for (int k = 0; k < KC; ++k) {
-                        acc[j][k] += blk[TL ? j : 0][k];
-                        blk[TL ? j : 0][k] = 0.f;
-                    }
-            }
-        }
-        // line l+1 goes to the other buffer while l is read; with one buffer,
-        // after every thread's taps of line l
-        if (nbuf == 1) __syncthreads();
-        if (more) stage_store(lines + (nbuf == 2 ? ((l + 1) & 1) * bufsz : 0));
-        __syncthreads();
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     }
+    __syncthreads();
+    for (int st = 0; st < nst; ++st) {
+        if constexpr (STG == STG_REGS) {
+            store(st + 1);
+            load(min(st + 2, nst - 1));
+        } else {
+            if (st + 1 < nst) load(st + 1);
+        }
+        const int l0 = first_line(st);
+        for (int ln = lbeg + st * NLS - l0; ln < NLS; ++ln) {
+            const int l = l0 + ln;
+            if constexpr (TL)
+                if (l % LB == 0 && l > lbeg) flush();
+            const unsigned lb = lds0 + (unsigned)((st & 1) * bufb + ln * lineb) + rho;
+            const int w0l = wfirst(l);
+#pragma unroll
+            for (int j = 0; j < PPT; ++j)
+                if ((unsigned)(l - jb[j]) < (unsigned)(je[j] - jb[j])) taps(j, lb, w0l);
+        }
+        if constexpr (STG != STG_REGS) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
     }
 
+    // ---- epilogue
+    if (TL || E.mode == EPI_P) {
+        flush();
+        return;
+    }
     double d2 = 0.0;
     const float inv1s = 1.f / (1.f + E.sigma);
+    const float *__restrict__ phi = E.phi;
+    const float *__restrict__ gd = E.gdata;
+    float *__restrict__ out = E.out;
 #pragma unroll
     for (int j = 0; j < PPT; ++j) {
-        const int slot = (tid + NTH * j) / BT;
-        const int a = slot < A ? gcls[grp * A + slot] : -1;
-        const int b = bt * BT + fwd_ray(tid + NTH * j, a, lperm) % BT;
+        const int a = cl[j], b = bin[j];
         if (a < 0 || b >= Ns) continue;
-        if (E.mode == EPI_P) {
-            float *dst = P + (((size_t)a * Nz + z) * Ns + b) * K + k0;
+        // all K channels of the workgroup's NQ / K4 slices are here (K4 = 1,
+        // 2 or 4 divides NQ).  A slice's quads are summed as a tree, which no
+        // lane order changes.
+        for (int r = 0; r < E.Npi; ++r) {
+            const int i = r * E.n0 + a;
+            float s[NQ];
 #pragma unroll
-            for (int k = 0; k < KC; ++k)
-                if (k0 + k < K) dst[k] = acc[j][k];
-            continue;
-        }
-        // every half-turn of class a (K <= KC here); out, gdata and phi do not
-        // overlap, so the loads of all half-turns may be issued ahead of the
-        // stores
-        const float *__restrict__ phi = E.phi;
-        const float *__restrict__ gd = E.gdata;
-        float *__restrict__ out = E.out;
-        // Channels k >= K of the chunk were staged as zeros, so their sums
-        // are exactly 0 and a clamped (in-bounds) Phi index leaves v as it
-        // is.  The half-turns go in groups of HG whose loads (Phi rows, and
-        // for the prox g and h1) are all issued before any of them is used:
-        // with one workgroup per CU the epilogue's memory round trips are not
-        // hidden by other work, and a branch per channel or a round trip per
-        // half-turn cost up to 1 ms per launch.  Lanes past the last
-        // half-turn load that half-turn again and store nothing.
-        constexpr int HG = KC >= 16 ? 2 : 32 / KC;   // HG * KC <= 32 Phi values in registers
-        for (int r0 = 0; r0 < E.Npi; r0 += HG) {
-            float ph[HG][KC], gv[HG], hv[HG];
-            size_t o[HG];
-#pragma unroll
-            for (int u = 0; u < HG; ++u) {
-                const int r = min(r0 + u, E.Npi - 1);
-                const int i = r * E.n0 + a;
-                const float *row = phi + (size_t)i * K;
-#pragma unroll
-                for (int k = 0; k < KC; ++k) ph[u][k] = row[k < K ? k : K - 1];
-                o[u] = ((size_t)i * Nz + z) * Ns + ((r & 1) ? Ns - 1 - b : b);
-                if (E.mode != EPI_G) {
-                    gv[u] = gd[o[u]];
-                    hv[u] = out[o[u]];
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < HG; ++u) {
-                if (r0 + u >= E.Npi) break;
-                float v = 0.f;
-#pragma unroll
-                for (int k = 0; k < KC; ++k) v = fmaf(ph[u][k], acc[j][k], v);
+            for (int q = 0; q < NQ; ++q)
+                s[q] = dot4(*(const float4 *)(phi + (size_t)i * Kp + 4 * ((q ^ rq) & (K4 - 1))), sums(j, q));
+            const int bo = (r & 1) ? Ns - 1 - b : b;
+            auto put = [&](int sl, float v) {   // slice sl of the workgroup
+                const int z = z0 + sl;
+                if (z >= A.Nz) return;
+                const size_t o = ((size_t)i * A.Nz + z) * Ns + bo;
                 if (E.mode == EPI_G) {
-                    out[o[u]] = v;
+                    out[o] = v;
                 } else {
-                    const float d = v - gv[u];
+                    const float d = v - gd[o];
                     d2 += (double)d * (double)d;
-                    out[o[u]] = (hv[u] + E.sigma * d) * inv1s;
+                    out[o] = (out[o] + E.sigma * d) * inv1s;
                 }
+            };
+            if (K4 == 1) {
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) put(q ^ rq, s[q]);
+            } else if (K4 == 2) {
+#pragma unroll
+                for (int q = 0; q + 1 < NQ; q += 2) put((q ^ rq) >> 1, s[q] + s[q + 1]);
+            } else if constexpr (NQ == 4) {
+                put(0, (s[0] + s[1]) + (s[2] + s[3]));
             }
         }
     }
@@ -461,44 +436,50 @@ __global__ __launch_bounds__(NTH) void k_project(
     }
 }
 
-// g(i,z,b) = sum_k Phi[i][k] P(a(i), z, b', k); rows (i,z) grid-strided over a
-// fixed number of workgroups so the FP64 partials have a fixed order.
+// g(i,z,b) = sum_k Phi[i][k] sum_lp P_lp(a(i), z, b', k): a workgroup takes
+// one class and EPT * NT of its (slice, bin) pairs; a thread adds its pair's
+// NLP partial sums once, keeps the KQ channel quads in registers and takes
+// every half-turn from them (the Phi rows are uniform over the workgroup).  The
+// order of the FP64 partials is fixed by the grid.
+template <int KQ>
 __global__ __launch_bounds__(NT) void k_contract(
     const float *__restrict__ P, const float *__restrict__ phi, float *__restrict__ out,
     const float *__restrict__ gdata, int mode, float sigma, double *__restrict__ part, int Nz,
-    int Ns, int K, int n0, int Ntheta)
+    int Ns, int K4, int n0, int Npi, int NLP, int EPT, int nch)
 {
     __shared__ double sh[NT / 64];
-    const long rows = (long)Ntheta * Nz;
+    const int a = blockIdx.x / nch, ch = blockIdx.x % nch;
+    const int Kp = 4 * K4, ne = Nz * Ns;
+    const size_t pstride = (size_t)n0 * ne * Kp;   // between the parts
     double d2 = 0.0;
     const float inv1s = 1.f / (1.f + sigma);
-    for (long row = blockIdx.x; row < rows; row += gridDim.x) {
-        const int i = (int)(row / Nz), z = (int)(row % Nz);
-        const int a = i % n0, rot = i / n0;
-        const float *ph = phi + (size_t)i * K;
-        const float *Pz = P + ((size_t)a * Nz + z) * Ns * K;
-        float *o = out + ((size_t)i * Nz + z) * Ns;
-        for (int b = threadIdx.x; b < Ns; b += NT) {
-            const int bp = (rot & 1) ? Ns - 1 - b : b;
-            const float *src = Pz + (size_t)bp * K;
+    for (int t = 0; t < EPT; ++t) {
+        const int e = (ch * EPT + t) * NT + (int)threadIdx.x;
+        if (e >= ne) break;
+        const int z = e / Ns, b = e % Ns;
+        const float *src = P + ((size_t)a * ne + e) * Kp;
+        v4 x[KQ];
+#pragma unroll
+        for (int q = 0; q < KQ; ++q) {
+            x[q] = v4{0.f, 0.f, 0.f, 0.f};
+            if (q >= K4) continue;
+            x[q] = *(const v4 *)(src + 4 * q);
+            for (int lp = 1; lp < NLP; ++lp) x[q] += *(const v4 *)(src + lp * pstride + 4 * q);
+        }
+        for (int r = 0; r < Npi; ++r) {
+            const int i = r * n0 + a;
+            const float *ph = phi + (size_t)i * Kp;
             float v = 0.f;
-            if ((K & 3) == 0) {
-                for (int k = 0; k < K; k += 4) {
-                    const float4 x = *(const float4 *)(src + k);
-                    v = fmaf(ph[k], x.x, v);
-                    v = fmaf(ph[k + 1], x.y, v);
-                    v = fmaf(ph[k + 2], x.z, v);
-                    v = fmaf(ph[k + 3], x.w, v);
-                }
-            } else {
-                for (int k = 0; k < K; ++k) v = fmaf(ph[k], src[k], v);
-            }
+#pragma unroll
+            for (int q = 0; q < KQ; ++q)
+                if (q < K4) v += dot4(*(const float4 *)(ph + 4 * q), x[q]);
+            const size_t o = ((size_t)i * Nz + z) * Ns + ((r & 1) ? Ns - 1 - b : b);
             if (mode == CONTRACT_STORE) {
-                o[b] = v;
+                out[o] = v;
             } else {   // Fig. 2 step 3: h1 <- (h1 + sigma (R f~ - g)) / (1 + sigma)
-                const float d = v - gdata[((size_t)i * Nz + z) * Ns + b];
+                const float d = v - gdata[o];
                 d2 += (double)d * (double)d;
-                o[b] = (o[b] + sigma * d) * inv1s;
+                out[o] = (out[o] + sigma * d) * inv1s;
             }
         }
     }
@@ -565,133 +546,98 @@ __global__ __launch_bounds__(NT) void k_fold(const float *__restrict__ g,
     }
 }
 
-template <int KC, int PPT, int PF, int VEC, bool TL, int NTH = FT, bool EXACT = false>
-static int launch_project_t(const Plan &p, const float *f, const FwdEpi &E, hipStream_t s,
-                            unsigned nb)
+template <int NQ, int PPT, int PF, bool TL, int NTH, int STG>
+static int launch_project_t(const Plan &p, const RayCfg &R, const float *f, const FwdEpi &E,
+                            hipStream_t s)
 {
     const rt_geom &G = p.g;
-    const FwdCfg &F = p.fwd;
-    auto kern = k_project<KC, PPT, PF, VEC, TL, NTH, EXACT>;
-    if (F.lds > 64 * 1024)   // beyond the default dynamic LDS limit: ask for what this plan needs
+    auto kern = k_project<NQ, PPT, PF, TL, NTH, STG>;
+    if (R.lds > 64 * 1024)   // beyond the default dynamic LDS limit: ask for what this plan needs
         RT_HIP(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                   (int)F.lds));
+                                   (int)R.lds));
+    const RayArgs A{G.N, G.Nz, G.Ns, G.K, R.K4, R.ngroups, R.NLP, R.nblocks};
     KTimer kt("k_project", s);
-    hipLaunchKernelGGL(kern, dim3(nb), dim3(NTH), F.lds, s, f, p.d_scr, p.d_gcls, p.d_gwalk,
-                       F.BT % 64 == 0 ? p.d_lperm : nullptr, p.d_ccos, p.d_csin, G.N, G.Nz, G.Ns, G.K, F.A, F.ngroups, F.BT, F.nbt,
-                       F.nkc, F.nbuf, nb, E);
+    hipLaunchKernelGGL(kern, dim3(R.nblocks), dim3(NTH), R.lds, s, f, p.d_scr, p.d_groups + R.group0,
+                       p.d_wcls, p.d_lanes + (size_t)(NQ == 4 ? 2 : NQ == 2 ? 1 : 0) * p.n0 * 64,
+                       p.d_ccos, p.d_csin, A, E);
     kt.stop();
     return RT_OK;
 }
 
-// two-level sums are planned for N > 512, where 16-channel chunks are not
-// used and 8 rays per thread or 8 float4 of prefetch only occur
-template <int KC, int PPT, int PF, int VEC>
-static int launch_project_l(const Plan &p, const float *f, const FwdEpi &E, hipStream_t s,
-                            unsigned nb)
+// the instances RayCfg plans for
+template <int NQ, int STG>
+static int launch_project_s(const Plan &p, const RayCfg &R, const float *f, const FwdEpi &E,
+                            hipStream_t s)
 {
-    if constexpr (KC == 16) {
-        return launch_project_t<KC, PPT, PF, VEC, false>(p, f, E, s, nb);
-    } else if constexpr (PPT == 8 || PF == 8) {
-        return launch_project_t<KC, PPT, PF, VEC, true>(p, f, E, s, nb);
-    } else {
-        return p.fwd.tl ? launch_project_t<KC, PPT, PF, VEC, true>(p, f, E, s, nb)
-                        : launch_project_t<KC, PPT, PF, VEC, false>(p, f, E, s, nb);
-    }
+    if (R.nth == 256) return launch_project_t<NQ, 1, RAY_PF_SMALL, false, 256, STG>(p, R, f, E, s);
+    if (R.tl) return launch_project_t<NQ, 2, RAY_PF, true, 1024, STG>(p, R, f, E, s);
+    return launch_project_t<NQ, 2, RAY_PF, false, 1024, STG>(p, R, f, E, s);
 }
 
-template <int KC, int PF, int VEC>
-static int launch_project_p(const Plan &p, const float *f, const FwdEpi &E, hipStream_t s,
-                            unsigned nb, int ppt)
+template <int NQ>
+static int launch_project_q(const Plan &p, const RayCfg &R, const float *f, const FwdEpi &E,
+                            hipStream_t s)
 {
-    switch (ppt) {
-    case 1: return launch_project_l<KC, 1, PF, VEC>(p, f, E, s, nb);
-    case 2: return launch_project_l<KC, 2, PF, VEC>(p, f, E, s, nb);
-    case 4: return launch_project_l<KC, 4, PF, VEC>(p, f, E, s, nb);
-    default:   // 8 rays per thread: planned only for KC <= 8 with float4 staging
-        if constexpr (KC <= 8 && VEC == 4 && PF == 4) {
-            return launch_project_l<KC, 8, PF, VEC>(p, f, E, s, nb);
-        } else {
-            return fail(RT_E_SHAPE, "no projection kernel for 8 rays per thread at KC=%d", KC);
-        }
-    }
+    // the buffer loads need every position of a window to have its own 32-bit
+    // offset: those before the line and past it included (STG_LINE), all
+    // slices of a workgroup's quads, at most 1 + (NQ - 1) / K4 more (STG_LIST)
+    const rt_geom &g = p.g;
+    const size_t lim = (size_t)1 << 32, pos = (size_t)g.N * g.K * 4;
+    if (g.K >= 4 && R.K4 % NQ == 0 && (g.N + 2 * RAY_WMAX) * pos < lim)
+        return launch_project_s<NQ, STG_LINE>(p, R, f, E, s);
+    if (g.K >= 4 && (size_t)NQ * g.N * pos < lim - 4096)
+        return launch_project_s<NQ, STG_LIST>(p, R, f, E, s);
+    return launch_project_s<NQ, STG_REGS>(p, R, f, E, s);
 }
 
-template <int KC, int VEC>
-static int launch_project_k(const Plan &p, const float *f, const FwdEpi &E, hipStream_t s,
-                            unsigned nb, int ppt)
+// workgroups of k_contract: per class, NT * EPT (slice, bin) pairs each
+struct ContractGrid {
+    int EPT, nch;
+    unsigned nb;
+};
+static ContractGrid contract_grid(const Plan &p)
 {
-    // scalar staging (K % 4 != 0) and 16-channel chunks are planned with 4
-    // float4 of prefetch per thread (registers of the two-level ray sums)
-    if constexpr (VEC == 1 || KC == 16) {
-        return launch_project_p<KC, 4, VEC>(p, f, E, s, nb, ppt);
-    } else {
-        return p.fwd.pf <= 4 ? launch_project_p<KC, 4, VEC>(p, f, E, s, nb, ppt)
-                             : launch_project_p<KC, 8, VEC>(p, f, E, s, nb, ppt);
-    }
+    const long ne = (long)p.g.Nz * p.g.Ns;
+    ContractGrid c;
+    c.EPT = (int)std::max(1L, std::min(4L, ne * p.n0 / (4096L * NT)));
+    c.nch = (int)((ne + (long)NT * c.EPT - 1) / ((long)NT * c.EPT));
+    c.nb = (unsigned)p.n0 * c.nch;
+    return c;
 }
-
-static unsigned row_blocks(long rows) { return (unsigned)std::min<long>(rows, 4096); }
 
 }  // namespace
-
-static unsigned project_blocks(const Plan &p)
-{
-    const FwdCfg &F = p.fwd;
-    return (unsigned)p.g.Nz * F.ngroups * F.nkc * F.nbt;
-}
 
 int launch_forward_pf(const Plan &p, const float *f, float *g, int mode, const float *gdata,
                       float *h1, float sigma, double *part, hipStream_t s)
 {
     const rt_geom &G = p.g;
-    const FwdCfg &F = p.fwd;
     if (G.Nz == 0) return RT_OK;
-    const int pairs = F.A * F.BT;
-    const int nth = F.nth;
-    const int ppt = pairs <= nth ? 1 : pairs <= 2 * nth ? 2 : pairs <= 4 * nth ? 4 : 8;
-    const unsigned nb = project_blocks(p);
-    const bool fused = F.nkc == 1;   // all K channels in one workgroup: contract in the epilogue
+    const RayCfg R = ray_cfg(p);
     FwdEpi E{};
-    E.phi = p.d_phi;
+    E.phi = p.d_phip;
     E.out = mode == CONTRACT_STORE ? g : h1;
     E.gdata = gdata;
-    E.part = fused ? part : nullptr;
+    E.part = R.fused ? part : nullptr;
     E.sigma = sigma;
-    E.mode = !fused ? EPI_P : (mode == CONTRACT_STORE ? EPI_G : EPI_PROX);
+    E.mode = !R.fused ? EPI_P : (mode == CONTRACT_STORE ? EPI_G : EPI_PROX);
     E.n0 = p.n0;
     E.Npi = G.Npi;
-    int rc;
-    if (nth == 2 * FT) {
-        // 16 waves of 2 rays: planned only for 16-channel float4 staging of
-        // lines of at most 512 positions (2 float4 of prefetch per thread)
-        if (F.vec != 4 || F.KC != 16 || ppt != 2 || F.tl || G.N * 16 > 4 * 2 * 2 * FT)
-            return fail(RT_E_SHAPE, "no 1024-thread projection kernel for this plan");
-        // the 2 float4 of the 1024 threads are exactly a line of 512 positions
-        // when N = 512 and every chunk holds 16 channels: unmasked staging
-        if (G.N == 512 && G.K % 16 == 0)
-            rc = launch_project_t<16, 2, 2, 4, false, 2 * FT, true>(p, f, E, s, nb);
-        else
-            rc = launch_project_t<16, 2, 2, 4, false, 2 * FT>(p, f, E, s, nb);
-    } else if (F.vec == 4) {
-        switch (F.KC) {
-        case 4: rc = launch_project_k<4, 4>(p, f, E, s, nb, ppt); break;
-        case 8: rc = launch_project_k<8, 4>(p, f, E, s, nb, ppt); break;
-        default: rc = launch_project_k<16, 4>(p, f, E, s, nb, ppt); break;
-        }
-    } else {
-        switch (F.KC) {   // the plan keeps KC <= 8 with scalar staging
-        case 4: rc = launch_project_k<4, 1>(p, f, E, s, nb, ppt); break;
-        case 8: rc = launch_project_k<8, 1>(p, f, E, s, nb, ppt); break;
-        default: return fail(RT_E_SHAPE, "no scalar-staging projection for KC=%d", F.KC);
-        }
-    }
+    const int rc = R.NQ == 4   ? launch_project_q<4>(p, R, f, E, s)
+                   : R.NQ == 2 ? launch_project_q<2>(p, R, f, E, s)
+                               : launch_project_q<1>(p, R, f, E, s);
     if (rc) return rc;
     RT_HIP(hipGetLastError());
-    if (fused) return RT_OK;
-    const unsigned nbc = row_blocks((long)G.Ntheta * G.Nz);
+    if (R.fused) return RT_OK;
+    const ContractGrid c = contract_grid(p);
     KTimer kt("k_contract", s);
-    hipLaunchKernelGGL(k_contract, dim3(nbc), dim3(NT), 0, s, p.d_scr, p.d_phi, E.out, gdata,
-                       mode, sigma, part, G.Nz, G.Ns, G.K, p.n0, G.Ntheta);
+#define RT_CONTRACT(Q) hipLaunchKernelGGL(k_contract<Q>, dim3(c.nb), dim3(NT), 0, s, p.d_scr, p.d_phip, \
+                                          E.out, gdata, mode, sigma, part, G.Nz, G.Ns, R.K4, p.n0,    \
+                                          G.Npi, R.NLP, c.EPT, c.nch)
+    if (R.K4 <= 2) RT_CONTRACT(2);
+    else if (R.K4 <= 4) RT_CONTRACT(4);
+    else if (R.K4 <= 8) RT_CONTRACT(8);
+    else RT_CONTRACT(16);
+#undef RT_CONTRACT
     kt.stop();
     RT_HIP(hipGetLastError());
     return RT_OK;
@@ -700,7 +646,9 @@ int launch_forward_pf(const Plan &p, const float *f, float *g, int mode, const f
 int forward_partials(const Plan &p)
 {
     if (p.form == RT_FORM_SF) return (int)sf_partials(p);
-    return p.fwd.nkc == 1 ? (int)project_blocks(p) : (int)row_blocks((long)p.g.Ntheta * p.g.Nz);
+    if (p.g.Nz == 0) return 1;
+    const RayCfg R = ray_cfg(p);
+    return (int)(R.fused ? R.nblocks : contract_grid(p).nb);
 }
 
 int launch_forward(const Plan &p, const float *f, float *g, int mode, const float *gdata,

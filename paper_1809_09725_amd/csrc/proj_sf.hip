@@ -462,7 +462,7 @@ static int launch_sf_d(const Plan &p, const SfEpi &E, hipStream_t s, unsigned nb
                                    (int)C.lds));
     KTimer kt("k_project_sf", s);
     hipLaunchKernelGGL(kern, dim3(nb), dim3(ST), C.lds, s, (const __bf16 *)p.d_f16, p.d_phi,
-                       p.d_gcls_sf, p.d_gwalk_sf, p.d_lperm, p.d_ccos, p.d_csin, G.N, G.Nz, G.Ns, G.K, C.A,
+                       p.d_gcls_sf, p.d_gwalk_sf, p.d_lanes, p.d_ccos, p.d_csin, G.N, G.Nz, G.Ns, G.K, C.A,
                        C.ngroups, C.BT, C.nbt, C.PCH, C.CS, C.NLP, nb, E);
     kt.stop();
     return RT_OK;

@@ -72,6 +72,7 @@ int power_iteration(Job &J, hipStream_t s)
     const Plan &full = *J.plan;
     Plan p = full;
     p.g.Nz = full.g.Nz > 0 ? 1 : 0;
+    p.nz_ref = p.g.Nz;
     const size_t nf = nf_of(p.g), ng = ng_of(p.g);
     float *x = J.ft, *y = J.work;
     int rc = launch_seeded_uniform(x, nf, J.prm.seed, s);
@@ -312,10 +313,10 @@ extern "C" int rt_job_bytes(const rt_geom *geom, rt_form form, rt_prec prec, siz
     if (rc) return rc;
     if (!bytes) return fail(RT_E_ARG, "bytes is NULL");
     const rt_geom &g = *geom;
-    const size_t tables = ((size_t)g.Ntheta * g.K + (size_t)g.Nt * g.K) * sizeof(float) +
-                          (size_t)(g.Ntheta / g.Npi) * (2 * sizeof(double) + 64) + 64 * 1024;
+    const size_t tables = ((size_t)g.Ntheta * (2 * g.K + 3) + (size_t)g.Nt * g.K) * sizeof(float) +
+                          (size_t)(g.Ntheta / g.Npi) * (2 * sizeof(double) + 3 * 64 + 4) + 64 * 1024;
     const size_t parts = ((size_t)1 << 18) * sizeof(double) + 16 * sizeof(double);
-    *bytes = tables + parts + plan_scratch_bytes(g) + n4_of(g) * sizeof(float) + job_state_bytes(g) +
+    *bytes = tables + parts + plan_scratch_bytes(g, g.Nz) + n4_of(g) * sizeof(float) + job_state_bytes(g) +
              (form == RT_FORM_SF ? shadow_bytes(g) + sf_partial_bytes(g) : 0);
     return RT_OK;
 }
