@@ -2,197 +2,244 @@
 // radadjapr): out_k(z,r,q) = sum_a sum_b w(theta0_a, b, q, r) g~(a,z,b,k), the
 // exact transpose of the ray-driven forward projection: the weight of bin b
 // for pixel p is max(0, 1 - |s_b - s_p| / c) / c with c = max(|cos|, |sin|),
-// Joseph's linear interpolation written from the pixel's side.
+// Joseph's linear interpolation written from the pixel's side.  The fold-sum
+// stores g~ / c, so that the weights here, c times the triangle weights, lie
+// in [0, 1].
 //
-// A 32x32 pixel tile takes the classes in rounds of CA; each round stages in
-// LDS the window of detector bins the tile's pixels reach for each class
-// (all KC channels of a bin in one row), then every pixel takes the two bins
-// around its s_p for each class.  A pixel's position relative to its class's
-// window is formed in FP64 once per class and stepped over the thread's rows
-// in 32.32 fixed point (the integer part is the window row, the fraction
-// gives the weights); weights and sums in FP32.
+// A workgroup takes a tile of 32 x 8 VPT pixels and NQ channel quads of the
+// list of all slices' quads (K = 16: one slice, K = 8: two).  Per class it
+// stages in LDS the window of detector bins the tile's pixels reach, then
+// every pixel takes the two bins around its s_p.  A pixel's position is formed
+// in FP64 once per class and stepped over the thread's rows in 32.32 fixed
+// point (the integer part gives the window row, the fraction the weights);
+// weights and sums in FP32.  Positions are absolute, so a pixel's bits do not
+// depend on its tile's shape.
+//
+// Stages of BP_CA classes, one per wave, are copied to LDS directly and double
+// buffered: a stage is on its way while the one before is summed, and one
+// barrier ends it.  A window row is NQ quads and, for NQ = 2 and 4, a spare
+// one (an odd number of 16-byte units: the 8 x 8 pixels of a read instruction
+// reach fewer than 16 consecutive rows per 16 lanes, which then fall in
+// distinct units).  The reads of g~ cost 128 bytes of LDS per pixel, class and
+// 16 channels; at 256 bytes per cycle and CU that is 5.3 ms at 512^2 x 128, K =
+// 16, 180 classes, and bounds the kernel with the FMAs (4.9 ms).
 #include "common.h"
 #include "internal.h"
 
 namespace rt {
 namespace {
 
-constexpr int BP_VPT = 4;     // pixels per thread (rows 8 apart)
+constexpr int BP_CA = NT / 64;   // classes per stage
+constexpr int BP_CH = 64;        // classes per fill of the class table (two fills kept)
 // Thread -> pixel: wave w of the tile takes columns 8w..8w+7 and lane l row
 // l / 8 of each 8-row step, so the 64 taps of one read instruction come from
-// an 8 x 8 pixel block.  Their detector positions then span few bins per
-// 16-lane pass of the LDS, which measured 4.1 cycles per 16-byte read on
-// sampled angles, against 7.2 for 2 rows x 32 columns.
+// an 8 x 8 pixel block, whose detector positions span few bins.
 __device__ inline int bp_col(int tid) { return 8 * (tid >> 6) + (tid & 7); }
 __device__ inline int bp_row(int tid) { return (tid >> 3) & 7; }
-constexpr int BP_MAXCA = 16;  // classes staged per round, at most
+// rows of the widest window of a tile of 32 x 8 vpt pixels: the positions'
+// span is at most the tile's diagonal; two bins around each position, one to
+// spare on either side
+constexpr int bp_rows(int vpt) { return vpt == 4 ? 44 + 6 : 32 + 6; }
+constexpr int bp_units(int nq) { return nq | 1; }   // 16-byte units per window row
+constexpr int bp_copies(int nq, int vpt) { return (bp_rows(vpt) * bp_units(nq) + 63) / 64; }
 
-// Four workgroups per CU: the bound holds the 16-channel kernel to 128
-// VGPRs (4 waves per SIMD, no spills) instead of 158 (3 waves), which
-// measured 5% faster at 512^2 and 2% at 1024^2
-template <int KC, int VEC>
-__global__ __launch_bounds__(NT, 4) void k_backproject(
-    const float *__restrict__ gt, float *__restrict__ out, const double *__restrict__ ccos,
-    const double *__restrict__ csin, int N, int Nz, int Ns, int K, int n0, int nkc, int ntq,
-    int ntr, int CA, int WMAX, unsigned nblocks)
+struct __attribute__((aligned(16))) BpClass {
+    double cs, sn;
+    long long D;     // 8 sin in 32.32 fixed point
+    float ic1, s1;   // 1 - 1/c and 2^-32 / c
+    int lo, pad[3];  // bin of the window's row 0
+};
+
+struct BpArgs {
+    int N, Nz, Ns, K, K4, n0, ntq, ntr;
+    unsigned nblocks;
+};
+
+// LIST: the quads are of several slices (K4 is no multiple of NQ); lanes
+// outside the detector or the list get an offset past the buffer.  Otherwise
+// the buffer is the slice's rows of one class and its bounds give the zeros.
+template <int NQ, int VPT, bool LIST>
+__global__ __launch_bounds__(NT, 4) void k_backproject(const float *__restrict__ gt,
+                                                       float *__restrict__ out,
+                                                       const double *__restrict__ ccos,
+                                                       const double *__restrict__ csin, BpArgs A)
 {
-    constexpr int stride = KC + 4;   // an odd number of 16-byte groups per bin
-    extern __shared__ float win[];   // [CA][WMAX][stride]
-    __shared__ int s_wb[BP_MAXCA], s_we[BP_MAXCA];   // window rows [wb, we) hold bins 0..Ns-1
-    __shared__ long long s_goff[BP_MAXCA];           // element offset of window row 0's bin in gt
-    __shared__ float s_inv[BP_MAXCA];                     // 1/c, c = max(|cos|, |sin|)
-    __shared__ float s_ic1[BP_MAXCA], s_s1[BP_MAXCA];     // 1 - 1/c and 2^-32 / c
-    __shared__ double s_base[BP_MAXCA];                   // hS - (bin of window row 0)
-    __shared__ long long s_D[BP_MAXCA];                   // 8 sin in 32.32 fixed point
-    unsigned lid = xcd_remap(blockIdx.x, nblocks);
-    const int tq = lid % ntq;
-    lid /= ntq;
-    const int tr = lid % ntr;
-    lid /= ntr;
-    const int kc = lid % nkc;
-    const int z = lid / nkc;
-    const int tid = threadIdx.x;
-    const int k0 = kc * KC;
+    constexpr int NU = bp_units(NQ), NI = bp_copies(NQ, VPT);
+    constexpr unsigned CLB = NI * 1024u, STB = BP_CA * CLB;   // bytes of a class's window, of a stage
+    extern __shared__ __align__(64) char smem[];              // [2][BP_CA][NI * 64 units]
+    __shared__ BpClass tab[2 * BP_CH];                        // class a in entry a mod 2 BP_CH
+    typedef float v4 __attribute__((ext_vector_type(4)));
+    typedef int i4 __attribute__((ext_vector_type(4)));
+    typedef __attribute__((address_space(3))) const v4 lds_v4;
+    const int N = A.N, Nz = A.Nz, Ns = A.Ns, K = A.K, K4 = A.K4, n0 = A.n0;
+    unsigned lid = xcd_remap(blockIdx.x, A.nblocks);
+    const int tq = lid % A.ntq;
+    lid /= A.ntq;
+    const int tr = lid % A.ntr;
+    const int cg = lid / A.ntr;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const double hN = 0.5 * (double)(N - 1), hS = 0.5 * (double)(Ns - 1);
+    const int z0 = cg * NQ / K4, kq0 = cg * NQ % K4;   // first quad
+    const unsigned Kb = 16u * K4;                      // bytes of a bin of g~
 
     const int q = tq * 32 + bp_col(tid);
-    const double x = (double)q - hN;
-    const double y0 = (double)(tr * 32 + bp_row(tid)) - hN;   // rows y0 + 8j, j < BP_VPT
+    // rows r0 + 8 j of the 32-row band, j0 <= j < j0 + VPT
+    const int band = tr * 8 * VPT / 32 * 32, j0 = (tr * 8 * VPT - band) / 8;
+    const int r0 = band + bp_row(tid);
+    const double x = (double)q - hN, y0 = (double)r0 - hN;
     const double xlo = (double)(tq * 32) - hN, xhi = xlo + 31.0;
-    const double ylo = (double)(tr * 32) - hN, yhi = ylo + 31.0;
+    const double ylo = (double)(tr * 8 * VPT) - hN, yhi = ylo + (8 * VPT - 1);
 
-    float acc[BP_VPT][KC];
-#pragma unroll
-    for (int j = 0; j < BP_VPT; ++j)
-#pragma unroll
-        for (int k = 0; k < KC; ++k) acc[j][k] = 0.f;
+    auto fill = [&](int a0) {   // classes [a0, a0 + BP_CH) into the table
+        const int a = a0 + tid;
+        if (tid >= BP_CH || a >= n0) return;
+        // s_p is affine in (x, y): the extreme positions are at the tile's
+        // corners; one spare bin below
+        const double cs = ccos[a], sn = csin[a];
+        const double u00 = fma(xlo, cs, fma(ylo, sn, hS)), u10 = fma(xhi, cs, fma(ylo, sn, hS));
+        const double u01 = fma(xlo, cs, fma(yhi, sn, hS)), u11 = fma(xhi, cs, fma(yhi, sn, hS));
+        const double umin = fmin(fmin(u00, u10), fmin(u01, u11));
+        const double ic = 1.0 / fmax(fabs(cs), fabs(sn));
+        BpClass &T = tab[a % (2 * BP_CH)];
+        T.cs = cs;
+        T.sn = sn;
+        T.D = (long long)llrint(sn * 34359738368.0);
+        T.ic1 = (float)(1.0 - ic);
+        T.s1 = (float)ic * 2.3283064365386963e-10f;
+        T.lo = (int)floor(umin) - 1;
+    };
 
-    for (int a0 = 0; a0 < n0; a0 += CA) {
-        const int nca = min(CA, n0 - a0);
-        __syncthreads();
-        if (tid < nca) {
-            // detector window of class a over the tile: s_p is affine in
-            // (x, y) and each rounding step is monotone, so the extreme
-            // positions of the tile's pixels are at its corners
-            const double cs = ccos[a0 + tid], sn = csin[a0 + tid];
-            const double u00 = fma(xlo, cs, fma(ylo, sn, hS));
-            const double u10 = fma(xhi, cs, fma(ylo, sn, hS));
-            const double u01 = fma(xlo, cs, fma(yhi, sn, hS));
-            const double u11 = fma(xhi, cs, fma(yhi, sn, hS));
-            const double umin = fmin(fmin(u00, u10), fmin(u01, u11));
-            const double umax = fmax(fmax(u00, u10), fmax(u01, u11));
-            // one spare bin on each side: a pixel's s_p, formed incrementally
-            // over its rows, may round an ulp outside [umin, umax]
-            const int lo = (int)floor(umin) - 1;
-            const int wn = (int)floor(umax) + 3 - lo;
-            s_wb[tid] = max(0, -lo);
-            s_we[tid] = min(wn, Ns - lo);
-            s_goff[tid] = (((long long)(a0 + tid) * Nz + z) * Ns + lo) * K + k0;
-            const double ic = 1.0 / fmax(fabs(cs), fabs(sn));
-            s_inv[tid] = (float)ic;
-            s_ic1[tid] = (float)(1.0 - ic);
-            s_s1[tid] = (float)ic * 2.3283064365386963e-10f;
-            s_base[tid] = hS - (double)lo;
-            s_D[tid] = (long long)llrint(sn * 34359738368.0);
-        }
-        __syncthreads();
-        {
-            // NT / CA threads per class window (CA divides NT): thread j of
-            // class c stages channel group j % NG of window rows j / NG, j / NG
-            // + RS, ...; the class's bounds and offsets are read once per
-            // round and the products fit 24 bits (w < WMAX, K <= 64).  The
-            // window holds g~ / c, so that the weights below are c times the
-            // triangle weights, in [0, 1].
-            constexpr int NG = VEC == 4 ? KC / 4 : KC;   // channel groups per window row
-            const int tpc = NT / CA;
-            const int c = tid / tpc, j = tid - c * tpc;
-            const int q = j % NG, RS = tpc / NG;
-            const int kofs = VEC == 4 ? 4 * q : q;   // first channel of the group
-            if (c < nca) {
-                const int wb = s_wb[c], we = s_we[c];
-                const float sc = s_inv[c];
-                const bool kin = k0 + kofs < K;
-                const float *src = gt + s_goff[c] + kofs;
-                float *dst = win + __mul24(c, WMAX) * stride + kofs;
-                for (int w = j / NG; w < WMAX; w += RS) {
-                    const bool in = kin && w >= wb && w < we;
-                    if constexpr (VEC == 4) {
-                        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-                        if (in) v = *(const float4 *)(src + __mul24(w, K));
-                        v.x *= sc;
-                        v.y *= sc;
-                        v.z *= sc;
-                        v.w *= sc;
-                        *(float4 *)(dst + __mul24(w, stride)) = v;
-                    } else {
-                        dst[__mul24(w, stride)] = in ? src[__mul24(w, K)] * sc : 0.f;
-                    }
-                }
-            }
-        }
-        __syncthreads();
-        for (int c = 0; c < nca; ++c) {
-            const double cs = ccos[a0 + c], sn = csin[a0 + c];
-            const float ic1 = s_ic1[c], s1 = s_s1[c];
-            // s_p minus the bin of the window's row 0, for the thread's first
-            // row: at least 1 up to FP64 rounding (the window keeps a spare bin
-            // below the tile's lowest position), so truncation is floor
-            const double rel = fma(x, cs, fma(y0, sn, s_base[c]));
-            const unsigned hi = (unsigned)rel;
-            const unsigned lo = (unsigned)((rel - (double)hi) * 4294967296.0);
-            // 32.32 fixed point whose integer part is the LDS row (class c's
-            // rows start at c WMAX); rows 8 apart add 8 sin, rounded to 2^-32,
-            // which moves a position by at most 2^-31 over the thread's rows
-            unsigned long long U = ((unsigned long long)(hi + (unsigned)(c * WMAX)) << 32) | lo;
-            const unsigned long long D = (unsigned long long)s_D[c];
+    // copy i of a wave: unit 64 i + lane of its class's window: row e / NU,
+    // quad e % NU (the spare unit and rows past the window take zeros)
+    unsigned goff[NI];
+    int grow[LIST ? NI : 1];
 #pragma unroll
-            for (int j = 0; j < BP_VPT; ++j) {
+    for (int i = 0; i < NI; ++i) {
+        const int e = 64 * i + lane, row = e / NU, u = e % NU;
+        const int gq = cg * NQ + u, zq = gq / K4 - z0, kq = gq % K4;
+        const bool ok = u < NQ && gq < Nz * K4 && row < bp_rows(VPT);
+        goff[i] = row * Kb + (LIST ? zq * (unsigned)Ns * Kb + kq * 16u : (kq0 + u) * 16u);
+        if constexpr (LIST) grow[i] = ok ? row : -(1 << 28);
+        else if (!ok) goff[i] = 0xc0000000u;   // stays past the buffer for every window start
+    }
+    const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) char *)smem;
+    // stage st into buffer st & 1 (inline assembly: the compiler adds no wait
+    // before the reads of the other buffer; the wait is the vmcnt(0) before
+    // the barrier that ends the stage)
+    auto issue = [&](int st) {
+        const int a = BP_CA * st + wave;
+        if (a >= n0) return;
+        const int lo = __builtin_amdgcn_readfirstlane(tab[a % (2 * BP_CH)].lo);
+        const char *base = (const char *)gt + ((size_t)a * Nz + z0) * Ns * Kb;
+        const unsigned end = (LIST ? min(Nz - z0, NQ) : 1) * (unsigned)Ns * Kb;
+        const i4 rs{(int)(unsigned)(size_t)base, (int)(((size_t)base >> 32) & 0xffff), (int)end, 0x00020000};
+        const unsigned dst = lds0 + (st & 1) * STB + wave * CLB;
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            unsigned off = goff[i] + (unsigned)lo * Kb;
+            if constexpr (LIST)
+                if ((unsigned)(grow[i] + lo) >= (unsigned)Ns) off = 0xffffff00u;
+            asm volatile("buffer_load_dwordx4 %0, %1, 0 offen lds"
+                         :: "v"(off), "s"(rs), "{m0}"(__builtin_amdgcn_readfirstlane(dst + i * 1024u))
+                         : "memory");
+        }
+    };
+
+    float acc[VPT][NQ][4];
+#pragma unroll
+    for (int j = 0; j < VPT; ++j)
+#pragma unroll
+        for (int k = 0; k < NQ; ++k)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) acc[j][k][t] = 0.f;
+
+    const int nst = (n0 + BP_CA - 1) / BP_CA;
+    fill(0);
+    __syncthreads();
+    issue(0);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    for (int st = 0; st < nst; ++st) {
+        if (st % (BP_CH / BP_CA) == 0) fill(BP_CA * st + BP_CH);
+        if (st + 1 < nst) issue(st + 1);
+        const int nc = min(BP_CA, n0 - BP_CA * st);
+        for (int c = 0; c < nc; ++c) {
+            const BpClass &T = tab[(BP_CA * st + c) % (2 * BP_CH)];
+            const float ic1 = T.ic1, s1 = T.s1;
+            const double s = fma(x, T.cs, fma(y0, T.sn, hS)), fl = floor(s);
+            const unsigned long long D = (unsigned long long)T.D;
+            // 32.32 fixed point: the integer part counts window rows; rows 8
+            // apart add 8 sin, rounded to 2^-32
+            unsigned long long U = ((unsigned long long)(unsigned)((int)fl - T.lo) << 32) |
+                                   (unsigned)((s - fl) * 4294967296.0);
+            if constexpr (VPT < 4) U += (unsigned long long)j0 * D;
+            const unsigned wbase = lds0 + (st & 1) * STB + c * CLB;
+#pragma unroll
+            for (int j = 0; j < VPT; ++j) {
                 if (j) {
                     U += D;
                     asm volatile("" : "+v"(U));   // one 64-bit add per row, not j*D
                 }
-                const unsigned row = (unsigned)(U >> 32);
                 const float fq = (float)(unsigned)U;   // the fraction in units of 2^-32
-                // triangle weights of the bins floor(u) and floor(u)+1 times c
-                // (the window holds g~ / c), max(0, 1 - |s_b - s_p| / c), which
-                // is at most 1: one fma with the clamp to [0, 1] each
+                // triangle weights of the bins floor(u) and floor(u)+1 times c:
+                // one fma with the clamp to [0, 1] each
                 const float w0 = fminf(fmaxf(fmaf(-fq, s1, 1.f), 0.f), 1.f);
                 const float w1 = fminf(fmaxf(fmaf(fq, s1, ic1), 0.f), 1.f);
-                const float *t0 = win + __umul24(row, stride);
+                const unsigned t0 = __umul24((unsigned)(U >> 32), NU * 16u) + wbase;
+                v4 x0[NQ], x1[NQ];
 #pragma unroll
-                for (int k = 0; k < KC; k += 4) {
-                    const float4 x0 = *(const float4 *)(t0 + k);
-                    const float4 x1 = *(const float4 *)(t0 + stride + k);
-                    acc[j][k + 0] = fmaf(w1, x1.x, fmaf(w0, x0.x, acc[j][k + 0]));
-                    acc[j][k + 1] = fmaf(w1, x1.y, fmaf(w0, x0.y, acc[j][k + 1]));
-                    acc[j][k + 2] = fmaf(w1, x1.z, fmaf(w0, x0.z, acc[j][k + 2]));
-                    acc[j][k + 3] = fmaf(w1, x1.w, fmaf(w0, x0.w, acc[j][k + 3]));
+                for (int k = 0; k < NQ; ++k) {
+                    x0[k] = *(lds_v4 *)(size_t)(t0 + 16 * k);
+                    x1[k] = *(lds_v4 *)(size_t)(t0 + 16 * (NU + k));
                 }
+                __builtin_amdgcn_sched_barrier(0);   // all reads are issued before the first FMA waits
+#pragma unroll
+                for (int k = 0; k < NQ; ++k)
+#pragma unroll
+                    for (int t = 0; t < 4; ++t)
+                        acc[j][k][t] = fmaf(w1, x1[k][t], fmaf(w0, x0[k][t], acc[j][k][t]));
             }
         }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
     }
 
     if (q >= N) return;
 #pragma unroll
-    for (int j = 0; j < BP_VPT; ++j) {
-        const int r = tr * 32 + bp_row(tid) + 8 * j;
+    for (int j = 0; j < VPT; ++j) {
+        const int r = r0 + 8 * (j0 + j);
         if (r >= N) continue;
-        float *dst = out + (((size_t)z * N + r) * N + q) * K + k0;
 #pragma unroll
-        for (int k = 0; k < KC; ++k)
-            if (k0 + k < K) dst[k] = acc[j][k];
+        for (int k = 0; k < NQ; ++k) {
+            const int gq = cg * NQ + k, z = gq / K4, c0 = 4 * (gq % K4);
+            if (z >= Nz) continue;
+            float *dst = out + (((size_t)z * N + r) * N + q) * K + c0;
+            if ((K & 3) == 0) {
+                *(v4 *)dst = v4{acc[j][k][0], acc[j][k][1], acc[j][k][2], acc[j][k][3]};
+            } else {
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+                    if (c0 + t < K) dst[t] = acc[j][k][t];
+            }
+        }
     }
 }
 
-template <int KC, int VEC>
-static void launch_bp_t(const Plan &p, float *out, hipStream_t s, unsigned nb, int ntq, int ntr)
+template <int NQ, int VPT>
+static void launch_bp_t(const Plan &p, float *out, hipStream_t s, int ncg, bool list)
 {
     const rt_geom &G = p.g;
-    const AdjCfg &B = p.adj;
+    BpArgs A{G.N, G.Nz, G.Ns, G.K, (G.K + 3) / 4, p.n0, (G.N + 31) / 32, (G.N + 8 * VPT - 1) / (8 * VPT), 0};
+    A.nblocks = (unsigned)ncg * A.ntq * A.ntr;
+    const size_t lds = (size_t)2 * BP_CA * bp_copies(NQ, VPT) * 1024;
     KTimer kt("k_backproject", s);
-    hipLaunchKernelGGL((k_backproject<KC, VEC>), dim3(nb), dim3(NT), B.lds, s, p.d_scr, out,
-                       p.d_ccos, p.d_csin, G.N, G.Nz, G.Ns, G.K, p.n0, B.nkc, ntq, ntr, B.CA,
-                       B.WMAX, nb);
+    if (list)
+        hipLaunchKernelGGL((k_backproject<NQ, VPT, true>), dim3(A.nblocks), dim3(NT), lds, s, p.d_scr,
+                           out, p.d_ccos, p.d_csin, A);
+    else
+        hipLaunchKernelGGL((k_backproject<NQ, VPT, false>), dim3(A.nblocks), dim3(NT), lds, s, p.d_scr,
+                           out, p.d_ccos, p.d_csin, A);
     kt.stop();
 }
 
@@ -201,22 +248,19 @@ static void launch_bp_t(const Plan &p, float *out, hipStream_t s, unsigned nb, i
 int launch_backproject(const Plan &p, float *out, hipStream_t s)
 {
     const rt_geom &G = p.g;
-    const AdjCfg &B = p.adj;
     if (G.Nz == 0) return RT_OK;
-    const int ntq = (G.N + 31) / 32, ntr = (G.N + 31) / 32;
-    const unsigned nb = (unsigned)G.Nz * B.nkc * ntr * ntq;
-    if (B.vec == 4) {
-        switch (B.KC) {
-        case 4: launch_bp_t<4, 4>(p, out, s, nb, ntq, ntr); break;
-        case 8: launch_bp_t<8, 4>(p, out, s, nb, ntq, ntr); break;
-        default: launch_bp_t<16, 4>(p, out, s, nb, ntq, ntr); break;
-        }
-    } else {
-        switch (B.KC) {
-        case 4: launch_bp_t<4, 1>(p, out, s, nb, ntq, ntr); break;
-        case 8: launch_bp_t<8, 1>(p, out, s, nb, ntq, ntr); break;
-        default: launch_bp_t<16, 1>(p, out, s, nb, ntq, ntr); break;
-        }
+    const int K4 = (G.K + 3) / 4, tq = G.Nz * K4;
+    const int NQ = tq >= 3 ? 4 : tq;
+    const int ncg = (tq + NQ - 1) / NQ;
+    const bool list = K4 % NQ != 0;
+    // 32 x 32 tiles where they give every CU its four workgroups, else 32 x 8
+    // (a pixel's bits are the same)
+    const long tiles = (long)ncg * ((G.N + 31) / 32) * ((G.N + 31) / 32);
+    const bool small = tiles < 1024;
+    switch (NQ) {
+    case 4: small ? launch_bp_t<4, 1>(p, out, s, ncg, list) : launch_bp_t<4, 4>(p, out, s, ncg, list); break;
+    case 2: small ? launch_bp_t<2, 1>(p, out, s, ncg, list) : launch_bp_t<2, 4>(p, out, s, ncg, list); break;
+    default: small ? launch_bp_t<1, 1>(p, out, s, ncg, list) : launch_bp_t<1, 4>(p, out, s, ncg, list); break;
     }
     RT_HIP(hipGetLastError());
     return RT_OK;

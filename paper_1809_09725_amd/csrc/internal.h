@@ -76,14 +76,6 @@ struct RayCfg {
     size_t lds = 0;       // bytes of LDS per workgroup
 };
 
-struct AdjCfg {
-    int KC = 4, nkc = 1, stride = 4, vec = 1;
-    int TQ = 32, TR = 32; // pixel tile
-    int CA = 8;           // classes staged per round
-    int WMAX = 0;         // bins of the widest staged window
-    size_t lds = 0;
-};
-
 // Synthesise-first (precision) projector: A classes per group, NPP frame
 // columns each (Npi rounded up to 4), A * NPP <= 32 columns in one MFMA tile;
 // lines in chunks of PCH positions, CS floats per LDS row; the BF16 shadow of
@@ -117,7 +109,6 @@ struct Plan {
     bool adjoint_only = false;
     std::vector<RayGroup> groups;   // full workgroups, then small ones
     int ngroups = 0;      // full workgroups
-    AdjCfg adj;
     SfCfg sf;
     TvCfg tv;
 
@@ -126,13 +117,14 @@ struct Plan {
     float *d_S = nullptr;       // [Nt][K]
     double *d_ccos = nullptr;   // [Ntheta0]
     double *d_csin = nullptr;
+    float *d_invc = nullptr;    // [Ntheta0] 1 / max(|cos|, |sin|)
     float *d_phip = nullptr;    // [Ntheta][K rounded up to 4], zero padded
     int *d_wcls = nullptr;      // classes by walk direction and sign of cos
     RayGroup *d_groups = nullptr;
     uint8_t *d_lanes = nullptr; // [3][Ntheta0][64] lane -> bin offset in its block of 64, for 1, 2, 4 channel quads
     int *d_gcls_sf = nullptr;   // class groups of the synthesise-first projector
     int *d_gwalk_sf = nullptr;
-    float *d_scr = nullptr;     // P (forward) [NLP][Ntheta0][Nz][Ns][K up to 4], g~ (adjoint) [Ntheta0][Nz][Ns][K]
+    float *d_scr = nullptr;     // P (forward) [NLP][Ntheta0][Nz][Ns][K up to 4], g~ / c (adjoint) [Ntheta0][Nz][Ns][K up to 4]
     float *d_frames = nullptr;  // [Nz][Nt][N][N]: time frames for tv_grad / tv_norm
     double *d_part = nullptr;   // FP64 partial sums
     size_t part_cap = 0;        // doubles in d_part

@@ -331,8 +331,6 @@ static int configure(Plan &p, TableUpload &up)
 {
     const rt_geom &g = p.g;
     const int n0 = p.n0;
-    const size_t budget = 80 * 1024;
-
     // ---- forward: classes by walk direction and sign of the main direction
     std::vector<int> rows, cols, by_dir[3];
     std::vector<RayDir> lists[3];
@@ -394,33 +392,6 @@ static int configure(Plan &p, TableUpload &up)
             }
         }
     }
-
-    // ---- adjoint: 32x32 pixel tiles, CA classes staged per round
-    AdjCfg &B = p.adj;
-    B.TQ = 32;
-    B.TR = 32;
-    B.CA = 8;
-    int wmax = 2;
-    for (int a = 0; a < n0; ++a) {
-        const double span = (B.TQ - 1) * std::fabs(p.T.ccos[a]) + (B.TR - 1) * std::fabs(p.T.csin[a]);
-        wmax = std::max(wmax, (int)std::ceil(span) + 6);
-    }
-    B.WMAX = wmax;
-    // KC channels per window row, stride KC + 4 floats; fewer classes per
-    // round when the window is wide.  9..12 channels take one 16-channel
-    // chunk: the same FMAs as two 8-channel chunks, with the ray geometry
-    // and the window staging done once
-    {
-        const int K4 = (g.K + 3) / 4 * 4;
-        B.KC = K4 > 8 ? 16 : K4 > 4 ? 8 : 4;
-        B.stride = B.KC + 4;
-        while (B.CA > 1 && (size_t)B.CA * B.WMAX * B.stride * sizeof(float) > budget) B.CA /= 2;
-        if ((size_t)B.CA * B.WMAX * B.stride * sizeof(float) > budget)
-            return fail(RT_E_SHAPE, "back-projection staging does not fit");
-    }
-    B.nkc = (g.K + B.KC - 1) / B.KC;
-    B.vec = (g.K % 4 == 0) ? 4 : 1;
-    B.lds = (size_t)B.CA * B.WMAX * B.stride * sizeof(float);
 
     p.tv.KT = g.K <= 8 ? 8 : g.K <= 16 ? 16 : g.K <= 32 ? 32 : 64;
 
@@ -507,6 +478,10 @@ static int create(const rt_geom *geom, rt_form form, rt_prec prec, const double 
     up.add(&p.d_S, S32);
     up.add(&p.d_ccos, p.T.ccos);
     up.add(&p.d_csin, p.T.csin);
+    std::vector<float> invc(p.n0);
+    for (int a = 0; a < p.n0; ++a)
+        invc[a] = (float)(1.0 / std::max(std::fabs(p.T.ccos[a]), std::fabs(p.T.csin[a])));
+    up.add(&p.d_invc, invc);
     if ((rc = up.upload(&p.d_tables, &p.bytes))) return rc;
     const size_t scr = std::max<size_t>(adjoint_only ? adjoint_scratch_bytes(p.g) : plan_scratch_bytes(p.g, nz_ref), 256);
     RT_HIP(hipMalloc(&p.d_scr, scr));

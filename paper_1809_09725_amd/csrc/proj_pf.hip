@@ -489,60 +489,46 @@ __global__ __launch_bounds__(NT) void k_contract(
     }
 }
 
-// g~(a,z,b,k) = sum_rot Phi[rot*n0+a][k] g(rot*n0+a, z, b')  (fold-sum, Sec. 4).
-// A workgroup takes one class a and a run of ZB slices: the class's Phi rows
-// are staged in LDS once, and each thread owns one bin of one slice: it reads
-// the Npi half-turn values of g once each and writes the bin's K channels
-// (consecutive threads write consecutive rows of g~).
-template <int KB4>   // channels in float4 groups: K <= 4 * KB4
+// g~(a,z,b,k) / c = sum_rot Phi[rot*n0+a][k] g(rot*n0+a, z, b') / c(a)  (fold-sum,
+// Sec. 4, with the back-projection's 1/c), K rounded up to 4 in a bin.  Bound by
+// HBM: g is read once, g~ written once.  A workgroup takes one class, whose Phi
+// rows it stages in LDS, and a run of its (slice, bin) pairs; a thread owns one
+// channel quad of a pair, so that consecutive threads write consecutive 16
+// bytes (a thread per pair wrote at 64-byte strides), and has the g values of
+// FB half-turns in flight at a time.
+constexpr int FB = 10;
 __global__ __launch_bounds__(NT) void k_fold(const float *__restrict__ g,
                                              const float *__restrict__ phi,
-                                             float *__restrict__ gt, int Nz, int Ns, int K,
-                                             int n0, int Npi, int ZB)
+                                             const float *__restrict__ invc,
+                                             float *__restrict__ gt, int Nz, int Ns, int K4,
+                                             int n0, int Npi, int run, int nrun)
 {
-    extern __shared__ float sphi[];   // Phi rows of class a: [Npi][4 * KB4], zero padded
-    const int nzb = (Nz + ZB - 1) / ZB;
-    const int a = blockIdx.x / nzb, z0 = (blockIdx.x % nzb) * ZB;
-    constexpr int KP = 4 * KB4;
-    for (int e = threadIdx.x; e < Npi * KP; e += NT) {
-        const int r = e / KP, k = e % KP;
-        sphi[e] = k < K ? phi[(size_t)(r * n0 + a) * K + k] : 0.f;
-    }
+    extern __shared__ v4 sphi[];   // Phi rows of class a: [Npi][K4]
+    const int a = blockIdx.x / nrun, e0 = (blockIdx.x % nrun) * run;
+    for (int e = threadIdx.x; e < Npi * K4; e += NT)
+        sphi[e] = *(const v4 *)(phi + ((size_t)(e / K4) * n0 + a) * 4 * K4 + 4 * (e % K4));
     __syncthreads();
-    const int z1 = min(Nz, z0 + ZB);
-    for (int e = threadIdx.x; e < (z1 - z0) * Ns; e += NT) {
-        const int z = z0 + e / Ns, b = e % Ns;
-        float4 acc[KB4];
+    const float ic = invc[a];
+    const int ne = Nz * Ns * K4, e1 = min(ne, e0 + run);
+    const size_t rstep = (size_t)n0 * Nz * Ns;   // next half-turn of the class
+    for (int e = e0 + (int)threadIdx.x; e < e1; e += NT) {
+        const int q = e % K4, zb = e / K4, z = zb / Ns, b = zb % Ns;
+        const float *src = g + ((size_t)a * Nz + z) * Ns;
+        v4 acc = {0.f, 0.f, 0.f, 0.f};
+        for (int r0 = 0; r0 < Npi; r0 += FB) {
+            float v[FB];
 #pragma unroll
-        for (int q = 0; q < KB4; ++q) acc[q] = make_float4(0.f, 0.f, 0.f, 0.f);
-        for (int rot = 0; rot < Npi; ++rot) {
-            const int i = rot * n0 + a;
-            const int bp = (rot & 1) ? Ns - 1 - b : b;
-            const float v = g[((size_t)i * Nz + z) * Ns + bp];
-            const float4 *ph = (const float4 *)(sphi + rot * KP);
+            for (int u = 0; u < FB; ++u)
+                if (r0 + u < Npi) v[u] = src[(r0 + u) * rstep + (((r0 + u) & 1) ? Ns - 1 - b : b)];
 #pragma unroll
-            for (int q = 0; q < KB4; ++q) {
-                const float4 w = ph[q];
-                acc[q].x = fmaf(w.x, v, acc[q].x);
-                acc[q].y = fmaf(w.y, v, acc[q].y);
-                acc[q].z = fmaf(w.z, v, acc[q].z);
-                acc[q].w = fmaf(w.w, v, acc[q].w);
-            }
+            for (int u = 0; u < FB; ++u)
+                if (r0 + u < Npi) {
+                    const v4 w = sphi[(r0 + u) * K4 + q];
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) acc[t] = fmaf(w[t], v[u], acc[t]);
+                }
         }
-        float *d = gt + (((size_t)a * Nz + z) * Ns + b) * K;
-        if ((K & 3) == 0) {
-#pragma unroll
-            for (int q = 0; q < KB4; ++q)
-                if (4 * q < K) *(float4 *)(d + 4 * q) = acc[q];
-        } else {
-#pragma unroll
-            for (int q = 0; q < KB4; ++q) {
-                const float c[4] = {acc[q].x, acc[q].y, acc[q].z, acc[q].w};
-#pragma unroll
-                for (int t = 0; t < 4; ++t)
-                    if (4 * q + t < K) d[4 * q + t] = c[t];
-            }
-        }
+        *(v4 *)(gt + ((size_t)a * ne + e) * 4) = acc * ic;
     }
 }
 
@@ -671,19 +657,15 @@ int launch_adjoint_pf(const Plan &p, const float *g, float *out, hipStream_t s)
 {
     const rt_geom &G = p.g;
     if (G.Nz == 0) return RT_OK;
-    // a workgroup per class and run of ZB slices (about 4 bins per thread)
-    const int ZB = std::max(1, std::min(G.Nz, 4 * NT / std::max(1, G.Ns)));
-    const unsigned nbf = (unsigned)p.n0 * ((G.Nz + ZB - 1) / ZB);
-    const int kb4 = (G.K + 3) / 4;
-    const size_t lds = (size_t)G.Npi * 4 * (kb4 <= 2 ? 2 : kb4 <= 4 ? 4 : kb4 <= 8 ? 8 : 16) * sizeof(float);
+    // a workgroup per class and run of 4 NT channel quads, fewer where that
+    // gives less than 4 workgroups per CU
+    const int K4 = (G.K + 3) / 4;
+    const long ne = (long)G.Nz * G.Ns * K4;
+    const int run = NT * (int)std::max(1L, std::min(4L, ne * p.n0 / (1024L * NT)));
+    const int nrun = (int)((ne + run - 1) / run);
     KTimer kt("k_fold", s);
-#define RT_FOLD(B) hipLaunchKernelGGL(k_fold<B>, dim3(nbf), dim3(NT), lds, s, g, p.d_phi, p.d_scr, \
-                                      G.Nz, G.Ns, G.K, p.n0, G.Npi, ZB)
-    if (kb4 <= 2) RT_FOLD(2);
-    else if (kb4 <= 4) RT_FOLD(4);
-    else if (kb4 <= 8) RT_FOLD(8);
-    else RT_FOLD(16);
-#undef RT_FOLD
+    hipLaunchKernelGGL(k_fold, dim3((unsigned)p.n0 * nrun), dim3(NT), (size_t)G.Npi * K4 * 16, s, g,
+                       p.d_phip, p.d_invc, p.d_scr, G.Nz, G.Ns, K4, p.n0, G.Npi, run, nrun);
     kt.stop();
     RT_HIP(hipGetLastError());
     return launch_backproject(p, out, s);

@@ -392,7 +392,8 @@ __global__ __launch_bounds__(NT) void k_to_bf16(const float *__restrict__ f,
 // multiple of 16.  One wave per 16-bin x 16-channel tile.
 // A: lane holds bins row = lane%16, half-turns 4*(lane/16) + 0..3 of the
 // current 16-chunk; B: Phi rows of those half-turns, channel lane%16;
-// C: bins 4*(lane/16) + 0..3, channel lane%16.
+// C: bins 4*(lane/16) + 0..3, channel lane%16.  Stored as g~ / c(a) (the
+// back-projection's weights), K rounded up to 4 in a bin.
 // Both operands are split into BF16 hi + lo parts and the three products
 // hi*hi + hi*lo + lo*hi are accumulated in FP32 (the lo*lo term is below
 // 2^-16 of the product): the sinogram fed to the adjoint is the dual h1 of
@@ -402,11 +403,12 @@ __global__ __launch_bounds__(NT) void k_to_bf16(const float *__restrict__ f,
 // products cost nothing measurable.
 __global__ __launch_bounds__(NT) void k_fold_mfma(const float *__restrict__ g,
                                                   const float *__restrict__ phi,
+                                                  const float *__restrict__ invc,
                                                   float *__restrict__ gt, int Nz, int Ns, int K,
                                                   int n0, int Npi)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int nbt = (Ns + 15) / 16, nkt = (K + 15) / 16;
+    const int nbt = (Ns + 15) / 16, nkt = (K + 15) / 16, Kp = (K + 3) / 4 * 4;
     const long tiles = (long)n0 * Nz * nbt * nkt;
     for (long t = (long)blockIdx.x * (NT / 64) + wave; t < tiles; t += (long)gridDim.x * (NT / 64)) {
         long u = t;
@@ -441,11 +443,12 @@ __global__ __launch_bounds__(NT) void k_fold_mfma(const float *__restrict__ g,
             cacc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ah, bl, cacc, 0, 0, 0);
             cacc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(ah, bh, cacc, 0, 0, 0);
         }
-        if (kcol < K) {
+        if (kcol < Kp) {
+            const float ic = invc[a];
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const int bo = btile * 16 + 4 * (lane >> 4) + q;
-                if (bo < Ns) gt[(((size_t)a * Nz + z) * Ns + bo) * K + kcol] = cacc[q];
+                if (bo < Ns) gt[(((size_t)a * Nz + z) * Ns + bo) * Kp + kcol] = cacc[q] * ic;
             }
         }
     }
@@ -607,8 +610,8 @@ int launch_fold_mfma(const Plan &p, const float *g, hipStream_t s)
     const long tiles = (long)p.n0 * G.Nz * ((G.Ns + 15) / 16) * ((G.K + 15) / 16);
     const unsigned nb = (unsigned)std::max<long>(1, std::min<long>((tiles + 3) / 4, 16384));
     KTimer kt("k_fold_mfma", s);
-    hipLaunchKernelGGL(k_fold_mfma, dim3(nb), dim3(NT), 0, s, g, p.d_phi, p.d_scr, G.Nz, G.Ns,
-                       G.K, p.n0, G.Npi);
+    hipLaunchKernelGGL(k_fold_mfma, dim3(nb), dim3(NT), 0, s, g, p.d_phi, p.d_invc, p.d_scr, G.Nz,
+                       G.Ns, G.K, p.n0, G.Npi);
     kt.stop();
     RT_HIP(hipGetLastError());
     return RT_OK;

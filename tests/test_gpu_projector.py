@@ -1,4 +1,5 @@
-"""R_T of the plain form at the edges of its work split, against the FP64 oracle.
+"""R_T and R_T* of the plain form at the edges of their work split, against the
+FP64 oracle.
 
 Tolerance 1e-5 of the result (rel-L2 and, scaled by the largest value, per
 element): each value is a sum of up to 2 N K products of unit scale in FP32,
@@ -52,6 +53,28 @@ def test_forward_edges(G):
     assert np.abs(got - want).max() <= 1e-5 * np.abs(want).max()
 
 
+ADJOINT_CASES = CASES + [
+    # 32 x 32 tiles (the cases above fill few: 32 x 8), ragged and aligned,
+    # quads of one and of several slices, a ragged last quad; detectors that end
+    # inside the slice; more classes than one fill of the class table
+    geom(128, 64, 128, 2, 5, 16), geom(100, 40, 60, 3, 9, 20), geom(97, 90, 140, 2, 7, 7),
+    geom(40, 3, 30, 2, 131, 16), geom(33, 2, 500, 4, 65, 6), geom(31, 2, 8, 2, 64, 16),
+]
+
+
+@pytest.mark.parametrize("G", ADJOINT_CASES, ids=lambda G: f"N{G.N}z{G.Nz}s{G.Ns}a{G.n0}k{G.K}")
+def test_adjoint_edges(G):
+    """Each value sums at most 2 Ntheta products of unit scale (weights up to
+    sqrt 2): the same bar."""
+    torch.cuda.set_device(DEV)
+    print(f"case {G}", flush=True)
+    g = inputs.uniform(G.g_shape, 7)
+    got = rt4d.Plan(G).adjoint(torch.from_numpy(g).to(DEV)).cpu().numpy().astype(np.float64)
+    want = O.adjoint(O.Geom(**G.__dict__), g)
+    assert np.linalg.norm(got - want) <= 1e-5 * np.linalg.norm(want)
+    assert np.abs(got - want).max() <= 1e-5 * np.abs(want).max()
+
+
 @pytest.mark.parametrize("K", [4, 8, 11, 16])
 def test_slices_do_not_depend_on_the_volume(K):
     """A slice's projections are the same bits whichever slices share its
@@ -69,3 +92,12 @@ def test_slices_do_not_depend_on_the_volume(K):
     assert torch.equal(a[:, keep], b[:, keep])
     assert torch.isnan(b[:, 3]).any() and not torch.isnan(b[:, 3]).all()
     assert not torch.isfinite(b[:, 9]).all()
+    g = torch.from_numpy(inputs.uniform(G.g_shape, 8)).to(DEV)
+    a = p.adjoint(g)
+    g2 = g.clone()
+    g2[5, 3, 50] = float("nan")
+    g2[70, 9, 20] = float("inf")
+    b = p.adjoint(g2)
+    assert torch.equal(a[keep], b[keep])
+    assert torch.isnan(b[3]).any() and not torch.isnan(b[3]).all()
+    assert not torch.isfinite(b[9]).all()
