@@ -226,6 +226,145 @@ __global__ __launch_bounds__(NT, 4) void k_backproject(const float *__restrict__
     }
 }
 
+// Few pixels: a workgroup takes 8 x 8 pixels, and its four waves take every
+// fourth class each, with windows of their own (no barriers), and add their sums
+// at the end in wave order.  A 64^2 slice is then 64 workgroups of n0 / 4
+// classes in sequence instead of 16 of n0: 21 -> 8 us at 90 classes, 8
+// channels.  The windows' rows per pixel double, so it is for images whose 32 x 8
+// tiles leave most CUs idle.
+constexpr int BS_CB = 4;      // classes per batch of copies, two batches in flight
+constexpr int BS_ROWS = 17;   // 7 sqrt 2 < 10 positions; two bins, one to spare on either side
+constexpr int bs_copies(int nq) { return (BS_ROWS * bp_units(nq) + 63) / 64; }
+
+template <int NQ, bool LIST>
+__global__ __launch_bounds__(NT) void k_backproject_small(const float *__restrict__ gt,
+                                                          float *__restrict__ out,
+                                                          const double *__restrict__ ccos,
+                                                          const double *__restrict__ csin, BpArgs A)
+{
+    constexpr int NU = bp_units(NQ), NI = bs_copies(NQ);
+    constexpr unsigned CLB = NI * 1024u, WVB = 2 * BS_CB * CLB;   // bytes of a window, of a wave's ring
+    extern __shared__ __align__(64) char smem[];                  // [4 waves][2][BS_CB][NI * 64 units]
+    typedef float v4 __attribute__((ext_vector_type(4)));
+    typedef int i4 __attribute__((ext_vector_type(4)));
+    typedef __attribute__((address_space(3))) const v4 lds_v4;
+    const int N = A.N, Nz = A.Nz, Ns = A.Ns, K = A.K, K4 = A.K4, n0 = A.n0;
+    unsigned lid = xcd_remap(blockIdx.x, A.nblocks);
+    const int tq = lid % A.ntq;
+    lid /= A.ntq;
+    const int tr = lid % A.ntr;
+    const int cg = lid / A.ntr;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const double hN = 0.5 * (double)(N - 1), hS = 0.5 * (double)(Ns - 1);
+    const int z0 = cg * NQ / K4, kq0 = cg * NQ % K4;
+    const unsigned Kb = 16u * K4;
+    const int q = tq * 8 + (lane & 7), r = tr * 8 + (lane >> 3);
+    const double x = (double)q - hN, y = (double)r - hN;
+    const double xm = (double)(tq * 8) + 3.5 - hN, ym = (double)(tr * 8) + 3.5 - hN;   // tile's middle
+
+    unsigned goff[NI];
+    int grow[NI];
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+        const int e = 64 * i + lane, row = e / NU, u = e % NU;
+        const int gq = cg * NQ + u, zq = gq / K4 - z0, kq = gq % K4;
+        goff[i] = row * Kb + (LIST ? zq * (unsigned)Ns * Kb + kq * 16u : (kq0 + u) * 16u);
+        grow[i] = u < NQ && gq < Nz * K4 && row < BS_ROWS ? row : -(1 << 28);
+    }
+    const unsigned ring = (unsigned)(size_t)(__attribute__((address_space(3))) char *)smem + wave * WVB;
+    // this wave's class i (past the end: the last class again, not summed)
+    auto cls = [&](int i) { return min(4 * i + wave, n0 - 1); };
+    // bin of the window's row 0: one below the lowest position of the tile
+    auto first = [&](double cs, double sn) {
+        return (int)floor(fma(xm, cs, fma(ym, sn, hS)) - 3.5 * (fabs(cs) + fabs(sn))) - 1;
+    };
+    auto issue = [&](int b) {   // batch b into half b & 1 of the ring
+#pragma unroll
+        for (int c = 0; c < BS_CB; ++c) {
+            const int a = cls(BS_CB * b + c);
+            const int lo = __builtin_amdgcn_readfirstlane(first(ccos[a], csin[a]));
+            const char *base = (const char *)gt + ((size_t)a * Nz + z0) * Ns * Kb;
+            const unsigned end = (LIST ? min(Nz - z0, NQ) : 1) * (unsigned)Ns * Kb;
+            const i4 rs{(int)(unsigned)(size_t)base, (int)(((size_t)base >> 32) & 0xffff), (int)end, 0x00020000};
+            const unsigned dst = ring + ((b & 1) * BS_CB + c) * CLB;
+#pragma unroll
+            for (int i = 0; i < NI; ++i) {
+                const unsigned off = (unsigned)(grow[i] + lo) < (unsigned)Ns ? goff[i] + (unsigned)lo * Kb : 0xffffff00u;
+                asm volatile("buffer_load_dwordx4 %0, %1, 0 offen lds"
+                             :: "v"(off), "s"(rs), "{m0}"(__builtin_amdgcn_readfirstlane(dst + i * 1024u))
+                             : "memory");
+            }
+        }
+    };
+
+    float acc[NQ][4];
+#pragma unroll
+    for (int k = 0; k < NQ; ++k)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) acc[k][t] = 0.f;
+    const int ncl = (n0 - wave + 3) / 4;   // this wave's classes
+    const int nb = (ncl + BS_CB - 1) / BS_CB;
+    if (nb > 0) issue(0);
+    for (int b = 0; b < nb; ++b) {
+        issue(b + 1);   // always, so that the count below is this batch's
+        asm volatile("s_waitcnt vmcnt(%0)" :: "n"(BS_CB * NI) : "memory");
+#pragma unroll
+        for (int c = 0; c < BS_CB; ++c) {
+            if (BS_CB * b + c >= ncl) break;
+            const int a = cls(BS_CB * b + c);
+            const double cs = ccos[a], sn = csin[a];
+            const float ic = (float)(1.0 / fmax(fabs(cs), fabs(sn)));
+            const double s = fma(x, cs, fma(y, sn, hS)), fl = floor(s);
+            const float fr = (float)(s - fl);
+            const float w0 = fminf(fmaxf(fmaf(-fr, ic, 1.f), 0.f), 1.f);
+            const float w1 = fminf(fmaxf(fmaf(fr, ic, 1.f - ic), 0.f), 1.f);
+            const unsigned t0 = ring + ((b & 1) * BS_CB + c) * CLB + __umul24((unsigned)((int)fl - first(cs, sn)), NU * 16u);
+#pragma unroll
+            for (int k = 0; k < NQ; ++k) {
+                const v4 x0 = *(lds_v4 *)(size_t)(t0 + 16 * k), x1 = *(lds_v4 *)(size_t)(t0 + 16 * (NU + k));
+#pragma unroll
+                for (int t = 0; t < 4; ++t) acc[k][t] = fmaf(w1, x1[t], fmaf(w0, x0[t], acc[k][t]));
+            }
+        }
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    // the waves' sums, [wave][NQ][lane]; wave w adds and writes quads w, w + 4, ..
+    v4 *sums = (v4 *)smem;
+#pragma unroll
+    for (int k = 0; k < NQ; ++k)
+        sums[(wave * NQ + k) * 64 + lane] = v4{acc[k][0], acc[k][1], acc[k][2], acc[k][3]};
+    __syncthreads();
+    if (wave >= NQ || q >= N || r >= N) return;
+    v4 v = sums[wave * 64 + lane];
+#pragma unroll
+    for (int w = 1; w < 4; ++w) v += sums[(w * NQ + wave) * 64 + lane];
+    const int gq = cg * NQ + wave, z = gq / K4, c0 = 4 * (gq % K4);
+    if (z >= Nz) return;
+    float *dst = out + (((size_t)z * N + r) * N + q) * K + c0;
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+        if (c0 + t < K) dst[t] = v[t];
+}
+
+template <int NQ>
+static void launch_bp_small(const Plan &p, float *out, hipStream_t s, int ncg, bool list)
+{
+    const rt_geom &G = p.g;
+    BpArgs A{G.N, G.Nz, G.Ns, G.K, (G.K + 3) / 4, p.n0, (G.N + 7) / 8, (G.N + 7) / 8, 0};
+    A.nblocks = (unsigned)ncg * A.ntq * A.ntr;
+    const size_t lds = (size_t)4 * 2 * BS_CB * bs_copies(NQ) * 1024;
+    KTimer kt("k_backproject", s);
+    if (list)
+        hipLaunchKernelGGL((k_backproject_small<NQ, true>), dim3(A.nblocks), dim3(NT), lds, s, p.d_scr,
+                           out, p.d_ccos, p.d_csin, A);
+    else
+        hipLaunchKernelGGL((k_backproject_small<NQ, false>), dim3(A.nblocks), dim3(NT), lds, s, p.d_scr,
+                           out, p.d_ccos, p.d_csin, A);
+    kt.stop();
+}
+
 template <int NQ, int VPT>
 static void launch_bp_t(const Plan &p, float *out, hipStream_t s, int ncg, bool list)
 {
@@ -253,10 +392,24 @@ int launch_backproject(const Plan &p, float *out, hipStream_t s)
     const int NQ = tq >= 3 ? 4 : tq;
     const int ncg = (tq + NQ - 1) / NQ;
     const bool list = K4 % NQ != 0;
-    // 32 x 32 tiles where they give every CU its four workgroups, else 32 x 8
-    // (a pixel's bits are the same)
-    const long tiles = (long)ncg * ((G.N + 31) / 32) * ((G.N + 31) / 32);
-    const bool small = tiles < 1024;
+    // 32 x 32 tiles where they give every CU its four workgroups, else 32 x 8 (a
+    // pixel's bits are the same); where those hold less than 1024 channel
+    // quads, 8 x 8 tiles, whose sums have an order of their own: the choice
+    // follows from nz_ref, not from Nz, so that a slab and its volume agree.
+    // Measured, 32 x 8 against 8 x 8: 512 quads (256^2, K = 8) 35 and 30 us,
+    // 1024 quads (256^2, K = 16) 42 and 46 us
+    const long t32 = (G.N + 31) / 32;
+    const long ref = std::max((long)p.nz_ref * K4, 1L) * t32 * ((G.N + 7) / 8);
+    const bool small = ncg * t32 * t32 < 1024;
+    if (ref < 1024) {
+        switch (NQ) {
+        case 4: launch_bp_small<4>(p, out, s, ncg, list); break;
+        case 2: launch_bp_small<2>(p, out, s, ncg, list); break;
+        default: launch_bp_small<1>(p, out, s, ncg, list); break;
+        }
+        RT_HIP(hipGetLastError());
+        return RT_OK;
+    }
     switch (NQ) {
     case 4: small ? launch_bp_t<4, 1>(p, out, s, ncg, list) : launch_bp_t<4, 4>(p, out, s, ncg, list); break;
     case 2: small ? launch_bp_t<2, 1>(p, out, s, ncg, list) : launch_bp_t<2, 4>(p, out, s, ncg, list); break;
