@@ -208,6 +208,7 @@ int launch_forward(const Plan &p, const float *f, float *g, int mode, const floa
                    float *h1, float sigma, double *part, hipStream_t s);
 int launch_adjoint(const Plan &p, const float *g, float *out, hipStream_t s);
 unsigned voxel_blocks(const rt_geom &g);  // workgroups (= partials) of the voxel kernels
+unsigned grad_blocks(const rt_geom &g);   // of the gradient kernels
 
 // 4D TV (tv.hip)
 int launch_tv_grad(const Plan &p, const float *f, float lambda2, float *pout, hipStream_t s);

@@ -271,7 +271,7 @@ int solve_ooc(const rt_geom &G, const double *phi, const double *Smat, const rt_
             return rc;
         res2 += v;
         if ((rc = launch_tv_norm(*pg, fD + vf, l2, pg->d_part, s, 0, S)) ||
-            (rc = launch_finish(pg->d_part, (int)voxel_blocks(pg->g), 1, pg->d_red, s)) ||
+            (rc = launch_finish(pg->d_part, (int)grad_blocks(pg->g), 1, pg->d_red, s)) ||
             (rc = fetch_red(*pg, &v, s)))
             return rc;
         tv += v;

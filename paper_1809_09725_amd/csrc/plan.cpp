@@ -501,7 +501,7 @@ static int create(const rt_geom *geom, rt_form form, rt_prec prec, const double 
     }
     // FP64 partials: h1 prox, shrink, primal update (two per workgroup), reductions
     p.part_cap = std::max<size_t>((size_t)1 << 18,
-                                  (size_t)forward_partials(p) + 3 * (size_t)voxel_blocks(p.g) + 64);
+                                  (size_t)forward_partials(p) + grad_blocks(p.g) + 2 * (size_t)voxel_blocks(p.g) + 64);
     RT_HIP(hipMalloc(&p.d_part, p.part_cap * sizeof(double)));
     RT_HIP(hipMalloc(&p.d_red, 16 * sizeof(double)));
     p.bytes += (p.part_cap + 16) * sizeof(double);

@@ -16,7 +16,7 @@ namespace {
 // Slots of Plan::d_part: the h1 prox's partials first, then the shrink's,
 // then the (two-wide) primal update's.
 size_t off_grad(const Plan &p) { return (size_t)forward_partials(p); }
-size_t off_div(const Plan &p) { return off_grad(p) + voxel_blocks(p.g); }
+size_t off_div(const Plan &p) { return off_grad(p) + grad_blocks(p.g); }
 
 // |S|_2 = sqrt(largest eigenvalue of S^T S), cyclic Jacobi on the K x K matrix.
 double s_norm(const Plan &p)
@@ -233,7 +233,7 @@ int step_job(Job &J, int n, hipStream_t s)
         if (check && p.g.Nz > 0) {
             const int nbv = (int)voxel_blocks(p.g);
             if ((rc = launch_finish(pf, forward_partials(p), 1, p.d_red, s))) return rc;
-            if ((rc = launch_finish(pg, nbv, 1, p.d_red + 1, s))) return rc;
+            if ((rc = launch_finish(pg, (int)grad_blocks(p.g), 1, p.d_red + 1, s))) return rc;
             if ((rc = launch_finish(pd, nbv, 2, p.d_red + 2, s))) return rc;
             double m[4];
             if ((rc = fetch(p, 4, m, s))) return rc;
@@ -259,7 +259,7 @@ int report_job(Job &J, rt_solve_report *rep, hipStream_t s)
         if (!rc) rc = launch_diff_sq_partials(J.sino, J.g, ng, p.d_part, nbg, s);
         if (!rc) rc = launch_finish(p.d_part, nbg, 1, p.d_red, s);
         if (!rc) rc = launch_tv_norm(p, J.f, (float)J.prm.lambda2, p.d_part + off_grad(p), s);
-        if (!rc) rc = launch_finish(p.d_part + off_grad(p), (int)voxel_blocks(p.g), 1, p.d_red + 1, s);
+        if (!rc) rc = launch_finish(p.d_part + off_grad(p), (int)grad_blocks(p.g), 1, p.d_red + 1, s);
         if (!rc && J.prm.mu > 0) rc = launch_dot_partials(J.f, J.f, nf, p.d_part, nbf, s);
         if (!rc && J.prm.mu > 0) rc = launch_finish(p.d_part, nbf, 1, p.d_red + 2, s);
         if (!rc) rc = fetch(p, J.prm.mu > 0 ? 3 : 2, m, s);
