@@ -71,7 +71,7 @@ struct RayCfg {
     int NLP = 1;          // line parts (> 1: partial sums, added by k_contract)
     int nth = RAY_NTH;    // threads per workgroup
     bool tl = false;      // two-level ray sums (N > 512)
-    bool fused = true;    // contraction in the epilogue
+    bool fusable = true;  // a workgroup can contract its own sums
     unsigned nblocks = 0;
     size_t lds = 0;       // bytes of LDS per workgroup
 };

@@ -233,7 +233,7 @@ RayCfg ray_cfg(const Plan &p)
     R.nth = L.small ? RAY_NTH_SMALL : RAY_NTH;
     R.group0 = L.small ? p.ngroups : 0;
     R.ngroups = L.small ? (int)p.groups.size() - p.ngroups : p.ngroups;
-    R.fused = R.NLP == 1 && !R.tl && R.K4 <= R.NQ && R.NQ % R.K4 == 0;
+    R.fusable = R.NLP == 1 && !R.tl && R.K4 <= R.NQ && R.NQ % R.K4 == 0;
     R.nblocks = (unsigned)R.ncg * R.ngroups * R.NLP;
     // stage buffers: as k_project lays them out
     const int rpj = R.nth / R.NQ, pf = L.small ? RAY_PF_SMALL : RAY_PF;

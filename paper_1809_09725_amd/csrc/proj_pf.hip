@@ -34,19 +34,14 @@ __device__ inline int clamp0_i32(int x, int hi)
     return r;
 }
 
-// What the projection does with its sums P(a,z,b,k): store them (EPI_P), or,
-// when one workgroup holds all K channels of its slices and all lines,
+// What the projection does with its sums P(a,z,b,k): store them (g == NULL),
+// or, when one workgroup holds all K channels of its slices and all lines,
 // contract them with Phi over the Npi half-turns with the s-flip (Sec. 4, eq.
-// radapr and the pi-periodicity) and store g (EPI_G) or apply the h1 prox of
-// Fig. 2 step 3 (EPI_PROX).
-enum { EPI_P = 0, EPI_G = 1, EPI_PROX = 2 };
+// radapr and the pi-periodicity) and store g.
 struct FwdEpi {
     const float *phi;     // [Ntheta][4 K4], channels K.. zero
-    float *out;           // g (EPI_G) or h1 (EPI_PROX)
-    const float *gdata;   // measured sinogram (EPI_PROX)
-    double *part;         // per-workgroup FP64 sum of (R f~ - g)^2, or NULL
-    float sigma;
-    int mode, n0, Npi;
+    float *g;
+    int n0, Npi;
 };
 
 // Work split of k_project (host: RayCfg).
@@ -116,7 +111,6 @@ __global__ __launch_bounds__(NTH) void k_project(
     constexpr int SH = NQ == 4 ? 6 : NQ == 2 ? 5 : 4;   // log2 of a row's bytes
     constexpr int RPJ = NTH / NQ;                       // rows one float4 per thread covers
     extern __shared__ __align__(64) char smem[];        // [2][NLS][W rows][NQ] float4
-    __shared__ double sh[NW];
     const int N = A.N, Ns = A.Ns, K = A.K, K4 = A.K4;
     unsigned lid = xcd_remap(blockIdx.x, A.nblocks);
     const int grp = lid % A.ngroups;
@@ -384,15 +378,10 @@ __global__ __launch_bounds__(NTH) void k_project(
     }
 
     // ---- epilogue
-    if (TL || E.mode == EPI_P) {
+    if (TL || !E.g) {
         flush();
         return;
     }
-    double d2 = 0.0;
-    const float inv1s = 1.f / (1.f + E.sigma);
-    const float *__restrict__ phi = E.phi;
-    const float *__restrict__ gd = E.gdata;
-    float *__restrict__ out = E.out;
 #pragma unroll
     for (int j = 0; j < PPT; ++j) {
         const int a = cl[j], b = bin[j];
@@ -405,19 +394,10 @@ __global__ __launch_bounds__(NTH) void k_project(
             float s[NQ];
 #pragma unroll
             for (int q = 0; q < NQ; ++q)
-                s[q] = dot4(*(const float4 *)(phi + (size_t)i * Kp + 4 * ((q ^ rq) & (K4 - 1))), sums(j, q));
+                s[q] = dot4(*(const float4 *)(E.phi + (size_t)i * Kp + 4 * ((q ^ rq) & (K4 - 1))), sums(j, q));
             const int bo = (r & 1) ? Ns - 1 - b : b;
             auto put = [&](int sl, float v) {   // slice sl of the workgroup
-                const int z = z0 + sl;
-                if (z >= A.Nz) return;
-                const size_t o = ((size_t)i * A.Nz + z) * Ns + bo;
-                if (E.mode == EPI_G) {
-                    out[o] = v;
-                } else {
-                    const float d = v - gd[o];
-                    d2 += (double)d * (double)d;
-                    out[o] = (out[o] + E.sigma * d) * inv1s;
-                }
+                if (z0 + sl < A.Nz) E.g[((size_t)i * A.Nz + z0 + sl) * Ns + bo] = v;
             };
             if (K4 == 1) {
 #pragma unroll
@@ -429,10 +409,6 @@ __global__ __launch_bounds__(NTH) void k_project(
                 put(0, (s[0] + s[1]) + (s[2] + s[3]));
             }
         }
-    }
-    if (E.part) {
-        const double sum = block_sum(d2, sh);
-        if (tid == 0) E.part[blockIdx.x] = sum;
     }
 }
 
@@ -599,25 +575,23 @@ int launch_forward_pf(const Plan &p, const float *f, float *g, int mode, const f
     const rt_geom &G = p.g;
     if (G.Nz == 0) return RT_OK;
     const RayCfg R = ray_cfg(p);
-    FwdEpi E{};
-    E.phi = p.d_phip;
-    E.out = mode == CONTRACT_STORE ? g : h1;
-    E.gdata = gdata;
-    E.part = R.fused ? part : nullptr;
-    E.sigma = sigma;
-    E.mode = !R.fused ? EPI_P : (mode == CONTRACT_STORE ? EPI_G : EPI_PROX);
-    E.n0 = p.n0;
-    E.Npi = G.Npi;
+    // The h1 prox runs in k_contract: its reads of g and h1 at the end of the
+    // projection, one workgroup per CU, are covered by nothing (512^2 x 32: 2.84
+    // ms with the prox inside, 2.69 + 0.12 without); so are the stores of many
+    // half-turns (40 of them: 346 us inside, 293 + 29 us outside; 10 of them
+    // at 512^2 x 128: 9.90 ms inside, 9.77 + 0.26 outside).
+    const bool fused = R.fusable && mode == CONTRACT_STORE && G.Npi <= 16;
+    const FwdEpi E{p.d_phip, fused ? g : nullptr, p.n0, G.Npi};
     const int rc = R.NQ == 4   ? launch_project_q<4>(p, R, f, E, s)
                    : R.NQ == 2 ? launch_project_q<2>(p, R, f, E, s)
                                : launch_project_q<1>(p, R, f, E, s);
     if (rc) return rc;
     RT_HIP(hipGetLastError());
-    if (R.fused) return RT_OK;
+    if (fused) return RT_OK;
     const ContractGrid c = contract_grid(p);
     KTimer kt("k_contract", s);
 #define RT_CONTRACT(Q) hipLaunchKernelGGL(k_contract<Q>, dim3(c.nb), dim3(NT), 0, s, p.d_scr, p.d_phip, \
-                                          E.out, gdata, mode, sigma, part, G.Nz, G.Ns, R.K4, p.n0,    \
+                                          mode == CONTRACT_STORE ? g : h1, gdata, mode, sigma, part, G.Nz, G.Ns, R.K4, p.n0,    \
                                           G.Npi, R.NLP, c.EPT, c.nch)
     if (R.K4 <= 2) RT_CONTRACT(2);
     else if (R.K4 <= 4) RT_CONTRACT(4);
@@ -629,12 +603,10 @@ int launch_forward_pf(const Plan &p, const float *f, float *g, int mode, const f
     return RT_OK;
 }
 
-int forward_partials(const Plan &p)
+int forward_partials(const Plan &p)   // of the h1 prox
 {
     if (p.form == RT_FORM_SF) return (int)sf_partials(p);
-    if (p.g.Nz == 0) return 1;
-    const RayCfg R = ray_cfg(p);
-    return (int)(R.fused ? R.nblocks : contract_grid(p).nb);
+    return (int)contract_grid(p).nb;
 }
 
 int launch_forward(const Plan &p, const float *f, float *g, int mode, const float *gdata,
