@@ -78,19 +78,15 @@ struct RayCfg {
 
 // Synthesise-first (precision) projector: A classes per group, NPP frame
 // columns each (Npi rounded up to 4), A * NPP <= 32 columns in one MFMA tile;
-// lines in chunks of PCH positions, CS floats per LDS row; the BF16 shadow of
-// f has KP = K rounded up to 16 channels per voxel.
+// lines in chunks of PCH positions; the BF16 shadow of f has KP = K rounded up to 16 channels per voxel.
 struct SfCfg {
-    int A = 1, ngroups = 0, BT = 1, nbt = 1, PCH = 32, CS = 20, NPP = 4, KP = 16;
+    int A = 1, ngroups = 0, BT = 1, nbt = 1, PCH = 32, NPP = 4, KP = 16;
     int UB = 1;           // bins per thread and class slot (BT = 512 UB covers Ns <= 2048)
     // line parts: with NLP > 1 a workgroup walks N / NLP lines of its slice
     // and stores partial ray sums, which k_sf_finish adds in a fixed order
     // (large slices: the BF16 copy of one part then stays in the last-level
     // cache while every class group of the slice streams it)
     int NLP = 1;
-    // B operand staging: 0 = through registers, one step ahead; 3 = global ->
-    // LDS copies into a 3-stage ring per wave, two steps ahead (KB = 2)
-    int DS = 0;
     size_t lds = 0;
 };
 

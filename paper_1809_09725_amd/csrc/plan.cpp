@@ -421,20 +421,9 @@ static int configure(Plan &p, TableUpload &up)
         C.KP = (g.K + 15) / 16 * 16;
         // an odd number of 16-byte groups per row: 16 consecutive positions
         // of a b128 access fall in distinct bank groups
-        const int c4 = C.A * C.NPP / 4;
-        C.CS = 4 * (c4 % 2 ? c4 : c4 + 1);
-        C.lds = (size_t)(C.PCH + 2) * C.CS * sizeof(float);
+        const int row = 4 * ((sf_slots(C.NPP, C.UB, kb) * C.NPP / 4) | 1);
+        C.lds = (size_t)2 * (C.PCH + 3) * row * sizeof(float);
         C.NLP = sf_line_parts(g);
-        // the staged B operand (8 waves x 3 stages x 2 KB copies of 1 KiB) for
-        // 17..32 channels: there the per-step B loads are twice as large and
-        // their latency bounds the step (2048^2 slab: 315 -> 252 ms); with 16
-        // channels the ring's LDS costs more than it hides (512^2: one
-        // workgroup per CU instead of two, 18.5 -> 28.6 ms)
-        const size_t ring = (size_t)8 * 3 * 2 * kb * 1024;
-        if (kb == 2 && C.lds + ring <= 160 * 1024) {
-            C.DS = 3;
-            C.lds += ring;
-        }
     }
 
     up.add(&p.d_wcls, wcls);

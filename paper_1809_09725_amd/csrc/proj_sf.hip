@@ -27,7 +27,7 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 
-constexpr int ST = 512;        // threads of a synthesise-first workgroup (8 wave64)
+constexpr int ST = 1024;       // threads of a synthesise-first workgroup (16 wave64)
 
 // FP32 -> BF16 with round-to-nearest-even (finite inputs).
 __device__ inline unsigned short bf16_rne(float x)
@@ -46,23 +46,13 @@ struct SfEpi {
     int prox, n0, Npi;
 };
 
-// Forward, synthesise-first.  Workgroup: slice z, a group of A classes of one
-// walk direction, bins [bt*BT, bt*BT + BT), and part lp of the NLP parts of
-// the slice's lines (NLP > 1: the ray sums over those lines are stored at
-// E.out + lp * E.pstride for k_sf_finish).  Consecutive workgroups take the
-// class groups of one part, so the part's BF16 lines are read while they are
-// still cached.  Thread t owns the rays (slot j, bin bt*BT + t') for the A
-// slots, t' being t reordered within its wave by slot j's lane map.  NPP:
-// frame columns per class (Npi rounded up to 4, the padding columns are
-// zero); KB: MFMA k-steps of 16 channels.
-//
-// The frames F[c][pos] = sum_k Phi[i(c)][k] f_k(pos) of a chunk of PCH
-// positions are one v_mfma_f32_32x32x16_bf16 product per 32-position tile:
-// A = Phi rows of the 32 frame columns (hi and lo BF16 parts), B = the BF16
-// shadow of f.  They land in LDS position-major, row 1 + pos - c0 holding the
-// A*NPP frames of position pos, so that a ray's tap at one position is NPP/4
-// 16-byte reads, the access of the plain form's staged lines.
-// The bin offset thread tid takes for class a: its own, reordered within its
+__device__ inline long long uniform64(long long v)
+{
+    return (long long)(((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32) |
+                       (unsigned)__builtin_amdgcn_readfirstlane((int)v));
+}
+
+// The bin offset thread tid (of the NB side by side) takes for class a: its own, reordered within its
 // wave's block of 64 bins by the class's lane map (the 16-lane tap reads at
 // positions 1/|c| apart then spread over the LDS bank groups; the row stride
 // CS is an odd number of 16-byte groups).
@@ -71,16 +61,48 @@ __device__ inline int sf_bin(int tid, int a, const unsigned char *__restrict__ l
     return a >= 0 ? (tid & ~63) | (int)lperm[a * 64 + (tid & 63)] : tid;
 }
 
-template <int NPP, int KB, int AS, int UB, int DS>
+// Forward, synthesise-first.  Workgroup: slice z, a group of A classes of one
+// walk direction, bins [bt*BT, bt*BT + BT), and part lp of the NLP parts of
+// the slice's lines (NLP > 1: the ray sums over those lines are stored at
+// E.out + lp * E.pstride for k_sf_finish).  Consecutive workgroups take the
+// class groups of one part, so the part's BF16 lines are read while they are
+// still cached.  A thread owns the rays (slot, bin) of its half of the A slots
+// (of the one slot, where there is one) at UT bins each.  NPP: frame columns
+// per class (Npi rounded up to 4, the padding columns are zero); KB: MFMA
+// k-steps of 16 channels.
+//
+// The frames F[c][pos] = sum_k Phi[i(c)][k] f_k(pos) of a chunk of PCH
+// positions are one v_mfma_f32_32x32x16_bf16 product per 32-position tile,
+// one tile per wave: A = Phi rows of the 32 frame columns (hi and lo BF16
+// parts), B = the BF16 shadow of f.  They land in LDS position-major, row
+// 1 + pos - c0 holding the frames of position pos, so that a ray's tap at one
+// position is NPP/4 16-byte reads, the access of the plain form's staged lines.
+//
+// What bounds it: per line of 1024 positions and 4 classes of 8 half-turns the
+// LDS takes about 2100 cycles (1024 for the frames' stores, 1100 for the
+// taps' reads), the vector units 1300 and the matrix cores 1024, of 5300 in
+// all; the operand loads (128-byte lines, of which a column walk uses half)
+// are hidden.  Two frame buffers let one barrier per step do, with the
+// products of the next step running under the taps of this one; 16 waves of
+// half the rays each keep more of the LDS reads in flight than 8.  Measured,
+// 1024^2 x 8, 256 classes, 8 half-turns, K = 32: 7.25 ms with one buffer and
+// two barriers per chunk, 5.58 with two buffers and 8 waves, 4.66 as it is;
+// 512^2 x 16, 180 classes, K = 16: 2.22 -> 1.50 ms; 2048^2 x 2, K = 32:
+// 12.7 -> 7.4 ms.
+template <int NPP, int KB, int AS, int UB>
 __global__ __launch_bounds__(ST) void k_project_sf(
     const __bf16 *__restrict__ f16, const float *__restrict__ phi, const int *__restrict__ gcls,
     const int *__restrict__ gwalk, const unsigned char *__restrict__ lperm, const double *__restrict__ ccos,
     const double *__restrict__ csin, int N, int Nz, int Ns, int K, int A, int ngroups, int BT,
-    int nbt, int PCH, int CS, int NLP, unsigned nblocks, SfEpi E)
+    int nbt, int PCH, int NLP, unsigned nblocks, SfEpi E)
 {
     constexpr int KP = 16 * KB;
-    constexpr int R = AS * UB;      // rays per thread: slot rho / UB, bin sf_bin(tid) + ST * (rho % UB)
-    extern __shared__ float fr[];   // [PCH + 2][CS]; rows 0 and PCH + 1 stay zero
+    constexpr int CS = 4 * ((AS * NPP / 4) | 1);   // floats per row
+    // waves: with several slots, the two halves of the workgroup take half of
+    // the slots each; NB threads side by side take UT bins each per slot
+    constexpr int SH = AS > 1 ? 2 : 1, AT = AS / SH, NB = ST / SH, UT = (UB * 512 + NB - 1) / NB;
+    constexpr int R = AT * UT;      // rays per thread: slot j0 + rho / UT, bin sf_bin(tb) + NB * (rho % UT)
+    extern __shared__ float fr[];   // two buffers [PCH + 3][CS]; rows 0, PCH + 1 and PCH + 2 stay zero
     __shared__ double sh[ST / 64];
     unsigned lid = xcd_remap(blockIdx.x, nblocks);
     const int bt = lid % nbt;
@@ -90,34 +112,34 @@ __global__ __launch_bounds__(ST) void k_project_sf(
     const int lp = lid % NLP;
     const int z = lid / NLP;
     const int lbeg = (int)((long)lp * N / NLP), lend = (int)((long)(lp + 1) * N / NLP);
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int half = SH > 1 ? wave / (NB / 64) : 0, tb = tid - half * NB, j0 = half * AT;
     const int walk = gwalk[grp];
     const int Npi = E.Npi;
-    const int CW = A * NPP;        // frame columns in use
     const double hN = 0.5 * (double)(N - 1), hS = 0.5 * (double)(Ns - 1);
 
-    // ---- rays of this thread
-    double base[R], slope[R];
-    float invc[R];
+    // ---- rays of this thread: position on line lbeg and its step per line
+    // (one value per class), in 32.32 fixed point as in the plain projector:
+    // FP64 once, then one exact integer add per line (the position carries the
+    // rounding of its start and of l s alone, below 2^-32 (1 + l)).  A ray
+    // outside the tile starts at -1e6 and stays outside.
+    long long U[R], Sl[AT];
+    float invc[AT];
 #pragma unroll
-    for (int rho = 0; rho < R; ++rho) {
-        const int j = rho / UB;
-        const int a = j < A ? gcls[grp * A + j] : -1;
-        const int bi = sf_bin(tid, a, lperm) + ST * (rho % UB), b = bt * BT + bi;
-        base[rho] = -1.0e9;   // far outside: never tapped
-        slope[rho] = 0.0;
-        invc[rho] = 0.f;
-        if (a >= 0 && bi < BT && b < Ns) {
-            const double cs = ccos[a], sn = csin[a], sb = (double)b - hS;
-            if (walk == 0) {
-                base[rho] = sb / cs + hN;
-                slope[rho] = -sn / cs;
-                invc[rho] = (float)(1.0 / fabs(cs));
-            } else {
-                base[rho] = sb / sn + hN;
-                slope[rho] = -cs / sn;
-                invc[rho] = (float)(1.0 / fabs(sn));
-            }
+    for (int j = 0; j < AT; ++j) {
+        const int a = j0 + j < A ? gcls[grp * A + j0 + j] : -1;
+        const double cs = a >= 0 ? ccos[a] : 1.0, sn = a >= 0 ? csin[a] : 0.0;
+        const double d = a < 0 || walk == 0 ? cs : sn, n = a < 0 || walk == 0 ? sn : cs;
+        const double slope = -n / d;
+        invc[j] = (float)(1.0 / fabs(d));
+        Sl[j] = uniform64((long long)llrint(slope * 4294967296.0));
+#pragma unroll
+        for (int u = 0; u < UT; ++u) {
+            const int bi = sf_bin(tb, a, lperm) + NB * u, b = bt * BT + bi;
+            double u0 = -1.0e6;
+            if (a >= 0 && bi < BT && b < Ns)
+                u0 = fma((double)lbeg - hN, slope, ((double)b - hS) / d + hN);
+            U[j * UT + u] = (long long)llrint(fmin(fmax(u0, -1.0e6), 1.0e6) * 4294967296.0);
         }
     }
     float acc[R][NPP];
@@ -144,7 +166,11 @@ __global__ __launch_bounds__(ST) void k_project_sf(
             }
     }
 
-    for (int e = tid; e < 2 * CS; e += ST) fr[e < CS ? e : (PCH + 1) * CS + (e - CS)] = 0.f;
+    const int bufsz = (PCH + 3) * CS;
+    for (int e = tid; e < 6 * CS; e += ST) {
+        const int k = e / CS, r = k % 3;
+        fr[k / 3 * bufsz + (r ? PCH + r : 0) * CS + e % CS] = 0.f;
+    }
 
     const __bf16 *fz = f16 + (size_t)z * N * N * KP;
     const size_t lstep = walk == 0 ? (size_t)N * KP : (size_t)KP;
@@ -152,151 +178,122 @@ __global__ __launch_bounds__(ST) void k_project_sf(
     const int nch = (N + PCH - 1) / PCH;
     const int nsteps = (lend - lbeg) * nch;   // (line, chunk) steps of this part
 
-    // B operand of one step for the wave's position tiles wave and wave + 8:
-    // lane holds position c0 + tile*32 + lane%32, channels kb*16 + 8*(lane/32) + 0..7
-    v8bf raw[2][KB];
-    auto load_step = [&](int st) {
-        const int l = lbeg + st / nch, c0 = (st % nch) * PCH;
-        const __bf16 *src = fz + (size_t)l * lstep + 8 * (lane >> 5);
+    // B operand of one step for the wave's position tile: lane holds
+    // position c0 + wave*32 + lane%32, channels kb*16 + 8*(lane/32) + 0..7.
+    // Steps are loaded in order; past the last one the last line is read again.
+    // Positions past the slice read its last one and are zeroed.
+    v8bf raw[KB];
+    const unsigned loff = (unsigned)((lane & 31) * pstep) + 8 * (lane >> 5);
+    int lch = 0, ll = lbeg;
+    auto load_step = [&]() {
+        const __bf16 *line = fz + (size_t)ll * lstep;
+        const int p0 = lch * PCH + 32 * wave;
+        if (p0 + 32 <= N) {
+            const __bf16 *src = line + (size_t)p0 * pstep;
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int t = wave + 8 * h;
-            const int pos = c0 + t * 32 + (lane & 31);
-            const bool in = t * 32 < PCH && pos < N;
-#pragma unroll
-            for (int kb = 0; kb < KB; ++kb)
-                raw[h][kb] = in ? *(const v8bf *)(src + (size_t)pos * pstep + kb * 16) : v8bf{};
-        }
-    };
-    // DS > 0: the B operand goes global -> LDS directly, DS - 1 steps ahead,
-    // into a ring of DS stages private to the wave (NI copies of 64 x 16
-    // bytes per step).  The copies are issued from inline assembly, so the
-    // compiler does not treat them as LDS stores and adds no wait for them
-    // before the frame and tap reads; each step waits for its own copies with
-    // an explicit vmcnt.  Every copy reads a valid address (positions clamped
-    // to the slice, steps clamped to the last one), so the count per step is
-    // fixed; lanes outside the slice or the chunk are zeroed after the read.
-    constexpr int NI = 2 * KB;
-    char *wring = (char *)(fr + (size_t)(PCH + 2) * CS) + (size_t)wave * (DS > 0 ? DS : 1) * NI * 1024;
-    auto issue_step = [&](int st) {
-        const int sc = min(st, nsteps - 1);
-        const int l = lbeg + sc / nch, c0 = (sc % nch) * PCH;
-        const __bf16 *src = fz + (size_t)l * lstep + 8 * (lane >> 5);
-        char *dst = wring + (size_t)(st % (DS > 0 ? DS : 1)) * NI * 1024;
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int t = wave + 8 * h;
-            const int pos = min(c0 + t * 32 + (lane & 31), N - 1);
+            for (int kb = 0; kb < KB; ++kb) raw[kb] = *(const v8bf *)(src + loff + kb * 16);
+        } else {
+            const int pos = p0 + (lane & 31);
+            const __bf16 *src = line + (size_t)min(pos, N - 1) * pstep + 8 * (lane >> 5);
 #pragma unroll
             for (int kb = 0; kb < KB; ++kb) {
-                const __bf16 *ga = src + (size_t)pos * pstep + kb * 16;
-                const unsigned la = (unsigned)(size_t)(dst + (h * KB + kb) * 1024);
-                // the LDS destination goes in m0, bound as an input operand
-                asm volatile("global_load_lds_dwordx4 %0, off"
-                             :: "v"(ga), "{m0}"(__builtin_amdgcn_readfirstlane(la)) : "memory");
+                const v8bf x = *(const v8bf *)(src + kb * 16);
+                raw[kb] = pos < N ? x : v8bf{};
+            }
+        }
+        if (++lch == nch) {
+            lch = 0;
+            ll = min(ll + 1, lend - 1);
+        }
+    };
+    // the frames of one step
+    v16f d;
+    auto frames = [&]() {
+        d = v16f{};
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb) {
+            d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ahi[kb], raw[kb], d, 0, 0, 0);
+            d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(alo[kb], raw[kb], d, 0, 0, 0);
+        }
+    };
+    // ... into a buffer.  D[c][pos]: lane holds position lane%32 of its tile,
+    // columns 8g + 4(lane/32) + 0..3
+    auto store = [&](int buf) {
+        if (wave * 32 >= PCH) return;
+        float *row = fr + buf * bufsz + (1 + wave * 32 + (lane & 31)) * CS + 4 * (lane >> 5);
+#pragma unroll
+        for (int g = 0; g < 4; ++g)
+            if (8 * g + 8 <= AS * NPP || (8 * g < AS * NPP && lane < 32))
+                *(float4 *)(row + 8 * g) = make_float4(d[4 * g], d[4 * g + 1], d[4 * g + 2], d[4 * g + 3]);
+    };
+    // Taps of the rays whose positions fall in step st's chunk: rows q and
+    // q + 1 of the line, -1 <= q < PCH relative to the chunk; the zero rows on
+    // both sides stand for the neighbouring chunks' positions and for those
+    // outside the slice.  The rays of one bin set are taken together wherever
+    // one of the wave's is in the chunk (the group's classes are close in
+    // angle), the others reading the two zero rows at the end.
+    int row[R];
+    float frc[R];
+    int ch = 0;
+    auto taps = [&](int buf) {
+        if (ch == 0) {   // ray positions on this step's line
+#pragma unroll
+            for (int rho = 0; rho < R; ++rho) {
+                const unsigned q = (unsigned)(int)(U[rho] >> 32) + 1u;
+                frc[rho] = (float)(unsigned)U[rho] * 2.3283064365386963e-10f;
+                U[rho] += Sl[rho / UT];
+                row[rho] = q <= (unsigned)N ? (int)q : 1 << 28;
+            }
+        }
+        const int c0 = ch * PCH;
+        ch = ch + 1 == nch ? 0 : ch + 1;
+        const float *fb = fr + buf * bufsz + j0 * NPP;
+#pragma unroll
+        for (int u = 0; u < UT; ++u) {
+            unsigned q[AT];
+            bool any = false;
+#pragma unroll
+            for (int j = 0; j < AT; ++j) {
+                q[j] = min((unsigned)(row[j * UT + u] - c0), (unsigned)PCH + 1u);
+                any |= q[j] <= (unsigned)PCH;
+            }
+            if (!__any(any)) continue;
+#pragma unroll
+            for (int j = 0; j < AT; ++j) {
+                const int rho = j * UT + u;
+                const float a1 = frc[rho], a0 = 1.f - a1;
+                const float *F0 = fb + __umul24(q[j], CS) + j * NPP;
+#pragma unroll
+                for (int m = 0; m < NPP / 4; ++m) {
+                    const float4 x0 = *(const float4 *)(F0 + 4 * m);
+                    const float4 x1 = *(const float4 *)(F0 + CS + 4 * m);
+                    acc[rho][4 * m + 0] = fmaf(a1, x1.x, fmaf(a0, x0.x, acc[rho][4 * m + 0]));
+                    acc[rho][4 * m + 1] = fmaf(a1, x1.y, fmaf(a0, x0.y, acc[rho][4 * m + 1]));
+                    acc[rho][4 * m + 2] = fmaf(a1, x1.z, fmaf(a0, x0.z, acc[rho][4 * m + 2]));
+                    acc[rho][4 * m + 3] = fmaf(a1, x1.w, fmaf(a0, x0.w, acc[rho][4 * m + 3]));
+                }
             }
         }
     };
-    if constexpr (DS > 0) {
-        if (nsteps > 0)
-            for (int d = 0; d < DS - 1; ++d) issue_step(d);
-    } else {
-        if (nsteps > 0) load_step(0);
-    }
 
-    // Ray positions in 32.32 fixed point, as in the plain projector: u at
-    // line lbeg from FP64 once, then one exact integer add of the slope per
-    // line (the position carries the rounding of its start and of l s alone,
-    // below 2^-32 (1 + l)).  A ray outside the tile sits at -1e6.
-    long long U[R], Sl[R];
-#pragma unroll
-    for (int rho = 0; rho < R; ++rho) {
-        const double u0 = fmin(fmax(fma((double)lbeg - hN, slope[rho], base[rho]), -1.0e6), 1.0e6);
-        U[rho] = (long long)llrint(u0 * 4294967296.0);
-        Sl[rho] = (long long)llrint(slope[rho] * 4294967296.0);
-    }
-    int q0[R];
-    float w0[R], w1[R];
-    for (int st = 0; st < nsteps; ++st) {
-        const int c0 = (st % nch) * PCH;
-        if (c0 == 0) {   // ray positions on this step's line
-#pragma unroll
-            for (int rho = 0; rho < R; ++rho) {
-                const int q = (int)(U[rho] >> 32);
-                const float frc = (float)(unsigned)U[rho] * 2.3283064365386963e-10f;
-                U[rho] += Sl[rho];
-                const bool in = (unsigned)(q + 1) <= (unsigned)N;
-                q0[rho] = in ? q : -(1 << 28);
-                w1[rho] = in ? frc * invc[rho] : 0.f;
-                w0[rho] = in ? (1.f - frc) * invc[rho] : 0.f;
-            }
-        }
-        v8bf bop[2][KB];
-        if constexpr (DS > 0) {
-            issue_step(st + DS - 1);   // into the stage step st - 1 has finished with
-            asm volatile("s_waitcnt vmcnt(%0)" :: "n"(NI * (DS - 1)) : "memory");
-            const char *src = wring + (size_t)(st % DS) * NI * 1024 + lane * 16;
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int t = wave + 8 * h;
-                const bool in = t * 32 < PCH && c0 + t * 32 + (lane & 31) < N;
-#pragma unroll
-                for (int kb = 0; kb < KB; ++kb) {
-                    const v8bf x = *(const v8bf *)(src + (h * KB + kb) * 1024);
-                    bop[h][kb] = in ? x : v8bf{};
-                }
-            }
-        } else {
-#pragma unroll
-            for (int h = 0; h < 2; ++h)
-#pragma unroll
-                for (int kb = 0; kb < KB; ++kb) bop[h][kb] = raw[h][kb];
-            if (st + 1 < nsteps) load_step(st + 1);
-        }
-        v16f d0 = {}, d1 = {};
-#pragma unroll
-        for (int kb = 0; kb < KB; ++kb) {
-            d0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ahi[kb], bop[0][kb], d0, 0, 0, 0);
-            d1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ahi[kb], bop[1][kb], d1, 0, 0, 0);
-            d0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(alo[kb], bop[0][kb], d0, 0, 0, 0);
-            d1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(alo[kb], bop[1][kb], d1, 0, 0, 0);
-        }
-        __syncthreads();   // the previous step's taps are done with the frames
-        // D[c][pos]: lane holds position lane%32 of its tile, columns 8g + 4(lane/32) + 0..3
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int t = wave + 8 * h;
-            if (t * 32 >= PCH) continue;
-            const v16f &d = h ? d1 : d0;
-            float *row = fr + (1 + t * 32 + (lane & 31)) * CS + 4 * (lane >> 5);
-#pragma unroll
-            for (int g = 0; g < 4; ++g)
-                if (8 * g + 4 * (lane >> 5) < CW)
-                    *(float4 *)(row + 8 * g) = make_float4(d[4 * g], d[4 * g + 1], d[4 * g + 2], d[4 * g + 3]);
-        }
+    // Step st taps buffer st % 2; the matrix cores form the frames of step
+    // st + 1 meanwhile, from operands loaded one step ahead, and they are
+    // stored to the other buffer at the end.
+    if (nsteps > 0) {
+        load_step();
+        frames();
+        load_step();
+        store(0);
         __syncthreads();
-        // taps of the rays whose positions fall in this chunk
-#pragma unroll
-        for (int rho = 0; rho < R; ++rho) {
-            const int q = q0[rho] - c0;
-            const bool t0 = q >= 0 && q < PCH;
-            const bool t1 = q >= -1 && q < PCH - 1;
-            if (!(t0 || t1)) continue;
-            const float a0 = t0 ? w0[rho] : 0.f, a1 = t1 ? w1[rho] : 0.f;
-            const float *F0 = fr + (q + 1) * CS + (rho / UB) * NPP;
-#pragma unroll
-            for (int m = 0; m < NPP / 4; ++m) {
-                const float4 x0 = *(const float4 *)(F0 + 4 * m);
-                const float4 x1 = *(const float4 *)(F0 + CS + 4 * m);
-                acc[rho][4 * m + 0] = fmaf(a1, x1.x, fmaf(a0, x0.x, acc[rho][4 * m + 0]));
-                acc[rho][4 * m + 1] = fmaf(a1, x1.y, fmaf(a0, x0.y, acc[rho][4 * m + 1]));
-                acc[rho][4 * m + 2] = fmaf(a1, x1.z, fmaf(a0, x0.z, acc[rho][4 * m + 2]));
-                acc[rho][4 * m + 3] = fmaf(a1, x1.w, fmaf(a0, x0.w, acc[rho][4 * m + 3]));
-            }
+        for (int st = 0; st < nsteps; ++st) {
+            const int buf = st & 1;
+            frames();
+            load_step();
+            taps(buf);
+            store(buf ^ 1);
+            __syncthreads();
         }
     }
-
-    if constexpr (DS > 0) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the last copies landed
 
     // ---- epilogue: every half-turn r of class a lands on bin b (even r) or Ns-1-b (odd r)
     double d2 = 0.0;
@@ -307,9 +304,9 @@ __global__ __launch_bounds__(ST) void k_project_sf(
     float *__restrict__ out = E.out;
 #pragma unroll
     for (int rho = 0; rho < R; ++rho) {
-        const int j = rho / UB;
-        const int a = j < A ? gcls[grp * A + j] : -1;
-        const int bi = sf_bin(tid, a, lperm) + ST * (rho % UB), b = bt * BT + bi;
+        const int j = rho / UT;
+        const int a = j0 + j < A ? gcls[grp * A + j0 + j] : -1;
+        const int bi = sf_bin(tb, a, lperm) + NB * (rho % UT), b = bt * BT + bi;
         if (a < 0 || bi >= BT || b >= Ns) continue;
 #pragma unroll
         for (int r = 0; r < NPP; ++r) {
@@ -317,7 +314,7 @@ __global__ __launch_bounds__(ST) void k_project_sf(
             const int i = r * E.n0 + a;
             const int bo = (r & 1) ? Ns - 1 - b : b;
             const size_t o = ((size_t)i * Nz + z) * Ns + bo;
-            const float v = acc[rho][r];
+            const float v = acc[rho][r] * invc[j];
             if (!E.prox) {
                 out[o + lp * E.pstride] = v;
             } else {
@@ -454,31 +451,21 @@ __global__ __launch_bounds__(NT) void k_fold_mfma(const float *__restrict__ g,
     }
 }
 
-template <int NPP, int KB, int AS, int UB, int DS>
-static int launch_sf_d(const Plan &p, const SfEpi &E, hipStream_t s, unsigned nb)
+template <int NPP, int KB, int AS, int UB>
+static int launch_sf_t(const Plan &p, const SfEpi &E, hipStream_t s, unsigned nb)
 {
     const rt_geom &G = p.g;
     const SfCfg &C = p.sf;
-    auto kern = k_project_sf<NPP, KB, AS, UB, DS>;
+    auto kern = k_project_sf<NPP, KB, AS, UB>;
     if (C.lds > 64 * 1024)
         RT_HIP(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
                                    (int)C.lds));
     KTimer kt("k_project_sf", s);
     hipLaunchKernelGGL(kern, dim3(nb), dim3(ST), C.lds, s, (const __bf16 *)p.d_f16, p.d_phi,
                        p.d_gcls_sf, p.d_gwalk_sf, p.d_lanes, p.d_ccos, p.d_csin, G.N, G.Nz, G.Ns, G.K, C.A,
-                       C.ngroups, C.BT, C.nbt, C.PCH, C.CS, C.NLP, nb, E);
+                       C.ngroups, C.BT, C.nbt, C.PCH, C.NLP, nb, E);
     kt.stop();
     return RT_OK;
-}
-
-// the staged B operand is planned for KB = 2 only
-template <int NPP, int KB, int AS, int UB>
-static int launch_sf_t(const Plan &p, const SfEpi &E, hipStream_t s, unsigned nb)
-{
-    if constexpr (KB == 2) {
-        if (p.sf.DS == 3) return launch_sf_d<NPP, KB, AS, UB, 3>(p, E, s, nb);
-    }
-    return launch_sf_d<NPP, KB, AS, UB, 0>(p, E, s, nb);
 }
 
 // AS slots for one bin per thread; UB bins per thread take AS / UB slots

@@ -101,3 +101,32 @@ def test_slices_do_not_depend_on_the_volume(K):
     assert torch.equal(a[keep], b[keep])
     assert torch.isnan(b[3]).any() and not torch.isnan(b[3]).all()
     assert not torch.isfinite(b[9]).all()
+
+
+SF_CASES = [   # (geometry): slots per group 4, 2, 1 and 1, 2, 4 bins of 512 per slot; 16..64 channels
+    geom(37, 2, 41, 2, 9, 4), geom(64, 1, 64, 8, 7, 16), geom(33, 1, 60, 9, 6, 20), geom(31, 2, 30, 16, 5, 33),
+    geom(65, 1, 70, 17, 4, 40), geom(40, 1, 44, 27, 3, 64), geom(96, 1, 90, 32, 4, 64), geom(1, 2, 1, 3, 4, 7),
+    # lines of two and three chunks, with a few positions in the last one; one chunk exactly
+    geom(512, 1, 520, 4, 5, 8), geom(513, 1, 700, 8, 6, 32), geom(545, 1, 900, 12, 4, 24), geom(1030, 1, 300, 16, 3, 17),
+    geom(200, 1, 1300, 8, 5, 16), geom(150, 1, 2048, 12, 4, 30), geom(130, 1, 1100, 20, 3, 20), geom(90, 1, 2100, 4, 4, 64),
+]
+
+
+@pytest.mark.parametrize("G", SF_CASES, ids=lambda G: f"N{G.N}z{G.Nz}s{G.Ns}p{G.Npi}k{G.K}")
+def test_synthesise_first_edges(G):
+    """Volumes on the BF16 grid, so that only Phi's two BF16 parts (within
+    2^-17 of a value of at most 1) and FP32 sums over 2 N taps round, both
+    relative to S, the projection of sum_k |f_k|, and the positions, within
+    2^-32 (1 + l) on line l: below N^2 2^-31 of the largest sum_k |f_k| over
+    the lines (the angle pi is not exact in the oracle: rays that just miss the
+    slice have S near 1e-14 there)."""
+    torch.cuda.set_device(DEV)
+    print(f"case {G}", flush=True)
+    f = torch.from_numpy(inputs.uniform(G.f_shape, 8)).to(torch.bfloat16).to(torch.float32)
+    p = rt4d.Plan(G, form=rt4d.RT_FORM_SF, prec=rt4d.RT_PREC_BF16MFMA)
+    got = p.forward(f.to(DEV)).cpu().numpy().astype(np.float64)
+    want = O.forward(O.Geom(**G.__dict__), f.numpy())
+    G1 = O.Geom(**{**G.__dict__, "K": 1})
+    F = f.abs().sum(-1, keepdim=True).numpy()
+    S = O.forward(G1, F)
+    assert (np.abs(got - want) <= (2.0 ** -17 + 4 * G.N * 2.0 ** -24) * S + G.N ** 2 * 2.0 ** -31 * F.max()).all()
