@@ -78,14 +78,16 @@ struct RayCfg {
 
 // Synthesise-first (precision) projector: A classes per group, NPP frame
 // columns each (Npi rounded up to 4), A * NPP <= 32 columns in one MFMA tile;
-// lines in chunks of PCH positions; the BF16 shadow of f has KP = K rounded up to 16 channels per voxel.
+// lines in chunks of PCH positions; the BF16 shadow of
+// f has KP = K rounded up to 16 channels per voxel.
 struct SfCfg {
     int A = 1, ngroups = 0, BT = 1, nbt = 1, PCH = 32, NPP = 4, KP = 16;
     int UB = 1;           // bins per thread and class slot (BT = 512 UB covers Ns <= 2048)
     // line parts: with NLP > 1 a workgroup walks N / NLP lines of its slice
     // and stores partial ray sums, which k_sf_finish adds in a fixed order
     // (large slices: the BF16 copy of one part then stays in the last-level
-    // cache while every class group of the slice streams it)
+    // cache while every class group of the slice streams it; few workgroups:
+    // the parts fill the chip)
     int NLP = 1;
     size_t lds = 0;
 };
@@ -126,7 +128,7 @@ struct Plan {
     size_t part_cap = 0;        // doubles in d_part
     double *d_red = nullptr;    // final FP64 sums (16 doubles)
     void *d_f16 = nullptr;      // synthesise-first: BF16 shadow of f, [Nz][N][N][KP]
-    float *d_psf = nullptr;     // synthesise-first, NLP > 1: partial ray sums [NLP][Ntheta][Nz][Ns]
+    float *d_psf = nullptr;     // synthesise-first, large slices: partial ray sums [NLP][Ntheta][Nz][Ns] (else in d_scr)
     // bumped by every write of d_f16, so that a job knows whether the shadow
     // still holds its own f~
     mutable unsigned long long shadow_gen = 0;

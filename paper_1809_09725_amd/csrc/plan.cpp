@@ -423,7 +423,23 @@ static int configure(Plan &p, TableUpload &up)
         // of a b128 access fall in distinct bank groups
         const int row = 4 * ((sf_slots(C.NPP, C.UB, kb) * C.NPP / 4) | 1);
         C.lds = (size_t)2 * (C.PCH + 3) * row * sizeof(float);
+        // Few workgroups (one per CU fits): the lines in parts, as many as make
+        // the rounds of workgroups times a part's lines least, a workgroup's
+        // setup and its share of k_sf_finish counted as 24 lines; the partial
+        // sums go where the plain form keeps its own.  From the slices the
+        // order of the sums is planned for (p.nz_ref), like the plain form's
+        // parts.  Measured (forward): 512^2 x 1, 100 classes, 4 half-turns,
+        // K = 16: 333 us in one part, 71 in eight; 1024^2 x 2, 256 classes, 4
+        // half-turns, K = 32: 1.95 -> 1.11 ms; 256^2 x 1, 60 classes: 298 -> 46 us;
+        // 1024^2 x 8, 256 classes (512 workgroups): one part.
         C.NLP = sf_line_parts(g);
+        if (C.NLP == 1) {
+            const long wg = (long)p.nz_ref * C.ngroups * C.nbt;
+            const long room = (long)line_split(g, p.nz_ref).NLP * ((g.K + 3) / 4 * 4) / g.Npi;
+            auto cost = [&](long n) { return (wg * n + 255) / 256 * ((g.N + n - 1) / n + 24); };
+            for (long n = 2; n <= std::min<long>({room, 32, g.N}); ++n)
+                if (10 * cost(n) < 9 * cost(C.NLP)) C.NLP = (int)n;
+        }
     }
 
     up.add(&p.d_wcls, wcls);

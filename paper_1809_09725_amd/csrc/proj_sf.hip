@@ -548,7 +548,8 @@ int launch_forward_sf16(const Plan &p, float *g, int mode, const float *gdata, f
     SfEpi E{};
     float *dst = mode == CONTRACT_STORE ? g : h1;
     const bool parts = p.sf.NLP > 1;
-    E.out = parts ? p.d_psf : dst;
+    float *sums = p.d_psf ? p.d_psf : p.d_scr;
+    E.out = parts ? sums : dst;
     E.gdata = gdata;
     E.part = parts ? nullptr : part;
     E.pstride = parts ? ng_of(G) : 0;
@@ -572,7 +573,7 @@ int launch_forward_sf16(const Plan &p, float *g, int mode, const float *gdata, f
     RT_HIP(hipGetLastError());
     if (parts) {
         KTimer kt("k_sf_finish", s);
-        hipLaunchKernelGGL(k_sf_finish, dim3(sf_finish_blocks(G)), dim3(NT), 0, s, p.d_psf,
+        hipLaunchKernelGGL(k_sf_finish, dim3(sf_finish_blocks(G)), dim3(NT), 0, s, sums,
                            p.sf.NLP, ng_of(G), dst, gdata, mode == CONTRACT_PROX ? 1 : 0, sigma,
                            part);
         kt.stop();
