@@ -22,7 +22,10 @@
 // reach fewer than 16 consecutive rows per 16 lanes, which then fall in
 // distinct units).  The reads of g~ cost 128 bytes of LDS per pixel, class and
 // 16 channels; at 256 bytes per cycle and CU that is 5.3 ms at 512^2 x 128, K =
-// 16, 180 classes, and bounds the kernel with the FMAs (4.9 ms).
+// 16, 180 classes, and bounds the kernel with the FMAs (4.9 ms).  Measured there:
+// 8.33 ms with the windows staged through registers between two barriers per
+// round of classes, 6.69 as it is; one 512^2 slice, 180 classes: 193 us in 32 x
+// 32 tiles, 98 in smaller ones.
 #include "common.h"
 #include "internal.h"
 
@@ -229,7 +232,7 @@ __global__ __launch_bounds__(NT, 4) void k_backproject(const float *__restrict__
 // Few pixels: a workgroup takes 8 x 8 pixels, and its four waves take every
 // fourth class each, with windows of their own (no barriers), and add their sums
 // at the end in wave order.  A 64^2 slice is then 64 workgroups of n0 / 4
-// classes in sequence instead of 16 of n0: 21 -> 8 us at 90 classes, 8
+// classes in sequence instead of 16 of n0: 21 -> 13 us at 90 classes, 8
 // channels.  The windows' rows per pixel double, so it is for images whose 32 x 8
 // tiles leave most CUs idle.
 constexpr int BS_CB = 4;      // classes per batch of copies, two batches in flight

@@ -70,14 +70,7 @@ static double project_cost(double rounds, double lines, double blocks, int N, in
     return rounds * (lines * line + 6.0) + (parts_bytes > 0 ? 8.0 + parts_bytes / 2.0e6 : 0.0);
 }
 
-// The split of the lines and the workgroup size for nz slices.  The parts
-// fix the order in which a ray's taps are added, so they follow from nz_ref
-// alone: every plan of one volume, whole or a slab, passes the same.  One part
-// and full workgroups (32 ray blocks) where these fill the chip; else the
-// cheaper, by project_cost, of up to 16 parts of full workgroups and, for lines
-// of at most 256 positions, of workgroups of 4 ray blocks (several per CU).
-// Measured: one 512^2 slice of 16 channels over 180 classes, 46 full
-// workgroups, 577 us in one part.
+// Channel quads per workgroup: up to 4, of as many slices as it takes.
 static int quads_per_row(const rt_geom &g, int nz)
 {
     const long tq = (long)nz * ((g.K + 3) / 4);   // channel quads of nz slices
@@ -88,6 +81,14 @@ struct LineSplit {
     int NLP = 1;
     bool small = false;
 };
+// The split of the lines and the workgroup size for nz slices.  The parts
+// fix the order in which a ray's taps are added, so they follow from nz_ref
+// alone: every plan of one volume, whole or a slab, passes the same.  One part
+// and full workgroups (32 ray blocks) where these fill the chip; else the
+// cheaper, by project_cost, of up to 16 parts of full workgroups and, for lines
+// of at most 256 positions, of workgroups of 4 ray blocks (several per CU).
+// Measured: one 512^2 slice of 16 channels over 180 classes, 46 full
+// workgroups, 462 us in one part, 119 in five.
 static LineSplit line_split(const rt_geom &g, int nz)
 {
     LineSplit best;
@@ -177,7 +178,8 @@ static void ray_window(int N, int Ns, const RayDir *d, int n, int b0, int b1, Ra
 // line the LDS cycles of the taps and of the window's stores and a share of
 // the barrier, as k_project's comment has them.  At 512^2 over 180 classes two
 // blocks of 16 classes: windows of 247 positions on average; whole lines
-// (eight blocks of four classes) took 16% longer there and 2.1x at 1024^2.
+// (eight blocks of four classes) took 12.8 ms against 9.85 there (128 slices of
+// 16 channels) and 8.45 against 5.76 at 1024^2 x 8.
 static std::vector<RayGroup> ray_groups(const rt_geom &g, const std::vector<RayDir> (&lists)[3], int blocks, int wmax)
 {
     const int nbb = (g.Ns + 63) / 64, N = g.N, Ns = g.Ns;

@@ -10,11 +10,12 @@
 //
 // Kernels
 //   k_project      ray-driven projection of up to 16 channel columns for the
-//                  rays of several angle classes of one walk direction; each
-//                  line (row or column) of the slice is staged once in LDS and
-//                  shared by all rays of the workgroup.
-//   k_contract     sum over k with the s-flip; optionally fused with the
-//                  h1 prox of Fig. 2 and an FP64 partial of |R f~ - g|^2.
+//                  rays of a tile of bins and neighbouring angle classes of one
+//                  walk direction; the window of each line (row or column) of
+//                  the slice that they reach is staged once in LDS.
+//   k_contract     sum over the line parts and over k with the s-flip;
+//                  optionally fused with the h1 prox of Fig. 2 and an FP64
+//                  partial of |R f~ - g|^2.
 //   k_fold         the fold-sum g -> g~.
 // The back-projection of g~ is in backproject.hip.
 // Ray positions start in FP64 and are stepped in 32.32 fixed point; weights and
@@ -79,7 +80,15 @@ __device__ inline float dot4(float4 w, v4 x)
 // lines fit a stage.  Stages are double buffered, with the loads a stage
 // further ahead in registers; one barrier per stage.  With NLP > 1 a
 // workgroup walks one of NLP parts of the lines and stores partial sums
-// (EPI_P) that k_contract adds in part order.
+// that k_contract adds in part order.
+//
+// What bounds it: the tap reads of LDS, 8 bytes per channel sample, 5.1 cycles
+// each where 4.3 would be free of conflicts, with the FMAs close behind; at
+// 512^2 x 128, K = 16, 180 classes 9.85 ms, of which 8.0 remain without the
+// staging and its barriers.  With whole lines staged for all bins of four
+// classes, rows padded to 80 bytes and lanes ordered modulo 16 it was 13.1 ms
+// there, and 8.4 ms against 5.4 at 1024^2 x 8 over 300 classes, where whole
+// lines allowed 8 channels at a time.
 //
 // LDS.  A ds_read_b128 is served in four groups of 16 lanes ({0-3, 12-15,
 // 20-27}, {4-11, 16-19, 28-31}, and the same + 32), each over 16 units of 16
@@ -416,7 +425,9 @@ __global__ __launch_bounds__(NTH) void k_project(
 // one class and EPT * NT of its (slice, bin) pairs; a thread adds its pair's
 // NLP partial sums once, keeps the KQ channel quads in registers and takes
 // every half-turn from them (the Phi rows are uniform over the workgroup).  The
-// order of the FP64 partials is fixed by the grid.
+// order of the FP64 partials is fixed by the grid.  Bound by HBM: P, g and h1
+// once each; 1024^2 x 8, 300 classes, 12 half-turns with the prox: 437 us with
+// a thread per (half-turn, slice, bin) reading P each time, 113 as it is.
 template <int KQ>
 __global__ __launch_bounds__(NT) void k_contract(
     const float *__restrict__ P, const float *__restrict__ phi, float *__restrict__ out,
@@ -471,7 +482,8 @@ __global__ __launch_bounds__(NT) void k_contract(
 // rows it stages in LDS, and a run of its (slice, bin) pairs; a thread owns one
 // channel quad of a pair, so that consecutive threads write consecutive 16
 // bytes (a thread per pair wrote at 64-byte strides), and has the g values of
-// FB half-turns in flight at a time.
+// FB half-turns in flight at a time: 425 -> 281 us at 512^2 x 128, 10 half-turns,
+// K = 16 (1.23 GB, 4.4 TB/s).
 constexpr int FB = 10;
 __global__ __launch_bounds__(NT) void k_fold(const float *__restrict__ g,
                                              const float *__restrict__ phi,
