@@ -82,6 +82,7 @@ struct RayCfg {
 // f has KP = K rounded up to 16 channels per voxel.
 struct SfCfg {
     int A = 1, ngroups = 0, BT = 1, nbt = 1, PCH = 32, NPP = 4, KP = 16;
+    int ST = 1024;        // threads per workgroup, a wave per 32 positions of a chunk
     int UB = 1;           // bins per thread and class slot (BT = 512 UB covers Ns <= 2048)
     // line parts: with NLP > 1 a workgroup walks N / NLP lines of its slice
     // and stores partial ray sums, which k_sf_finish adds in a fixed order

@@ -419,13 +419,20 @@ static int configure(Plan &p, TableUpload &up)
         C.ngroups = (int)gwalk_sf.size();
         C.BT = std::min(g.Ns, 512 * C.UB);
         C.nbt = (g.Ns + C.BT - 1) / C.BT;
-        C.PCH = std::min(512, (g.N + 31) / 32 * 32);
+        // Workgroups of 512 threads and chunks of 256 positions, two per CU,
+        // where 1024 threads lack rays: lines and detectors of at most 256, or
+        // fewer than four slots of at most 512 bins.  Measured, 1024 against
+        // 512 threads: 128^2 x 60, 10 half-turns 1.42 and 0.56 ms; 256^2 x 64, 2
+        // of them 1.20 and 0.57; 512^2 x 128, 10 of them 17.8 and 15.9; four
+        // slots, 384^2 x 20, 8 half-turns 1.03 and 1.18; 512^2 x 16 1.50 and 1.56.
+        C.ST = C.UB == 1 && (C.NPP > 8 || std::max(g.N, g.Ns) <= 256) ? 512 : 1024;
+        C.PCH = std::min(C.ST / 2, (g.N + 31) / 32 * 32);
         C.KP = (g.K + 15) / 16 * 16;
         // an odd number of 16-byte groups per row: 16 consecutive positions
         // of a b128 access fall in distinct bank groups
         const int row = 4 * ((sf_slots(C.NPP, C.UB, kb) * C.NPP / 4) | 1);
         C.lds = (size_t)2 * (C.PCH + 3) * row * sizeof(float);
-        // Few workgroups (one per CU fits): the lines in parts, as many as make
+        // Few workgroups (one or two per CU fit): the lines in parts, as many as make
         // the rounds of workgroups times a part's lines least, a workgroup's
         // setup and its share of k_sf_finish counted as 24 lines; the partial
         // sums go where the plain form keeps its own.  From the slices the
@@ -438,7 +445,8 @@ static int configure(Plan &p, TableUpload &up)
         if (C.NLP == 1) {
             const long wg = (long)p.nz_ref * C.ngroups * C.nbt;
             const long room = (long)line_split(g, p.nz_ref).NLP * ((g.K + 3) / 4 * 4) / g.Npi;
-            auto cost = [&](long n) { return (wg * n + 255) / 256 * ((g.N + n - 1) / n + 24); };
+            const long fit = C.ST == 512 ? 512 : 256;
+            auto cost = [&](long n) { return (wg * n + fit - 1) / fit * ((g.N + n - 1) / n + 24); };
             for (long n = 2; n <= std::min<long>({room, 32, g.N}); ++n)
                 if (10 * cost(n) < 9 * cost(C.NLP)) C.NLP = (int)n;
         }

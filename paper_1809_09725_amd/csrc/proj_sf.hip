@@ -27,7 +27,6 @@ typedef float v4f __attribute__((ext_vector_type(4)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 
-constexpr int ST = 1024;       // threads of a synthesise-first workgroup (16 wave64)
 
 // FP32 -> BF16 with round-to-nearest-even (finite inputs).
 __device__ inline unsigned short bf16_rne(float x)
@@ -67,7 +66,7 @@ __device__ inline int sf_bin(int tid, int a, const unsigned char *__restrict__ l
 // E.out + lp * E.pstride for k_sf_finish).  Consecutive workgroups take the
 // class groups of one part, so the part's BF16 lines are read while they are
 // still cached.  A thread owns the rays (slot, bin) of its half of the A slots
-// (of the one slot, where there is one) at UT bins each.  NPP: frame columns
+// (of all of them with one slot or 512 threads) at UT bins each.  NPP: frame columns
 // per class (Npi rounded up to 4, the padding columns are zero); KB: MFMA
 // k-steps of 16 channels.
 //
@@ -84,12 +83,13 @@ __device__ inline int sf_bin(int tid, int a, const unsigned char *__restrict__ l
 // all; the operand loads (128-byte lines, of which a column walk uses half)
 // are hidden.  Two frame buffers let one barrier per step do, with the
 // products of the next step running under the taps of this one; 16 waves of
-// half the rays each keep more of the LDS reads in flight than 8.  Measured,
+// half the rays each (ST = 1024; ST = 512 where these would lack rays: two
+// workgroups per CU) keep more of the LDS reads in flight than 8.  Measured,
 // 1024^2 x 8, 256 classes, 8 half-turns, K = 32: 7.25 ms with one buffer and
 // two barriers per chunk, 5.58 with two buffers and 8 waves, 4.66 as it is;
 // 512^2 x 16, 180 classes, K = 16: 2.22 -> 1.50 ms; 2048^2 x 2, K = 32:
 // 12.7 -> 7.4 ms.
-template <int NPP, int KB, int AS, int UB>
+template <int NPP, int KB, int AS, int UB, int ST>
 __global__ __launch_bounds__(ST) void k_project_sf(
     const __bf16 *__restrict__ f16, const float *__restrict__ phi, const int *__restrict__ gcls,
     const int *__restrict__ gwalk, const unsigned char *__restrict__ lperm, const double *__restrict__ ccos,
@@ -98,9 +98,9 @@ __global__ __launch_bounds__(ST) void k_project_sf(
 {
     constexpr int KP = 16 * KB;
     constexpr int CS = 4 * ((AS * NPP / 4) | 1);   // floats per row
-    // waves: with several slots, the two halves of the workgroup take half of
-    // the slots each; NB threads side by side take UT bins each per slot
-    constexpr int SH = AS > 1 ? 2 : 1, AT = AS / SH, NB = ST / SH, UT = (UB * 512 + NB - 1) / NB;
+    // waves: with 1024 threads and several slots, the two halves of the
+    // workgroup take half of the slots each; NB threads side by side take UT bins each per slot
+    constexpr int SH = AS > 1 && ST == 1024 ? 2 : 1, AT = AS / SH, NB = ST / SH, UT = (UB * 512 + NB - 1) / NB;
     constexpr int R = AT * UT;      // rays per thread: slot j0 + rho / UT, bin sf_bin(tb) + NB * (rho % UT)
     extern __shared__ float fr[];   // two buffers [PCH + 3][CS]; rows 0, PCH + 1 and PCH + 2 stay zero
     __shared__ double sh[ST / 64];
@@ -451,12 +451,12 @@ __global__ __launch_bounds__(NT) void k_fold_mfma(const float *__restrict__ g,
     }
 }
 
-template <int NPP, int KB, int AS, int UB>
-static int launch_sf_t(const Plan &p, const SfEpi &E, hipStream_t s, unsigned nb)
+template <int NPP, int KB, int AS, int UB, int ST>
+static int launch_sf_s(const Plan &p, const SfEpi &E, hipStream_t s, unsigned nb)
 {
     const rt_geom &G = p.g;
     const SfCfg &C = p.sf;
-    auto kern = k_project_sf<NPP, KB, AS, UB>;
+    auto kern = k_project_sf<NPP, KB, AS, UB, ST>;
     if (C.lds > 64 * 1024)
         RT_HIP(hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize,
                                    (int)C.lds));
@@ -466,6 +466,15 @@ static int launch_sf_t(const Plan &p, const SfEpi &E, hipStream_t s, unsigned nb
                        C.ngroups, C.BT, C.nbt, C.PCH, C.NLP, nb, E);
     kt.stop();
     return RT_OK;
+}
+
+template <int NPP, int KB, int AS, int UB>
+static int launch_sf_t(const Plan &p, const SfEpi &E, hipStream_t s, unsigned nb)
+{
+    if constexpr (UB == 1) {
+        if (p.sf.ST == 512) return launch_sf_s<NPP, KB, AS, UB, 512>(p, E, s, nb);
+    }
+    return launch_sf_s<NPP, KB, AS, UB, 1024>(p, E, s, nb);
 }
 
 // AS slots for one bin per thread; UB bins per thread take AS / UB slots

@@ -106,7 +106,8 @@ def test_slices_do_not_depend_on_the_volume(K):
 SF_CASES = [   # (geometry): slots per group 4, 2, 1 and 1, 2, 4 bins of 512 per slot; 16..64 channels
     geom(37, 2, 41, 2, 9, 4), geom(64, 1, 64, 8, 7, 16), geom(33, 1, 60, 9, 6, 20), geom(31, 2, 30, 16, 5, 33),
     geom(65, 1, 70, 17, 4, 40), geom(40, 1, 44, 27, 3, 64), geom(96, 1, 90, 32, 4, 64), geom(1, 2, 1, 3, 4, 7),
-    # lines of two and three chunks, with a few positions in the last one; one chunk exactly
+    geom(400, 1, 400, 8, 5, 16), geom(257, 2, 256, 4, 4, 24), geom(256, 1, 256, 8, 4, 16),
+    # lines of two and more chunks, with a few positions in the last one; one chunk exactly
     geom(512, 1, 520, 4, 5, 8), geom(513, 1, 700, 8, 6, 32), geom(545, 1, 900, 12, 4, 24), geom(1030, 1, 300, 16, 3, 17),
     geom(200, 1, 1300, 8, 5, 16), geom(150, 1, 2048, 12, 4, 30), geom(130, 1, 1100, 20, 3, 20), geom(90, 1, 2100, 4, 4, 64),
 ]
