@@ -535,8 +535,8 @@ int pick_form(const rt_geom *geom, rt_form *form, rt_prec *prec)
         // per ray and line, project-first taps K channels; synthesise-first
         // taps the Npi frames (rounded up to 4) and forms them on the matrix
         // cores, which pays from about K = 2 Npi (measured per iteration at
-        // 8 half-turns: SF/PF 0.53-0.95 at K = 32, 0.97-1.08 at K = 16,
-        // 1.2-1.7 at K = 8; 1.24 at K = 16 over 12 half-turns)
+        // 8 half-turns, 256^2 to 1024^2 x 8: SF/PF 0.67-0.82 at K = 32, 0.84-0.99
+        // at K = 16, 1.27-1.37 at K = 8; 1.28 at K = 16 over 12 half-turns)
         const bool sf = *prec == RT_PREC_BF16MFMA && geom->K >= 2 * geom->Npi && geom->Npi <= 32;
         *form = sf ? RT_FORM_SF : RT_FORM_PF;
         *prec = sf ? RT_PREC_BF16MFMA : RT_PREC_FP32;
