@@ -426,6 +426,20 @@ static int configure(Plan &p, TableUpload &up)
         // of them 1.20 and 0.57; 512^2 x 128, 10 of them 17.8 and 15.9; four
         // slots, 384^2 x 20, 8 half-turns 1.03 and 1.18; 512^2 x 16 1.50 and 1.56.
         C.ST = C.UB == 1 && (C.NPP > 8 || std::max(g.N, g.Ns) <= 256) ? 512 : 1024;
+        // Above 32 channels the operands of the products take the registers that
+        // 16 waves leave.  33..48 channels: 512 threads (1024 against 512: 266^2 x
+        // 45, 4 half-turns, K = 35 1.55 and 1.06 ms; 800^2 x 4, 8 of them, K = 40
+        // 4.16 and 3.08; 720 bins of 700^2 x 4, 32 of them, K = 44 4.55 and 4.07),
+        // except for many half-turns over several tiles of bins (1300^2, 1400 bins,
+        // 32 of them 6.02 and 6.47).  More channels over more than 512 bins: 512
+        // threads where 1024 spill (32 frame columns; 965^2 x 3, 13 half-turns, K =
+        // 52 6.55 and 4.62; 1024^2 x 4, 32 of them, K = 64 11.0 and 8.5) or pad the
+        // lines with more positions (1213^2 x 4, 5 of them, K = 58 7.25 and 6.14);
+        // elsewhere 1024 (1024^2 x 8, 12 of them, K = 64 16.2 and 16.4).
+        const auto padded = [&](int pch) { return (g.N + pch - 1) / pch * pch; };
+        if ((kb == 3 && (C.NPP <= 20 || g.Ns <= 1024)) ||
+            (kb == 4 && C.UB > 1 && (sf_slots(C.NPP, C.UB, kb) * C.NPP == 32 || padded(256) < padded(512))))
+            C.ST = 512;
         C.PCH = std::min(C.ST / 2, (g.N + 31) / 32 * 32);
         C.KP = (g.K + 15) / 16 * 16;
         // an odd number of 16-byte groups per row: 16 consecutive positions

@@ -89,8 +89,17 @@ __device__ inline int sf_bin(int tid, int a, const unsigned char *__restrict__ l
 // two barriers per chunk, 5.58 with two buffers and 8 waves, 4.66 as it is;
 // 512^2 x 16, 180 classes, K = 16: 2.22 -> 1.50 ms; 2048^2 x 2, K = 32:
 // 12.7 -> 7.4 ms.
+// Waves per SIMD asked for: with 33..48 channels and two bins or slots of up
+// to 20 half-turns a thread, 512 threads are held to 128 registers (134 or 131
+// otherwise; at most three spilt), so that two workgroups do fit a CU: 512^2 x
+// 16, 16 half-turns, K = 48: 5.40 -> 4.67 ms.  More sums, or more channels, would
+// spill tens of registers (256^2 x 16, 16 half-turns, K = 64: 1.13 -> 1.85 ms).
+constexpr int sf_waves(int npp, int kb, int as, int ub, int st)
+{
+    return st == 512 && kb == 3 && as * ub == 2 && npp <= 20 ? 4 : st / 256;
+}
 template <int NPP, int KB, int AS, int UB, int ST>
-__global__ __launch_bounds__(ST) void k_project_sf(
+__global__ __launch_bounds__(ST, sf_waves(NPP, KB, AS, UB, ST)) void k_project_sf(
     const __bf16 *__restrict__ f16, const float *__restrict__ phi, const int *__restrict__ gcls,
     const int *__restrict__ gwalk, const unsigned char *__restrict__ lperm, const double *__restrict__ ccos,
     const double *__restrict__ csin, int N, int Nz, int Ns, int K, int A, int ngroups, int BT,
@@ -471,7 +480,7 @@ static int launch_sf_s(const Plan &p, const SfEpi &E, hipStream_t s, unsigned nb
 template <int NPP, int KB, int AS, int UB>
 static int launch_sf_t(const Plan &p, const SfEpi &E, hipStream_t s, unsigned nb)
 {
-    if constexpr (UB == 1) {
+    if constexpr (UB == 1 || KB >= 3) {   // as the plan chooses ST
         if (p.sf.ST == 512) return launch_sf_s<NPP, KB, AS, UB, 512>(p, E, s, nb);
     }
     return launch_sf_s<NPP, KB, AS, UB, 1024>(p, E, s, nb);

@@ -131,3 +131,16 @@ def test_synthesise_first_edges(G):
     F = f.abs().sum(-1, keepdim=True).numpy()
     S = O.forward(G1, F)
     assert (np.abs(got - want) <= (2.0 ** -17 + 4 * G.N * 2.0 ** -24) * S + G.N ** 2 * 2.0 ** -31 * F.max()).all()
+
+
+SF_WIDE = [   # 33..64 channels over more than 512 bins: 512 threads (the first six), 1024 (the last three)
+    geom(311, 1, 561, 20, 2, 39), geom(100, 1, 1300, 12, 3, 40), geom(70, 1, 1400, 4, 3, 48), geom(520, 1, 600, 13, 3, 52),
+    geom(130, 1, 900, 32, 2, 64), geom(600, 1, 600, 5, 3, 58),
+    geom(120, 1, 1400, 28, 2, 44), geom(300, 1, 700, 5, 4, 58), geom(257, 1, 1100, 12, 2, 64),
+]
+
+
+@pytest.mark.parametrize("G", SF_WIDE, ids=lambda G: f"N{G.N}s{G.Ns}p{G.Npi}k{G.K}")
+def test_synthesise_first_many_channels(G):
+    """The thread counts above 32 channels, at the same bar."""
+    test_synthesise_first_edges(G)
