@@ -289,21 +289,26 @@ __global__ __launch_bounds__(NTH) void k_project(
         const float w0 = invc[j] - w1;
         const unsigned t0 = ((unsigned)clamp0_i32(q0 - w0l, W - 2) << SH) + lb;
         v4 x[NQ], y[NQ];
-        //ORD-BEGIN
 #pragma unroll
         for (int q = 0; q < NQ; ++q) x[q] = *(lds_v4 *)(size_t)(t0 ^ (16u * q));
 #pragma unroll
         for (int q = 0; q < NQ; ++q) y[q] = *(lds_v4 *)(size_t)((t0 ^ (16u * q)) + (1u << SH));
         __builtin_amdgcn_sched_barrier(0);   // all reads are issued before the first FMA waits
+        if constexpr (TL) {   // one rounding at the size of the sum per line (see flush)
 #pragma unroll
-        for (int q = 0; q < NQ; ++q)
+            for (int q = 0; q < NQ; ++q)
 #pragma unroll
-            for (int t = 0; t < 4; ++t) acc[j][q][t] = fmaf(w0, x[q][t], acc[j][q][t]);
+                for (int t = 0; t < 4; ++t) acc[j][q][t] += fmaf(w1, y[q][t], w0 * x[q][t]);
+        } else {
 #pragma unroll
-        for (int q = 0; q < NQ; ++q)
+            for (int q = 0; q < NQ; ++q)
 #pragma unroll
-            for (int t = 0; t < 4; ++t) acc[j][q][t] = fmaf(w1, y[q][t], acc[j][q][t]);
-        //ORD-END
+                for (int t = 0; t < 4; ++t) acc[j][q][t] = fmaf(w0, x[q][t], acc[j][q][t]);
+#pragma unroll
+            for (int q = 0; q < NQ; ++q)
+#pragma unroll
+                for (int t = 0; t < 4; ++t) acc[j][q][t] = fmaf(w1, y[q][t], acc[j][q][t]);
+        }
 #pragma unroll
         for (int q = 0; q < NQ; ++q)
 #pragma unroll
@@ -327,8 +332,14 @@ __global__ __launch_bounds__(NTH) void k_project(
     // lines are summed in registers and then added to P, so that the FP32
     // rounding of a long ray grows with sqrt(LB) + sqrt(N / LB) additions
     // instead of sqrt(N).  A second set of sums in registers would not fit
-    // 16 waves per CU; P costs 6% of the line traffic.  All reads of P are
-    // issued before the first is used.
+    // 16 waves per CU; adding to P takes the L2 traffic of 2 KB per ray block
+    // and quad column.  All reads of P are issued before the first is used.
+    // Both taps of a line are summed before they are added to the block's sum,
+    // which is then rounded once a line.  Error of signed volumes (rel-L2, a
+    // CPU emulation of the sums at N = 640, 1024, 2048), and k_project at 1024^2
+    // x 8, K = 16, 300 classes: LB = 64 and two FMAs a line 2.21, 2.23,
+    // 2.29e-7, 5.47 ms; LB = 32 and two FMAs 1.74, 1.87, 2.09e-7, 6.05 ms; LB
+    // = 64 as it is 1.67, 1.75, 1.85e-7, 5.79 ms.
     constexpr int LB = 64;
     bool first = true;
     auto flush = [&]() {

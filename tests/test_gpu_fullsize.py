@@ -209,3 +209,13 @@ def test_c5_properties():
     print(f"precision vs plain forward: rel {d.item():.3e}", flush=True)
     assert d.item() <= 3e-3
     sf.close()
+
+
+def test_c3_plain_slab_in_one_part():
+    """The plain form's two-level sums with whole lines per workgroup: 8 slices
+    of the 1024^2 workload with its 300 classes fill the chip, so that the
+    lines are not cut into parts (25 classes over 2 slices, as the 2048^2 check
+    above takes them, are walked in two parts; the ray groups follow the
+    classes' spacing).  Sampled slices against the FP64 oracle."""
+    G = rt4d.Geom(N=1024, Nz=8, Ns=1024, Ntheta=3600, Npi=12, K=16, Nt=12)
+    check_sampled(G, rt4d.RT_FORM_PF, rt4d.RT_PREC_FP32, (0, 5), (7,), 1e-5, route="folded")

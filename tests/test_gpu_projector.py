@@ -103,6 +103,35 @@ def test_slices_do_not_depend_on_the_volume(K):
     assert not torch.isfinite(b[9]).all()
 
 
+@pytest.mark.parametrize("N", [513, 640, 1024])
+def test_two_level_sums_rounding(N):
+    """Lines of more than 512 positions in one part (the workgroups fill the
+    chip), signed data, where rounding errors add as a random walk.  A sum of
+    terms of unit size over blocks of L lines, kept one rounding per addition
+    and blocks added likewise, collects the variance sum of l over each block
+    (N L / 2 in all, N L with two roundings per line) plus N^2 / (2 L) of the
+    block sums, in units of the terms' variance and of a rounding's, whose rms
+    is below 2^-25 of the value (half a unit roundoff); K channels contracted
+    add K / 2.  Blocks of 32 lines with two roundings, relative to the N of the
+    sum: 2^-25 sqrt(32 + N / 64 + K / 2)."""
+    torch.cuda.set_device(DEV)
+    G = geom(N, 32, N, 1, 300, 4)
+    f = torch.zeros(G.f_shape, device=DEV)
+    zs = (0, 13, 30)
+    host = {z: inputs.uniform((N, N, 4), 40 + z) for z in zs}
+    for z in zs:
+        f[z] = torch.from_numpy(host[z]).to(DEV)
+    got = rt4d.Plan(G).forward(f)
+    num = den = 0.0
+    for z in zs:
+        want = O.forward(O.Geom(**{**G.__dict__, "Nz": 1}), host[z][None])[:, 0]
+        num += float(np.sum((got[:, z].cpu().numpy().astype(np.float64) - want) ** 2))
+        den += float(np.sum(want ** 2))
+    bound = 2.0 ** -25 * np.sqrt(32 + N / 64 + 4 / 2)
+    print(f"N {N}: rel-L2 {np.sqrt(num / den):.3e} (bound {bound:.3e})", flush=True)
+    assert np.sqrt(num / den) <= bound
+
+
 SF_CASES = [   # (geometry): slots per group 4, 2, 1 and 1, 2, 4 bins of 512 per slot; 16..64 channels
     geom(37, 2, 41, 2, 9, 4), geom(64, 1, 64, 8, 7, 16), geom(33, 1, 60, 9, 6, 20), geom(31, 2, 30, 16, 5, 33),
     geom(65, 1, 70, 17, 4, 40), geom(40, 1, 44, 27, 3, 64), geom(96, 1, 90, 32, 4, 64), geom(1, 2, 1, 3, 4, 7),
