@@ -310,6 +310,9 @@ __global__ __launch_bounds__(NT) void k_backproject_small(const float *__restric
     const int nb = (ncl + BS_CB - 1) / BS_CB;
     if (nb > 0) issue(0);
     for (int b = 0; b < nb; ++b) {
+        // the taps of batch b - 1 have left the half of the ring that batch b + 1
+        // is copied to (the copies' order after LDS reads is nowhere else kept)
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         issue(b + 1);   // always, so that the count below is this batch's
         asm volatile("s_waitcnt vmcnt(%0)" :: "n"(BS_CB * NI) : "memory");
 #pragma unroll
