@@ -184,8 +184,22 @@ __global__ __launch_bounds__(NT) void k_frames(const float *__restrict__ f,
 // unconditional, from clamped addresses, and the differences at the last index
 // of an axis are selected to zero.  Measured with the shrink: 256^2 x 8, 8
 // frames 80 -> 33 us; 512^2 x 32, 10 frames 606 -> 587 us (5.2 TB/s).
+// h2 of a voxel is read and written once here and next read after the
+// back-projection has streamed through L2: streaming (non-temporal) accesses
+// leave L2 to the frames' neighbour reads (STREAM, for planes of a multiple of
+// 64 bytes).  Where a plane is no such multiple, neighbouring waves share lines
+// of h2, which then have to meet in L2: 919^2 x 8, 8 frames 613 us streaming,
+// 408 with ordinary accesses; 512^2 x 32, 10 frames 567 and 584 us.
 constexpr int UF = 4;
-template <int MODE>
+template <bool STREAM>
+__device__ inline float ld(const float *p) { return STREAM ? __builtin_nontemporal_load(p) : *p; }
+template <bool STREAM>
+__device__ inline void st(float v, float *p)
+{
+    if constexpr (STREAM) __builtin_nontemporal_store(v, p);
+    else *p = v;
+}
+template <int MODE, bool STREAM>
 __global__ __launch_bounds__(NT) void k_grad(const float *__restrict__ F, float lambda2,
                                              float sigma, float lambda1, float *__restrict__ p,
                                              double *__restrict__ part, int N, int Nz, int Nt,
@@ -231,14 +245,9 @@ __global__ __launch_bounds__(NT) void k_grad(const float *__restrict__ F, float 
                     const int m1 = min(m + 1, Nt - 1);
                     f1[u] = own ? cf[m1 * NT] : Fz[(size_t)m1 * plane];
                     if (MODE == 1) {
-                        // h2 of this voxel is read and written once here and next read
-                        // after the back-projection has streamed through L2: streaming
-                        // (non-temporal) accesses leave L2 to the frames' neighbour reads
                         const float *pm = pz + (size_t)m * 4 * plane;
-                        h[u] = make_float4(__builtin_nontemporal_load(pm),
-                                           __builtin_nontemporal_load(pm + plane),
-                                           __builtin_nontemporal_load(pm + 2 * plane),
-                                           __builtin_nontemporal_load(pm + 3 * plane));
+                        h[u] = make_float4(ld<STREAM>(pm), ld<STREAM>(pm + plane), ld<STREAM>(pm + 2 * plane),
+                                           ld<STREAM>(pm + 3 * plane));
                     }
                 }
 #pragma unroll
@@ -260,10 +269,10 @@ __global__ __launch_bounds__(NT) void k_grad(const float *__restrict__ F, float 
                     } else if (MODE == 1) {
                         float *pm = pz + (size_t)m * 4 * plane;
                         const float4 a = shrink_step(h[u], gx, gy, gz, gt, sigma, lambda1);
-                        __builtin_nontemporal_store(a.x, pm);
-                        __builtin_nontemporal_store(a.y, pm + plane);
-                        __builtin_nontemporal_store(a.z, pm + 2 * plane);
-                        __builtin_nontemporal_store(a.w, pm + 3 * plane);
+                        st<STREAM>(a.x, pm);
+                        st<STREAM>(a.y, pm + plane);
+                        st<STREAM>(a.z, pm + 2 * plane);
+                        st<STREAM>(a.w, pm + 3 * plane);
                     }
                     F0 = f1[u];
                 }
@@ -283,8 +292,11 @@ __global__ __launch_bounds__(NT) void k_grad(const float *__restrict__ F, float 
 // prox, f+ = (f - tau adj + tau S^T div h2) * cinv, cinv = 1 / (1 + mu tau),
 // and the extrapolation takes the step's theta: f~ = f+ + theta (f+ - f).
 // Slices [zbeg, zend) of the Nz present are computed; the others only serve
-// as z-neighbours.
-template <int KT, int MODE>
+// as z-neighbours.  UB frames are loaded together: 4 where the voxels are few
+// (latency), 2 in the primal step where they fill the chip (registers: 83
+// against 69 with 16 channels, 5 and 7 waves per SIMD; 1024^2 x 8, 3 frames, K =
+// 16 541 and 520 us; 300^2 x 5, 10 frames, K = 32 87 and 90 us).
+template <int KT, int MODE, int UB>
 __global__ __launch_bounds__(NT) void k_div(const float *__restrict__ pin,
                                             const float *__restrict__ S, float lambda2,
                                             float *__restrict__ out, const float *__restrict__ adj,
@@ -314,37 +326,43 @@ __global__ __launch_bounds__(NT) void k_div(const float *__restrict__ pin,
         const size_t v = v0 + threadIdx.x;
         __syncthreads();   // S staged; the previous chunk is done with rows
         if ((int)threadIdx.x < nv) {
-            const int q = (int)(v % N);
-            const int r = (int)((v / N) % N);
-            const size_t z = v / plane, pv = v % plane;
-            const float *pz = pin + z * Nt * 4 * plane + pv;
+            const unsigned pv = (unsigned)pv0 + threadIdx.x;
+            const int q = (int)(pv % (unsigned)N), r = (int)(pv / (unsigned)N);
+            const float *pz = pin + (size_t)zz * Nt * 4 * plane + pv;
             float acc[KT];
 #pragma unroll
             for (int k = 0; k < KT; ++k) acc[k] = 0.f;
             float tprev = 0.f;
-            // the loads of UF frames are issued together, from clamped
-            // addresses; absent neighbours are selected to zero
-            const size_t ox = q > 0 ? 1 : 0, oy = r > 0 ? N : 0, oz = z > 0 ? (size_t)Nt * 4 * plane : 0;
-            for (int m0 = 0; m0 < Nt; m0 += UF) {
-                float c[UF][4], n[UF][3];
+            // the loads of UB frames are issued together; absent neighbours are
+            // selected to zero and, not to add traffic, are loaded from the x
+            // component's address, which is read anyway (the z plane of a last
+            // slice, the t plane of a last frame: one 2272^2 slice, 18 frames, K = 4
+            // 318 us with these planes read, 242 as it is)
+            const size_t ox = q > 0 ? 1 : 0, oy = r > 0 ? N : 0;
+            const size_t o2 = zz < Nz - 1 ? 2 * plane : 0;
+            const long oz = zz > 0 ? 2 * (long)plane - 4 * (long)plane * Nt : 0;
+            for (int m0 = 0; m0 < Nt; m0 += UB) {
+                float c[UB][4], n[UB][3];
 #pragma unroll
-                for (int u = 0; u < UF; ++u) {
+                for (int u = 0; u < UB; ++u) {
                     if (m0 + u >= Nt) break;
                     const float *pm = pz + (size_t)(m0 + u) * 4 * plane;
-#pragma unroll
-                    for (int t = 0; t < 4; ++t) c[u][t] = pm[t * plane];
+                    c[u][0] = pm[0];
+                    c[u][1] = pm[plane];
+                    c[u][2] = pm[o2];
+                    c[u][3] = pm[m0 + u < Nt - 1 ? 3 * plane : 0];
                     n[u][0] = *(pm - ox);
                     n[u][1] = *(pm + plane - oy);
-                    n[u][2] = *(pm + 2 * plane - oz);
+                    n[u][2] = pm[oz];
                 }
 #pragma unroll
-                for (int u = 0; u < UF; ++u) {
+                for (int u = 0; u < UB; ++u) {
                     const int m = m0 + u;
                     if (m >= Nt) break;
                     const float tcur = m < Nt - 1 ? c[u][3] : 0.f;
                     const float d = div_step(q < N - 1 ? c[u][0] : 0.f, q > 0 ? n[u][0] : 0.f,
                                              r < N - 1 ? c[u][1] : 0.f, r > 0 ? n[u][1] : 0.f, Nz > 1,
-                                             (int)z < Nz - 1 ? c[u][2] : 0.f, z > 0 ? n[u][2] : 0.f, tcur,
+                                             zz < Nz - 1 ? c[u][2] : 0.f, zz > 0 ? n[u][2] : 0.f, tcur,
                                              tprev, lambda2);
                     tprev = tcur;
                     const float *Sm = sS + m * KT;
@@ -492,12 +510,14 @@ static int launch_grad_mode(const Plan &p, int mode, const char *name, const flo
     const int carry = lds > 0;
     const unsigned nb = grad_blocks(g);
     KTimer kt(name, s);
-    if (mode == 0)
-        hipLaunchKernelGGL(k_grad<0>, dim3(nb), dim3(NT), lds, s, F, lambda2, sigma, lambda1, pout, part, g.N, g.Nz, g.Nt, zbeg, zend, ZC, MC, carry);
-    else if (mode == 1)
-        hipLaunchKernelGGL(k_grad<1>, dim3(nb), dim3(NT), lds, s, F, lambda2, sigma, lambda1, pout, part, g.N, g.Nz, g.Nt, zbeg, zend, ZC, MC, carry);
-    else
-        hipLaunchKernelGGL(k_grad<2>, dim3(nb), dim3(NT), lds, s, F, lambda2, sigma, lambda1, pout, part, g.N, g.Nz, g.Nt, zbeg, zend, ZC, MC, carry);
+    const bool stream = (size_t)g.N * g.N % 16 == 0;
+#define RT_GRAD(...) hipLaunchKernelGGL((k_grad<__VA_ARGS__>), dim3(nb), dim3(NT), lds, s, F, lambda2, sigma, lambda1, \
+                                        pout, part, g.N, g.Nz, g.Nt, zbeg, zend, ZC, MC, carry)
+    if (mode == 0) RT_GRAD(0, false);
+    else if (mode == 2) RT_GRAD(2, false);
+    else if (stream) RT_GRAD(1, true);
+    else RT_GRAD(1, false);
+#undef RT_GRAD
     kt.stop();
     RT_HIP(hipGetLastError());
     return RT_OK;
@@ -537,9 +557,15 @@ static void launch_div_t(const Plan &p, const float *pin, float lambda2, float *
     const int KP = p.sf.KP;
     const int accel = cinv != 1.f || theta != 1.f;
     const int ZC = z_chunk((size_t)g.N * g.N, zend - zbeg);
-#define RT_DIV(KT) hipLaunchKernelGGL((k_div<KT, MODE>), dim3(nb), dim3(NT), lds, s, pin, p.d_S, \
-                                      lambda2, out, adj, ft, Ff, tau, cinv, theta, accel, part,   \
-                                      f16, KP, g.N, g.Nz, g.K, g.Nt, zbeg, zend, ZC)
+    const bool fill = MODE == 1 && ZC == 4;   // the voxels fill the chip
+#define RT_DIVU(KT, UB) hipLaunchKernelGGL((k_div<KT, MODE, UB>), dim3(nb), dim3(NT), lds, s, pin, p.d_S, \
+                                           lambda2, out, adj, ft, Ff, tau, cinv, theta, accel, part,   \
+                                           f16, KP, g.N, g.Nz, g.K, g.Nt, zbeg, zend, ZC)
+#define RT_DIV(KT)                       \
+    do {                                 \
+        if (fill) RT_DIVU(KT, MODE == 1 ? 2 : 4); \
+        else RT_DIVU(KT, 4);             \
+    } while (0)
     switch (p.tv.KT) {
     case 8: RT_DIV(8); break;
     case 16: RT_DIV(16); break;
@@ -547,6 +573,7 @@ static void launch_div_t(const Plan &p, const float *pin, float lambda2, float *
     default: RT_DIV(64); break;
     }
 #undef RT_DIV
+#undef RT_DIVU
 }
 
 int launch_tv_div(const Plan &p, const float *pin, float lambda2, float *out, hipStream_t s)
