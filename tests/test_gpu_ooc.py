@@ -138,3 +138,27 @@ def test_ooc_against_oracle(variant):
           f"{ro['objective']:.9e} vs {rr['objective']:.9e}", flush=True)
     assert e <= 1e-3 and m <= 1e-3
     assert abs(ro["objective"] - rr["objective"]) <= 1e-4 * abs(rr["objective"])
+
+
+@pytest.mark.parametrize("N,Ns,K,n0,Nz,slab", [
+    (200, 210, 8, 12, 56, 2),   # 32 x 32 tiles and four slices per TV work item; slabs 32 x 8 and one slice
+    (96, 100, 8, 64, 24, 1),    # 1728 channel quads: 32 x 8 tiles; 72 in a slab, where 8 x 8 tiles begin below 1024
+    (300, 310, 16, 10, 6, 2),   # 11 line parts; a volume of two slices takes 16
+    (560, 560, 4, 10, 6, 2),    # 15 line parts of two-level sums; four slices per TV work item, one in the slabs
+])
+def test_ooc_across_launch_thresholds(N, Ns, K, n0, Nz, slab):
+    """The kernels' work split follows the size of what is in core: line parts
+    of the projector, tiles of the back-projection, slices and frames per work
+    item of the TV.  Volumes and slabs on either side of each threshold: the
+    out-of-core iterate equals the in-core one bit for bit."""
+    torch.cuda.set_device(DEV)
+    G = rt4d.Geom(N=N, Nz=Nz, Ns=Ns, Ntheta=3 * n0, Npi=3, K=K, Nt=3)
+    print(f"case {G} slab {slab}", flush=True)
+    g, f0 = case(G, 151)
+    kw = dict(lambda1=2.0 ** -9 * float(N) ** 2, lambda2=3.0, n_iter=3, n_pow=5, seed=4)
+    ref, rr = in_core(G, g, f0, **kw)
+    f = f0.clone()
+    ro = rt4d.solve_ooc(G, g, f, slab, **kw)
+    assert torch.equal(f, ref)
+    assert ro["tau"] == rr["tau"] and ro["sigma"] == rr["sigma"]
+    assert abs(ro["objective"] - rr["objective"]) <= 1e-12 * abs(rr["objective"])
