@@ -20,6 +20,8 @@
 // The back-projection of g~ is in backproject.hip.
 // Ray positions start in FP64 and are stepped in 32.32 fixed point; weights and
 // accumulation in FP32.
+#include <type_traits>
+
 #include "common.h"
 #include "internal.h"
 
@@ -104,12 +106,16 @@ __device__ inline float dot4(float4 w, v4 x)
 // Staging (STG).  STG_LINE: the quads are of one slice; each line is a buffer
 // whose bounds give the zeros outside it, and the loads go to LDS directly.
 // STG_LIST: the quads are of several slices (K4 is no multiple of NQ); one
-// buffer over them, lanes outside get an offset past its end.  STG_REGS: fewer
-// than 4 channels, or offsets of more than 32 bits; masked loads through
+// buffer over them, lanes outside get an offset past its end.  STG_FEW: fewer
+// than 4 channels, a quad per slice; the same buffer, read into registers with
+// one load of K dwords per quad (three masked 4-byte loads took 1.39 ms against
+// 0.57 at 551^2 x 36, K = 3, 25 classes, and 0.46 against 0.32 at 256^2 x 64, 128
+// classes).  STG_REGS: offsets of more than 32 bits; masked loads through
 // registers.  Where K is no multiple of 4, a slice's last quad is staged as
 // its last four channels, all of them real; the sums are shifted into place
 // at the end.
-enum { STG_LINE = 0, STG_LIST = 1, STG_REGS = 2 };
+enum { STG_LINE = 0, STG_LIST = 1, STG_REGS = 2, STG_FEW = 3 };
+constexpr bool stg_regs(int stg) { return stg >= STG_REGS; }   // through registers
 template <int NQ, int PPT, int PF, bool TL, int NTH, int STG>
 __global__ __launch_bounds__(NTH) void k_project(
     const float *__restrict__ f, float *P, const RayGroup *__restrict__ groups,
@@ -212,11 +218,11 @@ __global__ __launch_bounds__(NTH) void k_project(
     const bool qok = gq < A.Nz * K4;             // a quad of the list
     const int kr = K & 3;                        // channels of a slice's last quad (0: 4)
     const unsigned coff = min(4 * kq, max(K - 4, 0)) * 4u;   // channel offset of the load
-    const unsigned goff = coff + p0 * pstep + (STG == STG_LIST ? zq * (unsigned)N * N * K * 4u : 0u);
+    const unsigned goff = coff + p0 * pstep + (STG == STG_LIST || STG == STG_FEW ? zq * (unsigned)N * N * K * 4u : 0u);
     const char *fz = (const char *)(f + (size_t)z0 * N * N * K);
     typedef float v4u __attribute__((ext_vector_type(4), aligned(4)));
     typedef int i4 __attribute__((ext_vector_type(4)));
-    v4 r[STG == STG_REGS ? PF : 1];
+    v4 r[stg_regs(STG) ? PF : 1];
     const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) char *)smem;
     auto first_line = [&](int st) { return min(lbeg + st * NLS, lend - NLS); };
     auto wfirst = [&](int l) { return (int)((G.wl0 + l * G.sw) >> 32); };   // window's first position
@@ -225,7 +231,40 @@ __global__ __launch_bounds__(NTH) void k_project(
     // issued from inline assembly, so that the compiler, which cannot tell the
     // two buffers apart, adds no wait for them before the tap reads; the wait
     // is the vmcnt(0) before the barrier that ends the stage.
-    auto load = [&](int st) {
+    // STG_FEW: KC channels of a position in one load, zeros from past the buffer's end
+    auto load_few = [&](int st, auto kc) __attribute__((always_inline)) {
+        constexpr int KC = decltype(kc)::value;
+        const int l0 = first_line(st);
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+            (void *)fz, 0, (unsigned)min(A.Nz - z0, NQ) * (unsigned)N * N * KC * 4u, 0x00020000);
+#pragma unroll
+        for (int j = 0; j < PF; ++j) {
+            const int ln = j >> sh_l, row = (j & ((1 << sh_l) - 1)) * RPJ;
+            if (ln >= NLS) break;
+            const int l = l0 + ln, pos = wfirst(l) + row + p0;
+            const bool in = qok && (unsigned)pos < (unsigned)N;
+            const unsigned off = in ? goff + (unsigned)(pos - p0) * pstep + l * lstep : 0xffffff00u;
+            v4 x = {0.f, 0.f, 0.f, 0.f};
+            if constexpr (KC == 3) {
+                const auto u = __builtin_amdgcn_raw_buffer_load_b96(rs, off, 0, 0);
+                x = v4{__uint_as_float(u[0]), __uint_as_float(u[1]), __uint_as_float(u[2]), 0.f};
+            } else if constexpr (KC == 2) {
+                const auto u = __builtin_amdgcn_raw_buffer_load_b64(rs, off, 0, 0);
+                x[0] = __uint_as_float(u[0]);
+                x[1] = __uint_as_float(u[1]);
+            } else {
+                x[0] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, off, 0, 0));
+            }
+            r[j] = x;
+        }
+    };
+    auto load = [&](int st) __attribute__((always_inline)) {
+        if constexpr (STG == STG_FEW) {
+            if (K == 3) load_few(st, std::integral_constant<int, 3>{});
+            else if (K == 2) load_few(st, std::integral_constant<int, 2>{});
+            else load_few(st, std::integral_constant<int, 1>{});
+            return;
+        }
         const int l0 = first_line(st);
         const unsigned buf = lds0 + (st & 1) * bufb + wave * 1024;
 #pragma unroll
@@ -238,15 +277,7 @@ __global__ __launch_bounds__(NTH) void k_project(
                 const char *src = fz + (qok ? (size_t)zq * N * N * K * 4 : 0) + (size_t)l * lstep +
                                   (size_t)(unsigned)max(pos, 0) * pstep + coff;
                 r[j] = v4{0.f, 0.f, 0.f, 0.f};
-                if (qok && (unsigned)pos < (unsigned)N) {
-                    if (K > 3) {
-                        r[j] = *(const v4u *)src;
-                    } else {
-#pragma unroll
-                        for (int t = 0; t < 3; ++t)
-                            if (t < K) r[j][t] = ((const float *)src)[t];
-                    }
-                }
+                if (qok && (unsigned)pos < (unsigned)N) r[j] = *(const v4u *)src;
             } else {
                 // STG_LINE: the bytes of the line up to its last position's
                 // end; a position before the line (the offset wraps) or past
@@ -267,13 +298,13 @@ __global__ __launch_bounds__(NTH) void k_project(
             }
         }
     };
-    auto store = [&](int st) {   // STG_REGS
+    auto store = [&](int st) {   // through registers
         char *dst = smem + (st & 1) * bufb + (tid << 4);
 #pragma unroll
         for (int j = 0; j < PF; ++j) {
             const int ln = j >> sh_l, row = (j & ((1 << sh_l) - 1)) * RPJ;
             if (ln >= NLS) break;
-            if (p0 + row < W) *(v4 *)(dst + ln * lineb + (row << SH)) = r[STG == STG_REGS ? j : 0];
+            if (p0 + row < W) *(v4 *)(dst + ln * lineb + (row << SH)) = r[stg_regs(STG) ? j : 0];
         }
     };
 
@@ -368,7 +399,7 @@ __global__ __launch_bounds__(NTH) void k_project(
     // stage st + 1 and are refilled with stage st + 2.)
     const int nst = (lend - lbeg + NLS - 1) / NLS;
     load(0);
-    if constexpr (STG == STG_REGS) {
+    if constexpr (stg_regs(STG)) {
         store(0);
         load(min(1, nst - 1));
     } else {
@@ -376,7 +407,7 @@ __global__ __launch_bounds__(NTH) void k_project(
     }
     __syncthreads();
     for (int st = 0; st < nst; ++st) {
-        if constexpr (STG == STG_REGS) {
+        if constexpr (stg_regs(STG)) {
             store(st + 1);
             load(min(st + 2, nst - 1));
         } else {
@@ -393,7 +424,7 @@ __global__ __launch_bounds__(NTH) void k_project(
             for (int j = 0; j < PPT; ++j)
                 if ((unsigned)(l - jb[j]) < (unsigned)(je[j] - jb[j])) taps(j, lb, w0l);
         }
-        if constexpr (STG != STG_REGS) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        if constexpr (!stg_regs(STG)) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
     }
 
@@ -565,13 +596,15 @@ static int launch_project_q(const Plan &p, const RayCfg &R, const float *f, cons
 {
     // the buffer loads need every position of a window to have its own 32-bit
     // offset: those before the line and past it included (STG_LINE), all
-    // slices of a workgroup's quads, at most 1 + (NQ - 1) / K4 more (STG_LIST)
+    // slices of a workgroup's quads, at most 1 + (NQ - 1) / K4 more (STG_LIST;
+    // STG_FEW, whose four slices of at most 3 channels take below 2^30 bytes)
     const rt_geom &g = p.g;
     const size_t lim = (size_t)1 << 32, pos = (size_t)g.N * g.K * 4;
     if (g.K >= 4 && R.K4 % NQ == 0 && (g.N + 2 * RAY_WMAX) * pos < lim)
         return launch_project_s<NQ, STG_LINE>(p, R, f, E, s);
     if (g.K >= 4 && (size_t)NQ * g.N * pos < lim - 4096)
         return launch_project_s<NQ, STG_LIST>(p, R, f, E, s);
+    if (g.K < 4) return launch_project_s<NQ, STG_FEW>(p, R, f, E, s);
     return launch_project_s<NQ, STG_REGS>(p, R, f, E, s);
 }
 

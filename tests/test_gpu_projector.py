@@ -53,6 +53,36 @@ def test_forward_edges(G):
     assert np.abs(got - want).max() <= 1e-5 * np.abs(want).max()
 
 
+FEW_CHANNELS = [   # a quad per slice: 1, 2 and 4 slices per workgroup and a ragged last one, long lines, many classes
+    geom(64, 9, 64, 3, 13, 1), geom(200, 7, 130, 2, 60, 3), geom(256, 20, 256, 2, 128, 2), geom(166, 5, 110, 18, 40, 2),
+    geom(530, 6, 530, 2, 7, 1), geom(600, 1, 400, 1, 9, 2), geom(600, 3, 620, 2, 12, 3), geom(600, 2, 620, 20, 4, 3),
+]
+
+
+@pytest.mark.parametrize("G", FEW_CHANNELS, ids=lambda G: f"N{G.N}z{G.Nz}s{G.Ns}p{G.Npi}k{G.K}")
+def test_forward_few_channels(G):
+    """Fewer than four channels, at the same bar."""
+    test_forward_edges(G)
+
+
+@pytest.mark.parametrize("G", [geom(3664, 1, 64, 1, 5, 20), geom(2048, 2, 90, 1, 5, 58)],
+                         ids=lambda G: f"N{G.N}z{G.Nz}k{G.K}")
+def test_forward_large_slices(G):
+    """Quads of a slice whose offsets take more than 32 bits (through
+    registers), and a list of quads over slices of 0.97 GB.  Lines of N > 512:
+    2^-25 sqrt(32 + N / 64 + K / 2) of the result in rel-L2, as the rounding
+    of two-level sums has it (line parts only lessen it)."""
+    torch.cuda.set_device(DEV)
+    print(f"case {G}", flush=True)
+    f = inputs.uniform(G.f_shape, 9)
+    got = rt4d.Plan(G).forward(torch.from_numpy(f).to(DEV)).cpu().numpy().astype(np.float64)
+    want = O.forward(O.Geom(**G.__dict__), f)
+    e = np.linalg.norm(got - want) / np.linalg.norm(want)
+    print(f"rel-L2 {e:.3e}", flush=True)
+    assert e <= 2.0 ** -25 * np.sqrt(32 + G.N / 64 + G.K / 2)
+    assert np.abs(got - want).max() <= 1e-5 * np.abs(want).max()
+
+
 ADJOINT_CASES = CASES + [
     # 32 x 32 tiles (the cases above fill few: 32 x 8), ragged and aligned,
     # quads of one and of several slices, a ragged last quad; detectors that end
