@@ -42,7 +42,6 @@ __device__ inline int clamp0_i32(int x, int hi)
 // contract them with Phi over the Npi half-turns with the s-flip (Sec. 4, eq.
 // radapr and the pi-periodicity) and store g.
 struct FwdEpi {
-    const float *phi;     // [Ntheta][4 K4], channels K.. zero
     float *g;
     int n0, Npi;
 };
@@ -120,7 +119,7 @@ template <int NQ, int PPT, int PF, bool TL, int NTH, int STG>
 __global__ __launch_bounds__(NTH) void k_project(
     const float *__restrict__ f, float *P, const RayGroup *__restrict__ groups,
     const int *__restrict__ wcls, const unsigned char *__restrict__ rlane, const double *__restrict__ ccos,
-    const double *__restrict__ csin, RayArgs A, FwdEpi E)
+    const double *__restrict__ csin, const float *__restrict__ phi, RayArgs A, FwdEpi E)
 {
     constexpr int NW = NTH / 64;
     constexpr int SH = NQ == 4 ? 6 : NQ == 2 ? 5 : 4;   // log2 of a row's bytes
@@ -348,13 +347,14 @@ __global__ __launch_bounds__(NTH) void k_project(
 
     // acc[j][q] holds column quad q ^ (rho / 16) of block j
     const int rq = (int)rho / 16, Kp = 4 * K4, nq = A.Nz * K4;
-    // quad q's sums with a ragged last quad's kr channels moved to its front
+    // a ragged last quad's kr channels moved to its front
+    auto front = [&](v4 x) {
+        return v4{kr == 1 ? x[3] : kr == 2 ? x[2] : x[1], kr == 1 ? 0.f : kr == 2 ? x[3] : x[2],
+                  kr == 3 ? x[3] : 0.f, 0.f};
+    };
     auto sums = [&](int j, int q) {
         v4 x{acc[j][q][0], acc[j][q][1], acc[j][q][2], acc[j][q][3]};
-        if (kr && K > 4 && (cg * NQ + (q ^ rq)) % K4 == K4 - 1)
-            x = v4{kr == 1 ? x[3] : kr == 2 ? x[2] : x[1], kr == 1 ? 0.f : kr == 2 ? x[3] : x[2],
-                   kr == 3 ? x[3] : 0.f, 0.f};
-        return x;
+        return kr && K > 4 && (cg * NQ + (q ^ rq)) % K4 == K4 - 1 ? front(x) : x;
     };
     auto psum = [&](int j, int g) {   // where P keeps column quad g of block j's ray
         return (v4 *)(P + ((((size_t)lp * E.n0 + cl[j]) * A.Nz + g / K4) * Ns + bin[j]) * Kp + 4 * (g % K4));
@@ -435,29 +435,53 @@ __global__ __launch_bounds__(NTH) void k_project(
     }
 #pragma unroll
     for (int j = 0; j < PPT; ++j) {
-        const int a = cl[j], b = bin[j];
+        const int a = __builtin_amdgcn_readfirstlane(cl[j]), b = bin[j];
         if (a < 0 || b >= Ns) continue;
         // all K channels of the workgroup's NQ / K4 slices are here (K4 = 1,
-        // 2 or 4 divides NQ).  A slice's quads are summed as a tree, which no
-        // lane order changes.
-        for (int r = 0; r < E.Npi; ++r) {
-            const int i = r * E.n0 + a;
-            float s[NQ];
+        // 2 or 4 divides NQ).  The quads are put in order first, so that the Phi
+        // rows are uniform over the wave.  A slice's quads are summed as a tree.
+        v4 x[NQ];
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) x[q] = v4{acc[j][q][0], acc[j][q][1], acc[j][q][2], acc[j][q][3]};
+#pragma unroll
+        for (int bit = 1; bit < NQ; bit *= 2)
 #pragma unroll
             for (int q = 0; q < NQ; ++q)
-                s[q] = dot4(*(const float4 *)(E.phi + (size_t)i * Kp + 4 * ((q ^ rq) & (K4 - 1))), sums(j, q));
-            const int bo = (r & 1) ? Ns - 1 - b : b;
-            auto put = [&](int sl, float v) {   // slice sl of the workgroup
-                if (z0 + sl < A.Nz) E.g[((size_t)i * A.Nz + z0 + sl) * Ns + bo] = v;
-            };
+#pragma unroll
+                for (int t = 0; t < 4; ++t)
+                    if (!(q & bit)) {
+                        float lo = x[q][t], hi = x[q | bit][t];
+                        asm volatile("" : "+v"(lo), "+v"(hi));   // two selects, not an index into x
+                        x[q][t] = rq & bit ? hi : lo;
+                        x[q | bit][t] = rq & bit ? lo : hi;
+                    }
+        if (kr && K > 4)
+#pragma unroll
+            for (int q = 0; q < NQ; ++q)
+                if ((cg * NQ + q) % K4 == K4 - 1) x[q] = front(x[q]);
+        // uniform addresses, stepped per half-turn: a wave alone issues an
+        // instruction in 8 cycles, and the address of each store formed anew
+        // took more of them than the rest
+        const float *pr = phi + (size_t)a * Kp;
+        float *gr = E.g + ((size_t)a * A.Nz + z0) * Ns;
+        const size_t pstep_r = (size_t)E.n0 * Kp, gstep_r = (size_t)E.n0 * A.Nz * Ns;
+        const int nsl = min(NQ / K4, A.Nz - z0);   // slices of the workgroup
+#pragma unroll 2
+        for (int r = 0; r < E.Npi; ++r, pr += pstep_r, gr += gstep_r) {
+            float s[NQ];
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) s[q] = dot4(*(const float4 *)(pr + 4 * (q & (K4 - 1))), x[q]);
+            const unsigned bo = (r & 1) ? Ns - 1 - b : b;
             if (K4 == 1) {
 #pragma unroll
-                for (int q = 0; q < NQ; ++q) put(q ^ rq, s[q]);
+                for (int q = 0; q < NQ; ++q)
+                    if (q < nsl) gr[(size_t)q * Ns + bo] = s[q];
             } else if (K4 == 2) {
 #pragma unroll
-                for (int q = 0; q + 1 < NQ; q += 2) put((q ^ rq) >> 1, s[q] + s[q + 1]);
+                for (int q = 0; q + 1 < NQ; q += 2)
+                    if (q / 2 < nsl) gr[(size_t)(q / 2) * Ns + bo] = s[q] + s[q + 1];
             } else if constexpr (NQ == 4) {
-                put(0, (s[0] + s[1]) + (s[2] + s[3]));
+                gr[bo] = (s[0] + s[1]) + (s[2] + s[3]);
             }
         }
     }
@@ -474,10 +498,11 @@ template <int KQ>
 __global__ __launch_bounds__(NT) void k_contract(
     const float *__restrict__ P, const float *__restrict__ phi, float *__restrict__ out,
     const float *__restrict__ gdata, int mode, float sigma, double *__restrict__ part, int Nz,
-    int Ns, int K4, int n0, int Npi, int NLP, int EPT, int nch)
+    int Ns, int K4, int n0, int Npi, int NLP, int EPT, int nch, int RP)
 {
     __shared__ double sh[NT / 64];
-    const int a = blockIdx.x / nch, ch = blockIdx.x % nch;
+    const int rp = blockIdx.x % RP, a = blockIdx.x / RP / nch, ch = blockIdx.x / RP % nch;
+    const int rbeg = rp * Npi / RP, rend = (rp + 1) * Npi / RP;
     const int Kp = 4 * K4, ne = Nz * Ns;
     const size_t pstride = (size_t)n0 * ne * Kp;   // between the parts
     double d2 = 0.0;
@@ -495,7 +520,7 @@ __global__ __launch_bounds__(NT) void k_contract(
             x[q] = *(const v4 *)(src + 4 * q);
             for (int lp = 1; lp < NLP; ++lp) x[q] += *(const v4 *)(src + lp * pstride + 4 * q);
         }
-        for (int r = 0; r < Npi; ++r) {
+        for (int r = rbeg; r < rend; ++r) {
             const int i = r * n0 + a;
             const float *ph = phi + (size_t)i * Kp;
             float v = 0.f;
@@ -575,7 +600,7 @@ static int launch_project_t(const Plan &p, const RayCfg &R, const float *f, cons
     KTimer kt("k_project", s);
     hipLaunchKernelGGL(kern, dim3(R.nblocks), dim3(NTH), R.lds, s, f, p.d_scr, p.d_groups + R.group0,
                        p.d_wcls, p.d_lanes + (size_t)(NQ == 4 ? 2 : NQ == 2 ? 1 : 0) * p.n0 * 64,
-                       p.d_ccos, p.d_csin, A, E);
+                       p.d_ccos, p.d_csin, p.d_phip, A, E);
     kt.stop();
     return RT_OK;
 }
@@ -608,18 +633,27 @@ static int launch_project_q(const Plan &p, const RayCfg &R, const float *f, cons
     return launch_project_s<NQ, STG_REGS>(p, R, f, E, s);
 }
 
-// workgroups of k_contract: per class, NT * EPT (slice, bin) pairs each
+// workgroups of k_contract: per class, NT * EPT (slice, bin) pairs and one of RP
+// parts of the half-turns each.  The half-turns are walked one after the other
+// (their Phi rows, g and h1 are read as they come up): where the pairs make
+// less than 4 workgroups per CU, they are split, into no more parts than reading
+// P in each of them costs 4 MB.  Measured, one part against the split: 64^2 x 4,
+// 30 classes, 40 half-turns, K = 8 14.5 and 9.0 us; 64^2, 90 classes, 8 half-turns
+// with the prox 8.4 and 7.6; 8^2 x 5, 34 half-turns, K = 45 30 and 7.5; 512^2, 180
+// classes (29 MB of P), 10 half-turns 15.3 and, split into six, 54.6.
 struct ContractGrid {
-    int EPT, nch;
+    int EPT, nch, RP;
     unsigned nb;
 };
-static ContractGrid contract_grid(const Plan &p)
+static ContractGrid contract_grid(const Plan &p, int NLP)
 {
     const long ne = (long)p.g.Nz * p.g.Ns;
     ContractGrid c;
     c.EPT = (int)std::max(1L, std::min(4L, ne * p.n0 / (4096L * NT)));
     c.nch = (int)((ne + (long)NT * c.EPT - 1) / ((long)NT * c.EPT));
-    c.nb = (unsigned)p.n0 * c.nch;
+    const long nw = std::max((long)p.n0 * c.nch, 1L), pb = std::max(NLP * ne * p.n0 * ((p.g.K + 3) / 4 * 16), 1L);
+    c.RP = (int)std::max(1L, std::min<long>({p.g.Npi, (1024 + nw - 1) / nw, 1 + (4L << 20) / pb}));
+    c.nb = (unsigned)(nw * c.RP);
     return c;
 }
 
@@ -633,22 +667,24 @@ int launch_forward_pf(const Plan &p, const float *f, float *g, int mode, const f
     const RayCfg R = ray_cfg(p);
     // The h1 prox runs in k_contract: its reads of g and h1 at the end of the
     // projection, one workgroup per CU, are covered by nothing (512^2 x 32: 2.84
-    // ms with the prox inside, 2.69 + 0.12 without); so are the stores of many
-    // half-turns (40 of them: 346 us inside, 293 + 29 us outside; 10 of them
-    // at 512^2 x 128: 9.90 ms inside, 9.77 + 0.26 outside).
+    // ms with the prox inside, 2.69 + 0.12 without).  So is the contraction of
+    // more than 16 half-turns where the workgroups are few (8^2 x 22, 234 classes,
+    // 19 of them, K = 16: 27.9 us inside, 22.0 outside); in large volumes the two
+    // are equal (315^2 x 20, 40 of them 320 and 325 us), and fewer half-turns are
+    // better inside (512^2 x 128, 10 of them: 9.90 and 10.03 ms).
     const bool fused = R.fusable && mode == CONTRACT_STORE && G.Npi <= 16;
-    const FwdEpi E{p.d_phip, fused ? g : nullptr, p.n0, G.Npi};
+    const FwdEpi E{fused ? g : nullptr, p.n0, G.Npi};
     const int rc = R.NQ == 4   ? launch_project_q<4>(p, R, f, E, s)
                    : R.NQ == 2 ? launch_project_q<2>(p, R, f, E, s)
                                : launch_project_q<1>(p, R, f, E, s);
     if (rc) return rc;
     RT_HIP(hipGetLastError());
     if (fused) return RT_OK;
-    const ContractGrid c = contract_grid(p);
+    const ContractGrid c = contract_grid(p, R.NLP);
     KTimer kt("k_contract", s);
 #define RT_CONTRACT(Q) hipLaunchKernelGGL(k_contract<Q>, dim3(c.nb), dim3(NT), 0, s, p.d_scr, p.d_phip, \
                                           mode == CONTRACT_STORE ? g : h1, gdata, mode, sigma, part, G.Nz, G.Ns, R.K4, p.n0,    \
-                                          G.Npi, R.NLP, c.EPT, c.nch)
+                                          G.Npi, R.NLP, c.EPT, c.nch, c.RP)
     if (R.K4 <= 2) RT_CONTRACT(2);
     else if (R.K4 <= 4) RT_CONTRACT(4);
     else if (R.K4 <= 8) RT_CONTRACT(8);
@@ -662,7 +698,7 @@ int launch_forward_pf(const Plan &p, const float *f, float *g, int mode, const f
 int forward_partials(const Plan &p)   // of the h1 prox
 {
     if (p.form == RT_FORM_SF) return (int)sf_partials(p);
-    return (int)contract_grid(p).nb;
+    return (int)contract_grid(p, ray_cfg(p).NLP).nb;
 }
 
 int launch_forward(const Plan &p, const float *f, float *g, int mode, const float *gdata,

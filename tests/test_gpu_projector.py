@@ -65,6 +65,18 @@ def test_forward_few_channels(G):
     test_forward_edges(G)
 
 
+MANY_HALF_TURNS = [   # contracted in parts of the half-turns, with and without line parts; in the projection, ragged last group
+    geom(20, 2, 24, 40, 3, 20), geom(8, 5, 5, 34, 12, 45), geom(64, 1, 64, 20, 9, 8), geom(40, 3, 50, 17, 7, 6),
+    geom(48, 15, 48, 13, 60, 7), geom(48, 16, 48, 16, 60, 4), geom(48, 7, 48, 9, 70, 16), geom(30, 9, 33, 5, 64, 3),
+]
+
+
+@pytest.mark.parametrize("G", MANY_HALF_TURNS, ids=lambda G: f"N{G.N}z{G.Nz}s{G.Ns}p{G.Npi}k{G.K}")
+def test_forward_many_half_turns(G):
+    """The contraction with Phi over many half-turns, at the same bar."""
+    test_forward_edges(G)
+
+
 @pytest.mark.parametrize("G", [geom(3664, 1, 64, 1, 5, 20), geom(2048, 2, 90, 1, 5, 58)],
                          ids=lambda G: f"N{G.N}z{G.Nz}k{G.K}")
 def test_forward_large_slices(G):
