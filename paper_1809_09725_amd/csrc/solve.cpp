@@ -313,9 +313,19 @@ extern "C" int rt_job_bytes(const rt_geom *geom, rt_form form, rt_prec prec, siz
     if (rc) return rc;
     if (!bytes) return fail(RT_E_ARG, "bytes is NULL");
     const rt_geom &g = *geom;
+    const size_t n0 = (size_t)(g.Ntheta / g.Npi), nbb = (size_t)(g.Ns + 63) / 64, ne = (size_t)g.Nz * g.Ns;
+    // per angle Phi twice (once with K rounded up to 4); per class the trigonometric
+    // tables, lane orders and class lists; at most a ray group per class and block
+    // of 64 bins, full and small
     const size_t tables = ((size_t)g.Ntheta * (2 * g.K + 3) + (size_t)g.Nt * g.K) * sizeof(float) +
-                          (size_t)(g.Ntheta / g.Npi) * (2 * sizeof(double) + 3 * 64 + 4) + 64 * 1024;
-    const size_t parts = ((size_t)1 << 18) * sizeof(double) + 16 * sizeof(double);
+                          n0 * (2 * sizeof(double) + 3 * 64 + 6 * sizeof(int)) +
+                          2 * n0 * nbb * sizeof(RayGroup) + 64 * 1024;
+    // partial sums: of the h1 prox (k_contract: 1024 pairs a workgroup where there
+    // are that many; the synthesise-first projector: at least a class and 512 bins), of
+    // the voxel kernels
+    const size_t parts = (std::max((size_t)1 << 18,
+                                   n0 * std::max(ne / 1024 + 1, (size_t)g.Nz * ((g.Ns + 511) / 512)) + 3 * 8192 + 64) +
+                          16) * sizeof(double);
     *bytes = tables + parts + plan_scratch_bytes(g, g.Nz) + n4_of(g) * sizeof(float) + job_state_bytes(g) +
              (form == RT_FORM_SF ? shadow_bytes(g) + sf_partial_bytes(g) : 0);
     return RT_OK;

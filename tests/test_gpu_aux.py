@@ -56,3 +56,25 @@ def test_timing_counters_around_a_forward():
     rt4d.timing_reset()
     assert rt4d.timing_read("k_project") == (0.0, 0)
     plan.close()
+
+
+@pytest.mark.parametrize("sf,dims", [
+    (False, dict(N=16, Nz=1, Ns=2048, n0=3000, Npi=1, K=1)),      # many bins and classes: ray groups
+    (False, dict(N=32, Nz=1, Ns=91, n0=16000, Npi=1, K=1)),       # many classes: class lists
+    (True, dict(N=32, Nz=2, Ns=100, n0=9000, Npi=1, K=2)),
+    (False, dict(N=8, Nz=512, Ns=2048, n0=300, Npi=1, K=1)),      # more than 2^18 partial sums
+    (False, dict(N=64, Nz=3, Ns=91, n0=90, Npi=8, K=7)), (True, dict(N=128, Nz=1, Ns=128, n0=60, Npi=4, K=16)),
+])
+def test_job_bytes_cover_the_plan(sf, dims):
+    """rt_job_bytes, the admission's figure, is at least what the plan holds
+    and a job's state ((2 f + 2 g + 5 frames) floats) take."""
+    torch.cuda.set_device(DEV)
+    n0 = dims.pop("n0")
+    G = rt4d.Geom(Ntheta=dims["Npi"] * n0, Nt=1, **dims)
+    form = (rt4d.RT_FORM_SF, rt4d.RT_PREC_BF16MFMA) if sf else (rt4d.RT_FORM_PF, rt4d.RT_PREC_FP32)
+    plan = rt4d.Plan(G, *form)
+    nv = G.Nz * G.N * G.N
+    state = 4 * (2 * nv * G.K + 2 * G.Ntheta * G.Nz * G.Ns + 5 * nv * G.Nt)
+    print(f"{G}: plan {plan.bytes} + state {state}, rt_job_bytes {rt4d.rt_job_bytes(G, *form)}", flush=True)
+    assert plan.bytes + state <= rt4d.rt_job_bytes(G, *form)
+    plan.close()
