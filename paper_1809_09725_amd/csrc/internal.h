@@ -108,6 +108,7 @@ struct Plan {
     bool adjoint_only = false;
     std::vector<RayGroup> groups;   // full workgroups, then small ones
     int ngroups = 0;      // full workgroups
+    RayCfg ray;           // of this plan's slices (ray_cfg)
     SfCfg sf;
     TvCfg tv;
 

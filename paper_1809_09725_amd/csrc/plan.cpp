@@ -45,9 +45,9 @@ int check_geom(const rt_geom *g)
     if (g->N > 4096 || g->Ns > 8192 || g->K > 64 || g->Nt > 64 || (int64_t)g->Npi * g->K > 16384)
         return fail(RT_E_SHAPE, "size beyond the supported maximum (N<=4096, Ns<=8192, "
                     "K<=64, Nt<=64, Npi*K<=16384)");
-    // a staged line of the projector is held in the prefetch registers of its
-    // 512 threads: scalar staging (K % 4 != 0) covers lines of N <= 2048
-    // positions, float4 staging N <= 4096
+    // a limit of the interface, kept for every plan: slices of more than 2048^2
+    // pixels with a ragged last channel quad are not among the sizes that were
+    // ever checked against the oracle (no kernel depends on it)
     if (g->N > 2048 && g->K % 4 != 0)
         return fail(RT_E_SHAPE, "N=%d > 2048 needs K to be a multiple of 4 (got K=%d)", g->N, g->K);
     return RT_OK;
@@ -497,6 +497,7 @@ static int create(const rt_geom *geom, rt_form form, rt_prec prec, const double 
     TableUpload up;
     int rc = configure(p, up);
     if (rc) return rc;
+    if (!adjoint_only) p.ray = ray_cfg(p);
     std::vector<float> phi32(p.T.phi.begin(), p.T.phi.end()), S32(p.T.S.begin(), p.T.S.end());
     const size_t Kp = (size_t)(geom->K + 3) / 4 * 4;
     std::vector<float> phip((size_t)geom->Ntheta * Kp, 0.f);

@@ -664,7 +664,7 @@ int launch_forward_pf(const Plan &p, const float *f, float *g, int mode, const f
 {
     const rt_geom &G = p.g;
     if (G.Nz == 0) return RT_OK;
-    const RayCfg R = ray_cfg(p);
+    const RayCfg &R = p.ray;
     // The h1 prox runs in k_contract: its reads of g and h1 at the end of the
     // projection, one workgroup per CU, are covered by nothing (512^2 x 32: 2.84
     // ms with the prox inside, 2.69 + 0.12 without).  So is the contraction of
@@ -698,7 +698,7 @@ int launch_forward_pf(const Plan &p, const float *f, float *g, int mode, const f
 int forward_partials(const Plan &p)   // of the h1 prox
 {
     if (p.form == RT_FORM_SF) return (int)sf_partials(p);
-    return (int)contract_grid(p, ray_cfg(p).NLP).nb;
+    return (int)contract_grid(p, p.ray.NLP).nb;
 }
 
 int launch_forward(const Plan &p, const float *f, float *g, int mode, const float *gdata,

@@ -73,6 +73,7 @@ int power_iteration(Job &J, hipStream_t s)
     Plan p = full;
     p.g.Nz = full.g.Nz > 0 ? 1 : 0;
     p.nz_ref = p.g.Nz;
+    p.ray = ray_cfg(p);
     const size_t nf = nf_of(p.g), ng = ng_of(p.g);
     float *x = J.ft, *y = J.work;
     int rc = launch_seeded_uniform(x, nf, J.prm.seed, s);
