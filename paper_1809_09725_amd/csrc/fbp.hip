@@ -55,7 +55,7 @@ __global__ __launch_bounds__(SL_T) void k_shepp_logan(const float *__restrict__ 
     const int TPR = SL_T / RPW;             // threads per row
     const int rr = threadIdx.x / TPR, lt = threadIdx.x % TPR;
     const long r = r0 + rr;
-    if (r >= rows) return;
+    if (rr >= RPW || r >= rows) return;   // RPW need not divide the threads
     const float *row = srow + (size_t)rr * Nsp;
     for (int b0 = 4 * lt; b0 < Ns; b0 += 4 * TPR) {
         float acc[4] = {0.f, 0.f, 0.f, 0.f};

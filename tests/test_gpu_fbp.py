@@ -53,6 +53,22 @@ def test_filter_parity(Ns, nth):
     assert e <= 1e-5
 
 
+@pytest.mark.parametrize("Ns", [140, 158, 179, 200, 270, 304, 340])
+def test_filter_rows_per_workgroup(Ns):
+    """Rows of a length of which 3, 5, 6 or 7 go to a workgroup, a number that
+    does not divide its threads: every row, and the same bits each time."""
+    G = rt4d.Geom(N=4, Nz=3, Ns=Ns, Ntheta=667, Npi=1, K=1, Nt=1)
+    p = rt4d.Plan(G)
+    g = inputs.uniform(G.g_shape, 170 + Ns)
+    q = p.fbp_filter(T(g))
+    want = O.shepp_logan(og(G), g)
+    e = rel(q.cpu().numpy(), want)
+    print(f"Ns={Ns}: rel {e:.2e}", flush=True)
+    assert e <= 1e-5
+    for _ in range(5):
+        assert torch.equal(p.fbp_filter(T(g)), q)
+
+
 FBP_SHAPES = [
     rt4d.Geom(N=64, Nz=1, Ns=64, Ntheta=720, Npi=8, K=8, Nt=8),
     rt4d.Geom(N=45, Nz=3, Ns=50, Ntheta=3 * 37, Npi=3, K=5, Nt=3),      # ragged, K % 4 != 0
