@@ -218,9 +218,9 @@ __global__ __launch_bounds__(NT) void k_grad(const float *__restrict__ F, float 
     // the workgroups of a plane's rows y and y+1 share an XCD's L2 (xcd_remap)
     const size_t lid = xcd_remap(blockIdx.x, gridDim.x);
     for (size_t it = lid * NT + threadIdx.x; it < nitem; it += (size_t)gridDim.x * NT) {
-        const size_t pv = it % plane;
+        const unsigned pv = (unsigned)(it % plane);
         const int chunk = (int)(it / plane), mb = chunk % nmc * MC, me = min(Nt, mb + MC);
-        const int q = (int)(pv % N), r = (int)(pv / N);
+        const int q = (int)(pv % (unsigned)N), r = (int)(pv / (unsigned)N);
         const bool hx = q < N - 1, hy = r < N - 1;
         const size_t ox = hx ? 1 : 0, oy = hy ? N : 0;
         const int z0 = zbeg + chunk / nmc * ZC, ze = min(zend, z0 + ZC);
