@@ -45,13 +45,14 @@ struct Tables {
     std::vector<double> ccos, csin;     // [Ntheta0] cos/sin of theta0_a
 };
 
-// Rays of one workgroup of the plain projector (k_project): bin blocks [bb0,
-// bb0 + bbt) (64 bins each) of the classes [cls0, cls0 + ncls) of the class
-// list, which share one walk direction (0: rows, |cos| >= |sin|; 1: columns)
-// and neighbour each other in angle.  On line l their taps lie in the W
+// Rays of one workgroup of the plain projector (k_project): bins [b0, b0 + nb)
+// of the classes [cls0, cls0 + ncls) of the class list, which share one walk
+// direction (0: rows, |cos| >= |sin|; 1: columns) and neighbour each other in
+// angle; a wave's block of 64 is 64 rays of the list of classes times bins, of two
+// classes where nb is no multiple of 64.  On line l their taps lie in the W
 // positions from floor(wl0 + l sw) on (32.32 fixed point).
 struct RayGroup {
-    int walk, cls0, ncls, bb0, bbt, W;
+    int walk, cls0, ncls, b0, nb, W;
     long long wl0, sw;
 };
 // float4 staged per thread and stage, threads and ray blocks of a workgroup

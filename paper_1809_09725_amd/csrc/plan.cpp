@@ -94,10 +94,10 @@ static LineSplit line_split(const rt_geom &g, int nz)
     LineSplit best;
     if (nz < 1) return best;
     const long n0 = g.Ntheta / g.Npi;
-    const long K4 = (g.K + 3) / 4, nbb = (g.Ns + 63) / 64;
+    const long K4 = (g.K + 3) / 4;
     const int NQ = quads_per_row(g, nz);
     const long ncg = (nz * K4 + NQ - 1) / NQ;
-    const long half = (n0 + 1) / 2 * nbb;   // ray blocks of a walk, about
+    const long half = ((n0 + 1) / 2 * g.Ns + 63) / 64;   // ray blocks of a walk, about
     const bool fusable = g.N <= 512 && K4 <= NQ && NQ % K4 == 0;
     double cost = 1e300;
     for (int small = 0; small < (g.N <= 256 ? 2 : 1); ++small) {
@@ -119,6 +119,24 @@ static LineSplit line_split(const rt_geom &g, int nz)
         }
     }
     return best;
+}
+
+// The workgroup size for nz slices, of which the full size has `ngroups` ray
+// groups: line_split's; but where that is one part of full workgroups, small
+// ones all the same for lines of at most 64 positions (the 16 waves of a full
+// one then spend more on its barriers than on taps: 48^2 x 40, 8 channels, 200
+// classes: 70 us full, 39 small; 64^2 x 120, 16 channels, 30 classes: 69 and
+// 47), and for lines of at most 128 where the full ones fill less than 0.7 of
+// the rounds that they take (128^2 x 40, 8 channels, 200 classes, 1.2 rounds:
+// 239 and 176).  In fuller rounds small ones lose there: 70^2 x 120, 8
+// channels, 90 classes: 88 and 122.
+static bool small_workgroups(const rt_geom &g, int nz, int ngroups)
+{
+    const LineSplit L = line_split(g, nz);
+    if (L.small || L.NLP > 1 || nz < 1) return L.small;
+    const int NQ = quads_per_row(g, nz);
+    const long W = ((long)nz * ((g.K + 3) / 4) + NQ - 1) / NQ * ngroups, slots = (W + 255) / 256 * 256;
+    return g.N <= 64 || (g.N <= 128 && W * 10 < slots * 7);
 }
 
 size_t adjoint_scratch_bytes(const rt_geom &g)
@@ -171,15 +189,16 @@ static void ray_window(int N, int Ns, const RayDir *d, int n, int b0, int b1, Ra
     }
 }
 
-// Ray groups of at most `blocks` bin blocks with windows of at most wmax
-// positions.  A group is a tile of bin blocks over neighbouring classes; more
-// classes and fewer bins (or the reverse) widen the window by their fan-out
-// (their spacing).  The tile width is the power of two that costs least: per
-// line the LDS cycles of the taps and of the window's stores and a share of
-// the barrier, as k_project's comment has them.  At 512^2 over 180 classes two
-// blocks of 16 classes: windows of 247 positions on average; whole lines
-// (eight blocks of four classes) took 12.8 ms against 9.85 there (128 slices of
-// 16 channels) and 8.45 against 5.76 at 1024^2 x 8.
+// Ray groups of at most `blocks` blocks of 64 rays with windows of at most
+// wmax positions.  A group is a tile of bins (blocks of 64, the last one up to
+// the detector's end) over neighbouring classes; more classes and fewer bins
+// (or the reverse) widen the window by their fan-out (their spacing).  The
+// tile width is the power of two that costs least: per line the LDS cycles of
+// the taps and of the window's stores and a share of the barrier, as
+// k_project's comment has them.  At 512^2 over 180 classes two blocks of 16
+// classes: windows of 247 positions on average; whole lines (eight blocks of
+// four classes) took 12.8 ms against 9.85 there (128 slices of 16 channels)
+// and 8.45 against 5.76 at 1024^2 x 8.
 static std::vector<RayGroup> ray_groups(const rt_geom &g, const std::vector<RayDir> (&lists)[3], int blocks, int wmax)
 {
     const int nbb = (g.Ns + 63) / 64, N = g.N, Ns = g.Ns;
@@ -196,17 +215,30 @@ static std::vector<RayGroup> ray_groups(const rt_geom &g, const std::vector<RayD
             for (int t = 0; t < nt; ++t) {
                 RayGroup G{};
                 G.walk = s == 1;
-                G.bb0 = t * (nbb / nt) + std::min(t, nbb % nt);
-                G.bbt = nbb / nt + (t < nbb % nt ? 1 : 0);
-                const int b0 = G.bb0 * 64, b1 = std::min((G.bb0 + G.bbt) * 64, Ns) - 1;
+                const int bbt = nbb / nt + (t < nbb % nt ? 1 : 0);
+                G.b0 = 64 * (t * (nbb / nt) + std::min(t, nbb % nt));
+                G.nb = std::min(64 * bbt, Ns - G.b0);
+                const int b1 = G.b0 + G.nb - 1;
                 for (int i = 0; i < (int)L.size(); i += G.ncls) {
-                    G.cls0 = cls0 + i;
-                    G.ncls = std::min(blocks / G.bbt, (int)L.size() - i);
-                    ray_window(N, Ns, L.data() + i, G.ncls, b0, b1, G);
-                    while (G.W > wmax && G.ncls > 1) ray_window(N, Ns, L.data() + i, --G.ncls, b0, b1, G);
-                    if (G.W > wmax) fits = false;
-                    const int lines = std::max(1, wmax / G.W >= 4 ? 4 : wmax / G.W >= 2 ? 2 : 1);
-                    cost += G.ncls * G.bbt * 40.0 + G.W * 0.5 + 500.0 / lines;
+                    // classes of whole blocks or, at the detector's end, as many
+                    // as fit the rays: what costs less per ray
+                    RayGroup best_g{};
+                    double best_c = 1e300;
+                    for (int ncls : {blocks / bbt, blocks * 64 / G.nb}) {
+                        G.cls0 = cls0 + i;
+                        G.ncls = std::min(ncls, (int)L.size() - i);
+                        ray_window(N, Ns, L.data() + i, G.ncls, G.b0, b1, G);
+                        while (G.W > wmax && G.ncls > 1) ray_window(N, Ns, L.data() + i, --G.ncls, G.b0, b1, G);
+                        if (G.W > wmax) fits = false;
+                        const int lines = std::max(1, wmax / G.W >= 4 ? 4 : wmax / G.W >= 2 ? 2 : 1);
+                        const double c = (G.ncls * G.nb + 63) / 64 * 40.0 + G.W * 0.5 + 500.0 / lines;
+                        if (c / G.ncls < best_c) {
+                            best_c = c / G.ncls;
+                            best_g = G;
+                        }
+                    }
+                    G = best_g;
+                    cost += best_c * G.ncls;
                     v.push_back(G);
                 }
             }
@@ -232,13 +264,14 @@ RayCfg ray_cfg(const Plan &p)
     R.ncg = (tq + R.NQ - 1) / R.NQ;
     R.tl = g.N > 512;
     R.NLP = L.NLP;
-    R.nth = L.small ? RAY_NTH_SMALL : RAY_NTH;
-    R.group0 = L.small ? p.ngroups : 0;
-    R.ngroups = L.small ? (int)p.groups.size() - p.ngroups : p.ngroups;
+    const bool small = small_workgroups(g, p.nz_ref, p.ngroups);
+    R.nth = small ? RAY_NTH_SMALL : RAY_NTH;
+    R.group0 = small ? p.ngroups : 0;
+    R.ngroups = small ? (int)p.groups.size() - p.ngroups : p.ngroups;
     R.fusable = R.NLP == 1 && !R.tl && R.K4 <= R.NQ && R.NQ % R.K4 == 0;
     R.nblocks = (unsigned)R.ncg * R.ngroups * R.NLP;
     // stage buffers: as k_project lays them out
-    const int rpj = R.nth / R.NQ, pf = L.small ? RAY_PF_SMALL : RAY_PF;
+    const int rpj = R.nth / R.NQ, pf = small ? RAY_PF_SMALL : RAY_PF;
     int rows = 0;
     for (int i = 0; i < R.ngroups; ++i) {
         const int W = p.groups[R.group0 + i].W;
@@ -349,14 +382,14 @@ static int configure(Plan &p, TableUpload &up)
     if (!p.adjoint_only) p.groups = ray_groups(g, lists, RAY_BLOCKS, RAY_WMAX);
     p.ngroups = (int)p.groups.size();
     if (!p.adjoint_only && !p.ngroups) return fail(RT_E_SHAPE, "no ray groups of the projector for N=%d Ns=%d", g.N, g.Ns);
-    if (!p.adjoint_only && (line_split(g, p.nz_ref).small || line_split(g, 1).small)) {
+    if (!p.adjoint_only && (small_workgroups(g, p.nz_ref, p.ngroups) || small_workgroups(g, 1, p.ngroups))) {
         const std::vector<RayGroup> v = ray_groups(g, lists, RAY_BLOCKS_SMALL, RAY_WMAX_SMALL);
         p.groups.insert(p.groups.end(), v.begin(), v.end());
     }
 
     // Lane order of the forward waves.  A wave's 64 rays are 64 consecutive
-    // bins of one class; their positions on a line are spaced 1/|c| in [1,
-    // sqrt 2] apart.  A 16-byte LDS read is served 16 lanes at a time, in the
+    // bins of one class, or of neighbours in the order of the first; their
+    // positions on a line are spaced 1/|c| in [1, sqrt 2] apart.  A 16-byte LDS read is served 16 lanes at a time, in the
     // groups of lane quads {0,3,5,6}, {1,2,4,7} and the same + 8 (measured: a
     // lane on the same 16-byte unit as lane 0 costs a cycle for the lanes of
     // its group alone).  With NQ quads per staged position the lanes of a

@@ -68,8 +68,11 @@ __device__ inline float dot4(float4 w, v4 x)
 // Columns.  The Nz * K4 channel quads of all slices form one list; a
 // workgroup takes NQ consecutive ones, so K = 16 is one slice per workgroup
 // and K = 8 two, and a position of a staged line is NQ * 16 bytes in LDS.
-// Rays.  A workgroup takes one RayGroup: a tile of bins (blocks of 64) of
-// neighbouring classes of one walk direction, PPT blocks per wave.  Lines no
+// Rays.  A workgroup takes one RayGroup: a tile of bins of neighbouring
+// classes of one walk direction, as blocks of 64 rays, PPT blocks per wave.
+// Where the detector is no multiple of 64 a block runs on into the next class
+// (with a block per class and 64 bins, 100 bins left 22% of the lanes idle:
+// 100^2 x 40, 8 channels, 200 classes 205 us, packed 115).  Lines no
 // ray of a block crosses are skipped (a wave-uniform interval per block): 9%
 // of the tap work at Ns = N, more where the detector is wider than the slice.
 // Lines.  Only the window of W positions that the group's rays reach on a
@@ -152,12 +155,21 @@ __global__ __launch_bounds__(NTH) void k_project(
     // its guard positions, rays off the slice.
     long long U[PPT], S[PPT];
     float invc[PPT], sfr[PPT];
-    int cl[PPT], bin[PPT], jb[PPT], je[PPT];   // class (-1: none), bin, lines [jb, je) of the block
+    int cl[PPT], bin[PPT], jb[PPT], je[PPT];   // class (-1: none) and bin of a lane, lines [jb, je) of the block
+    const int nrays = G.ncls * G.nb;
 #pragma unroll
     for (int j = 0; j < PPT; ++j) {
-        const int n = j * NW + wave;
-        const int a = n < G.ncls * G.bbt ? wcls[G.cls0 + n / G.bbt] : -1;
-        const int b = a >= 0 ? (G.bb0 + n % G.bbt) * 64 + (int)rlane[a * 64 + lane] : Ns;
+        // block n: rays 64 n .. of the list of classes times bins, in the lane
+        // order of its first ray's class
+        const int first = (j * NW + wave) * 64;
+        int a = -1, b = Ns;
+        if (first < nrays) {
+            const int ray = first + (int)rlane[wcls[G.cls0 + first / G.nb] * 64 + lane], c = ray / G.nb;
+            if (ray < nrays) {
+                a = wcls[G.cls0 + c];
+                b = G.b0 + ray - c * G.nb;
+            }
+        }
         cl[j] = a;
         bin[j] = b;
         double base = -1.0e6, slope = 0.0, lo = 2.0e6, hi = -2.0e6;
@@ -435,8 +447,6 @@ __global__ __launch_bounds__(NTH) void k_project(
     }
 #pragma unroll
     for (int j = 0; j < PPT; ++j) {
-        const int a = __builtin_amdgcn_readfirstlane(cl[j]), b = bin[j];
-        if (a < 0 || b >= Ns) continue;
         // all K channels of the workgroup's NQ / K4 slices are here (K4 = 1,
         // 2 or 4 divides NQ).  The quads are put in order first, so that the Phi
         // rows are uniform over the wave.  A slice's quads are summed as a tree.
@@ -462,28 +472,35 @@ __global__ __launch_bounds__(NTH) void k_project(
         // uniform addresses, stepped per half-turn: a wave alone issues an
         // instruction in 8 cycles, and the address of each store formed anew
         // took more of them than the rest
-        const float *pr = phi + (size_t)a * Kp;
-        float *gr = E.g + ((size_t)a * A.Nz + z0) * Ns;
         const size_t pstep_r = (size_t)E.n0 * Kp, gstep_r = (size_t)E.n0 * A.Nz * Ns;
-        const int nsl = min(NQ / K4, A.Nz - z0);   // slices of the workgroup
+        const int b = bin[j], nsl = min(NQ / K4, A.Nz - z0);   // nsl: slices of the workgroup
+        auto contract = [&](int a) __attribute__((always_inline)) {
+            const float *pr = phi + (size_t)a * Kp;
+            float *gr = E.g + ((size_t)a * A.Nz + z0) * Ns;
 #pragma unroll 2
-        for (int r = 0; r < E.Npi; ++r, pr += pstep_r, gr += gstep_r) {
-            float s[NQ];
+            for (int r = 0; r < E.Npi; ++r, pr += pstep_r, gr += gstep_r) {
+                float s[NQ];
 #pragma unroll
-            for (int q = 0; q < NQ; ++q) s[q] = dot4(*(const float4 *)(pr + 4 * (q & (K4 - 1))), x[q]);
-            const unsigned bo = (r & 1) ? Ns - 1 - b : b;
-            if (K4 == 1) {
+                for (int q = 0; q < NQ; ++q) s[q] = dot4(*(const float4 *)(pr + 4 * (q & (K4 - 1))), x[q]);
+                const unsigned bo = (r & 1) ? Ns - 1 - b : b;
+                if (K4 == 1) {
 #pragma unroll
-                for (int q = 0; q < NQ; ++q)
-                    if (q < nsl) gr[(size_t)q * Ns + bo] = s[q];
-            } else if (K4 == 2) {
+                    for (int q = 0; q < NQ; ++q)
+                        if (q < nsl) gr[(size_t)q * Ns + bo] = s[q];
+                } else if (K4 == 2) {
 #pragma unroll
-                for (int q = 0; q + 1 < NQ; q += 2)
-                    if (q / 2 < nsl) gr[(size_t)(q / 2) * Ns + bo] = s[q] + s[q + 1];
-            } else if constexpr (NQ == 4) {
-                gr[bo] = (s[0] + s[1]) + (s[2] + s[3]);
+                    for (int q = 0; q + 1 < NQ; q += 2)
+                        if (q / 2 < nsl) gr[(size_t)(q / 2) * Ns + bo] = s[q] + s[q + 1];
+                } else if constexpr (NQ == 4) {
+                    gr[bo] = (s[0] + s[1]) + (s[2] + s[3]);
+                }
             }
-        }
+        };
+        if (cl[j] < 0) continue;
+        // one class in the block (uniform addresses), or several
+        const int a0 = __builtin_amdgcn_readfirstlane(cl[j]);
+        if (__all(cl[j] == a0)) contract(a0);
+        else contract(cl[j]);
     }
 }
 

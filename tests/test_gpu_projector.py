@@ -77,6 +77,20 @@ def test_forward_many_half_turns(G):
     test_forward_edges(G)
 
 
+PACKED_RAYS = [   # detectors of no whole number of ray blocks: blocks over two and more classes, in full and small workgroups,
+    # fused with Phi, through line parts, per ragged quad and below four channels; half-turns of both directions of the bins
+    geom(70, 1, 70, 2, 200, 16), geom(80, 40, 80, 3, 90, 8), geom(100, 30, 100, 2, 200, 7), geom(130, 12, 130, 3, 70, 4),
+    geom(66, 40, 66, 18, 60, 16), geom(66, 5, 17, 5, 300, 2), geom(33, 50, 5, 3, 201, 16), geom(48, 40, 48, 8, 100, 15),
+    geom(128, 20, 129, 2, 180, 16), geom(256, 20, 257, 2, 90, 8), geom(530, 2, 530, 2, 40, 12), geom(64, 12, 1, 4, 150, 20),
+]
+
+
+@pytest.mark.parametrize("G", PACKED_RAYS, ids=lambda G: f"N{G.N}z{G.Nz}s{G.Ns}a{G.n0}k{G.K}")
+def test_forward_packed_rays(G):
+    """Ray blocks over several classes, at the same bar."""
+    test_forward_edges(G)
+
+
 @pytest.mark.parametrize("G", [geom(3664, 1, 64, 1, 5, 20), geom(2048, 2, 90, 1, 5, 58)],
                          ids=lambda G: f"N{G.N}z{G.Nz}k{G.K}")
 def test_forward_large_slices(G):
