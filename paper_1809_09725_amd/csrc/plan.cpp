@@ -89,7 +89,7 @@ struct LineSplit {
 // of at most 256 positions, of workgroups of 4 ray blocks (several per CU).
 // Measured: one 512^2 slice of 16 channels over 180 classes, 46 full
 // workgroups, 462 us in one part, 119 in five.
-static LineSplit line_split(const rt_geom &g, int nz)
+static LineSplit line_split(const rt_geom &g, int nz, bool whole_blocks = false)
 {
     LineSplit best;
     if (nz < 1) return best;
@@ -97,7 +97,8 @@ static LineSplit line_split(const rt_geom &g, int nz)
     const long K4 = (g.K + 3) / 4;
     const int NQ = quads_per_row(g, nz);
     const long ncg = (nz * K4 + NQ - 1) / NQ;
-    const long half = ((n0 + 1) / 2 * g.Ns + 63) / 64;   // ray blocks of a walk, about
+    const long per = whole_blocks ? (g.Ns + 63) / 64 * 64 : g.Ns;
+    const long half = ((n0 + 1) / 2 * per + 63) / 64;   // ray blocks of a walk, about
     const bool fusable = g.N <= 512 && K4 <= NQ && NQ % K4 == 0;
     double cost = 1e300;
     for (int small = 0; small < (g.N <= 256 ? 2 : 1); ++small) {
@@ -139,6 +140,13 @@ static bool small_workgroups(const rt_geom &g, int nz, int ngroups)
     return g.N <= 64 || (g.N <= 128 && W * 10 < slots * 7);
 }
 
+// Line parts that a plan's scratch has room for: also the split that fits with
+// whole blocks of bins, more parts at times, which the precision form may use.
+static int line_parts_room(const rt_geom &g, int nz)
+{
+    return std::max(line_split(g, nz).NLP, line_split(g, nz, true).NLP);
+}
+
 size_t adjoint_scratch_bytes(const rt_geom &g)
 {
     return (size_t)(g.Ntheta / g.Npi) * g.Nz * g.Ns * ((size_t)(g.K + 3) / 4 * 4) * sizeof(float);
@@ -148,8 +156,8 @@ size_t plan_scratch_bytes(const rt_geom &g, int nz_ref)
 {
     const size_t n0 = (size_t)(g.Ntheta / g.Npi), Kp = (size_t)(g.K + 3) / 4 * 4;
     // partial ray sums of the whole volume, or of the one slice of the power iteration
-    const size_t slices = std::max((size_t)g.Nz * line_split(g, nz_ref).NLP,
-                                   g.Nz > 0 ? (size_t)line_split(g, 1).NLP : 0);
+    const size_t slices = std::max((size_t)g.Nz * line_parts_room(g, nz_ref),
+                                   g.Nz > 0 ? (size_t)line_parts_room(g, 1) : 0);
     return n0 * slices * g.Ns * Kp * sizeof(float);
 }
 
@@ -491,7 +499,7 @@ static int configure(Plan &p, TableUpload &up)
         C.NLP = sf_line_parts(g);
         if (C.NLP == 1) {
             const long wg = (long)p.nz_ref * C.ngroups * C.nbt;
-            const long room = (long)line_split(g, p.nz_ref).NLP * ((g.K + 3) / 4 * 4) / g.Npi;
+            const long room = (long)line_parts_room(g, p.nz_ref) * ((g.K + 3) / 4 * 4) / g.Npi;
             const long fit = C.ST == 512 ? 512 : 256;
             auto cost = [&](long n) { return (wg * n + fit - 1) / fit * ((g.N + n - 1) / n + 24); };
             for (long n = 2; n <= std::min<long>({room, 32, g.N}); ++n)
