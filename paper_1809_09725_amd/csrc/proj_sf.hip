@@ -90,8 +90,8 @@ __device__ inline int sf_bin(int tid, int a, const unsigned char *__restrict__ l
 // 512^2 x 16, 180 classes, K = 16: 2.22 -> 1.50 ms; 2048^2 x 2, K = 32:
 // 12.7 -> 7.4 ms.
 // Waves per SIMD asked for: with 33..48 channels and two bins or slots of up
-// to 20 half-turns a thread, 512 threads are held to 128 registers (134 or 131
-// otherwise; at most three spilt), so that two workgroups do fit a CU: 512^2 x
+// to 20 half-turns a thread, 512 threads are held to 128 registers (a few more
+// otherwise), so that two workgroups do fit a CU: 512^2 x
 // 16, 16 half-turns, K = 48: 5.40 -> 4.67 ms.  More sums, or more channels, would
 // spill tens of registers (256^2 x 16, 16 half-turns, K = 64: 1.13 -> 1.85 ms).
 constexpr int sf_waves(int npp, int kb, int as, int ub, int st)
@@ -190,34 +190,39 @@ __global__ __launch_bounds__(ST, sf_waves(NPP, KB, AS, UB, ST)) void k_project_s
     // B operand of one step for the wave's position tile: lane holds
     // position c0 + wave*32 + lane%32, channels kb*16 + 8*(lane/32) + 0..7.
     // Steps are loaded in order; past the last one the last line is read again.
-    // Positions past the slice read its last one and are zeroed.
+    // Positions past the slice read its last one and are zeroed before the
+    // product (zeroed as they were loaded, the waves at a line's end waited for
+    // their loads in every step, and the workgroup with them: 300^2 x 2, 567 bins,
+    // 329 classes, 18 half-turns, K = 54: 1.84 and 1.21 ms).
     v8bf raw[KB];
-    const unsigned loff = (unsigned)((lane & 31) * pstep) + 8 * (lane >> 5);
-    int lch = 0, ll = lbeg;
+    const int lpos = 32 * wave + (lane & 31);
+    const unsigned pbytes = (unsigned)pstep * 2;   // a slice is at most 2^31 bytes
+    const char *line = (const char *)(fz + (size_t)lbeg * lstep);
+    // first position of the chunk: to load next, loaded, of the frames, and tapped
+    int lc0 = 0, rc0 = 0, dc0 = 0, c0 = 0;
+    int left = lend - lbeg;
     auto load_step = [&]() {
-        const __bf16 *line = fz + (size_t)ll * lstep;
-        const int p0 = lch * PCH + 32 * wave;
-        if (p0 + 32 <= N) {
-            const __bf16 *src = line + (size_t)p0 * pstep;
+        const unsigned off = (unsigned)min(lc0 + lpos, N - 1) * pbytes + 16 * (lane >> 5);
 #pragma unroll
-            for (int kb = 0; kb < KB; ++kb) raw[kb] = *(const v8bf *)(src + loff + kb * 16);
-        } else {
-            const int pos = p0 + (lane & 31);
-            const __bf16 *src = line + (size_t)min(pos, N - 1) * pstep + 8 * (lane >> 5);
-#pragma unroll
-            for (int kb = 0; kb < KB; ++kb) {
-                const v8bf x = *(const v8bf *)(src + kb * 16);
-                raw[kb] = pos < N ? x : v8bf{};
-            }
-        }
-        if (++lch == nch) {
-            lch = 0;
-            ll = min(ll + 1, lend - 1);
+        for (int kb = 0; kb < KB; ++kb) raw[kb] = *(const v8bf *)(line + off + kb * 32);
+        rc0 = lc0;
+        lc0 += PCH;
+        if (lc0 >= N) {
+            lc0 = 0;
+            line += --left > 0 ? 2 * lstep : 0;
         }
     };
     // the frames of one step
     v16f d;
     auto frames = [&]() {
+        if (rc0 + 32 * wave + 32 > N) {
+            asm volatile("");   // a branch: as selects in every step 3 to 5% slower
+            const bool in = rc0 + lpos < N;
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb) raw[kb] = in ? raw[kb] : v8bf{};
+        }
+        c0 = dc0;
+        dc0 = rc0;
         d = v16f{};
 #pragma unroll
         for (int kb = 0; kb < KB; ++kb) {
@@ -243,9 +248,8 @@ __global__ __launch_bounds__(ST, sf_waves(NPP, KB, AS, UB, ST)) void k_project_s
     // angle), the others reading the two zero rows at the end.
     int row[R];
     float frc[R];
-    int ch = 0;
     auto taps = [&](int buf) {
-        if (ch == 0) {   // ray positions on this step's line
+        if (c0 == 0) {   // ray positions on this step's line
 #pragma unroll
             for (int rho = 0; rho < R; ++rho) {
                 const unsigned q = (unsigned)(int)(U[rho] >> 32) + 1u;
@@ -254,8 +258,6 @@ __global__ __launch_bounds__(ST, sf_waves(NPP, KB, AS, UB, ST)) void k_project_s
                 row[rho] = q <= (unsigned)N ? (int)q : 1 << 28;
             }
         }
-        const int c0 = ch * PCH;
-        ch = ch + 1 == nch ? 0 : ch + 1;
         const float *fb = fr + buf * bufsz + j0 * NPP;
 #pragma unroll
         for (int u = 0; u < UT; ++u) {
