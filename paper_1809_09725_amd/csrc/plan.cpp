@@ -460,6 +460,7 @@ static int configure(Plan &p, TableUpload &up)
         C.ngroups = (int)gwalk_sf.size();
         C.BT = std::min(g.Ns, 512 * C.UB);
         C.nbt = (g.Ns + C.BT - 1) / C.BT;
+        // Positions of a line are taken in chunks of half as many as threads.
         // Workgroups of 512 threads and chunks of 256 positions, two per CU,
         // where 1024 threads lack rays: lines and detectors of at most 256, or
         // fewer than four slots of at most 512 bins.  Measured, 1024 against
@@ -477,10 +478,25 @@ static int configure(Plan &p, TableUpload &up)
         // 52 6.55 and 4.62; 1024^2 x 4, 32 of them, K = 64 11.0 and 8.5) or pad the
         // lines with more positions (1213^2 x 4, 5 of them, K = 58 7.25 and 6.14);
         // elsewhere 1024 (1024^2 x 8, 12 of them, K = 64 16.2 and 16.4).
+        const int cols = sf_slots(C.NPP, C.UB, kb) * C.NPP, sums = cols * C.UB;   // frame columns, ray sums
         const auto padded = [&](int pch) { return (g.N + pch - 1) / pch * pch; };
         if ((kb == 3 && (C.NPP <= 20 || g.Ns <= 1024)) ||
-            (kb == 4 && C.UB > 1 && (sf_slots(C.NPP, C.UB, kb) * C.NPP == 32 || padded(256) < padded(512))))
+            (kb == 4 && C.UB > 1 && (cols == 32 || padded(256) < padded(512))))
             C.ST = 512;
+        // Lines of 257..384 positions in one chunk, of 640 or 768 threads, where
+        // 512 would be taken or more than 32 channels: two chunks of 256 are half
+        // padding.  100 classes, 5 slices, 512 threads against 640 or 768: 270^2, 20
+        // half-turns, K = 16 389 and 248 us; 300^2, 600 bins, 24 of them, K = 40 889
+        // and 550; 384^2, 28 of them, K = 60 1.45 and 1.15 ms (1024: 339, 657, 1.24).
+        // Of 385..512 positions above 32 channels: 512 threads where two workgroups
+        // fit a CU by their registers or 1024 would spill, otherwise 1024 (410^2,
+        // 820 bins, 16 half-turns, K = 40: 820 and 588 us; where they fit, 8 of
+        // them: 493 and 556).
+        if (g.N > 256 && g.N <= 384 && (kb >= 3 || C.ST == 512))
+            C.ST = g.N <= 320 ? 640 : 768;
+        else if (g.N > 384 && g.N <= 512 && kb >= 3)
+            C.ST = (kb == 3 ? sums <= 40 && (cols < 32 || C.NPP > 8 || C.UB > 1) : sums <= 24) ||
+                   (kb == 4 && (C.NPP == 32 || sums == 64)) ? 512 : 1024;
         C.PCH = std::min(C.ST / 2, (g.N + 31) / 32 * 32);
         C.KP = (g.K + 15) / 16 * 16;
         // an odd number of 16-byte groups per row: 16 consecutive positions

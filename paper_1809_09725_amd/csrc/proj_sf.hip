@@ -96,7 +96,7 @@ __device__ inline int sf_bin(int tid, int a, const unsigned char *__restrict__ l
 // spill tens of registers (256^2 x 16, 16 half-turns, K = 64: 1.13 -> 1.85 ms).
 constexpr int sf_waves(int npp, int kb, int as, int ub, int st)
 {
-    return st == 512 && kb == 3 && as * ub == 2 && npp <= 20 ? 4 : st / 256;
+    return st == 512 && kb == 3 && as * ub == 2 && npp <= 20 ? 4 : (st + 255) / 256;
 }
 template <int NPP, int KB, int AS, int UB, int ST>
 __global__ __launch_bounds__(ST, sf_waves(NPP, KB, AS, UB, ST)) void k_project_sf(
@@ -487,6 +487,10 @@ static int launch_sf_t(const Plan &p, const SfEpi &E, hipStream_t s, unsigned nb
 {
     if constexpr (UB == 1 || KB >= 3) {   // as the plan chooses ST
         if (p.sf.ST == 512) return launch_sf_s<NPP, KB, AS, UB, 512>(p, E, s, nb);
+    }
+    if constexpr ((UB == 1 && NPP > 8) || KB >= 3) {
+        if (p.sf.ST == 640) return launch_sf_s<NPP, KB, AS, UB, 640>(p, E, s, nb);
+        if (p.sf.ST == 768) return launch_sf_s<NPP, KB, AS, UB, 768>(p, E, s, nb);
     }
     return launch_sf_s<NPP, KB, AS, UB, 1024>(p, E, s, nb);
 }

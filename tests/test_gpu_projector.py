@@ -218,7 +218,7 @@ def test_synthesise_first_edges(G):
     assert (np.abs(got - want) <= (2.0 ** -17 + 4 * G.N * 2.0 ** -24) * S + G.N ** 2 * 2.0 ** -31 * F.max()).all()
 
 
-SF_WIDE = [   # 33..64 channels over more than 512 bins: 512 threads (the first six), 1024 (the last three)
+SF_WIDE = [   # 33..64 channels over more than 512 bins
     geom(311, 1, 561, 20, 2, 39), geom(100, 1, 1300, 12, 3, 40), geom(70, 1, 1400, 4, 3, 48), geom(520, 1, 600, 13, 3, 52),
     geom(130, 1, 900, 32, 2, 64), geom(600, 1, 600, 5, 3, 58),
     geom(120, 1, 1400, 28, 2, 44), geom(300, 1, 700, 5, 4, 58), geom(257, 1, 1100, 12, 2, 64),
@@ -228,4 +228,17 @@ SF_WIDE = [   # 33..64 channels over more than 512 bins: 512 threads (the first 
 @pytest.mark.parametrize("G", SF_WIDE, ids=lambda G: f"N{G.N}s{G.Ns}p{G.Npi}k{G.K}")
 def test_synthesise_first_many_channels(G):
     """The thread counts above 32 channels, at the same bar."""
+    test_synthesise_first_edges(G)
+
+
+SF_CHUNKS = [   # one chunk of 640 threads, of 768 (and three bins of them), two of 1024; ragged ends of lines in each
+    geom(257, 1, 257, 9, 4, 16), geom(320, 1, 320, 20, 3, 24), geom(321, 2, 330, 28, 2, 7), geom(384, 1, 384, 16, 3, 32),
+    geom(290, 1, 700, 28, 3, 33), geom(300, 2, 290, 16, 3, 60), geom(318, 1, 1100, 8, 3, 40), geom(383, 1, 500, 4, 5, 64),
+    geom(350, 1, 1500, 4, 4, 48), geom(340, 1, 780, 32, 2, 50), geom(385, 1, 600, 12, 3, 40), geom(410, 1, 410, 8, 3, 64),
+]
+
+
+@pytest.mark.parametrize("G", SF_CHUNKS, ids=lambda G: f"N{G.N}s{G.Ns}p{G.Npi}k{G.K}")
+def test_synthesise_first_line_chunks(G):
+    """Lines of 257 to 512 positions, at the same bar."""
     test_synthesise_first_edges(G)
