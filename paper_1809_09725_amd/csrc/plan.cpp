@@ -405,7 +405,7 @@ static int configure(Plan &p, TableUpload &up)
     // in position; ordering the 64 rays by (r / c) modulo that and dealing
     // them out in turn spreads each such set evenly.  The precision form's
     // rows (an odd number of 16-byte units) take the order of NQ = 1.
-    std::vector<uint8_t> lanes((size_t)3 * n0 * 64, 0);
+    std::vector<uint8_t> lanes(p.adjoint_only ? 0 : (size_t)3 * n0 * 64, 0);
     static const int set_quads[3][8] = {   // lane quads of the sets, in order, of half a wave
         {0, 3, 5, 6, 1, 2, 4, 7}, {0, 3, 5, 6, 1, 2, 4, 7}, {0, 1, 2, 3, 4, 5, 6, 7}};
     for (int v = 0; v < 3 && !p.adjoint_only; ++v) {
@@ -555,14 +555,16 @@ static int create(const rt_geom *geom, rt_form form, rt_prec prec, const double 
     int rc = configure(p, up);
     if (rc) return rc;
     if (!adjoint_only) p.ray = ray_cfg(p);
-    std::vector<float> phi32(p.T.phi.begin(), p.T.phi.end()), S32(p.T.S.begin(), p.T.S.end());
     const size_t Kp = (size_t)(geom->K + 3) / 4 * 4;
     std::vector<float> phip((size_t)geom->Ntheta * Kp, 0.f);
     for (int i = 0; i < geom->Ntheta; ++i)
-        std::copy_n(phi32.begin() + (size_t)i * geom->K, geom->K, phip.begin() + (size_t)i * Kp);
-    up.add(&p.d_phi, phi32);
+        std::copy_n(p.T.phi.begin() + (size_t)i * geom->K, geom->K, phip.begin() + (size_t)i * Kp);
+    up.host.reserve(up.host.size() + 2 * phip.size() * sizeof(float) + ((size_t)1 << 16));
     up.add(&p.d_phip, phip);
-    up.add(&p.d_S, S32);
+    if (!adjoint_only) {
+        up.add(&p.d_phi, std::vector<float>(p.T.phi.begin(), p.T.phi.end()));
+        up.add(&p.d_S, std::vector<float>(p.T.S.begin(), p.T.S.end()));
+    }
     up.add(&p.d_ccos, p.T.ccos);
     up.add(&p.d_csin, p.T.csin);
     std::vector<float> invc(p.n0);
