@@ -89,7 +89,7 @@ struct LineSplit {
 // of at most 256 positions, of workgroups of 4 ray blocks (several per CU).
 // Measured: one 512^2 slice of 16 channels over 180 classes, 46 full
 // workgroups, 462 us in one part, 119 in five.
-static LineSplit line_split(const rt_geom &g, int nz, bool whole_blocks = false)
+static LineSplit line_split(const rt_geom &g, int nz, bool packed)
 {
     LineSplit best;
     if (nz < 1) return best;
@@ -97,7 +97,7 @@ static LineSplit line_split(const rt_geom &g, int nz, bool whole_blocks = false)
     const long K4 = (g.K + 3) / 4;
     const int NQ = quads_per_row(g, nz);
     const long ncg = (nz * K4 + NQ - 1) / NQ;
-    const long per = whole_blocks ? (g.Ns + 63) / 64 * 64 : g.Ns;
+    const long per = packed ? g.Ns : (g.Ns + 63) / 64 * 64;
     const long half = ((n0 + 1) / 2 * per + 63) / 64;   // ray blocks of a walk, about
     const bool fusable = g.N <= 512 && K4 <= NQ && NQ % K4 == 0;
     double cost = 1e300;
@@ -131,20 +131,29 @@ static LineSplit line_split(const rt_geom &g, int nz, bool whole_blocks = false)
 // the rounds that they take (128^2 x 40, 8 channels, 200 classes, 1.2 rounds:
 // 239 and 176).  In fuller rounds small ones lose there: 70^2 x 120, 8
 // channels, 90 classes: 88 and 122.
-static bool small_workgroups(const rt_geom &g, int nz, int ngroups)
+static bool small_workgroups(const rt_geom &g, int nz, bool packed, int ngroups)
 {
-    const LineSplit L = line_split(g, nz);
+    const LineSplit L = line_split(g, nz, packed);
     if (L.small || L.NLP > 1 || nz < 1) return L.small;
     const int NQ = quads_per_row(g, nz);
     const long W = ((long)nz * ((g.K + 3) / 4) + NQ - 1) / NQ * ngroups, slots = (W + 255) / 256 * 256;
     return g.N <= 64 || (g.N <= 128 && W * 10 < slots * 7);
 }
 
-// Line parts that a plan's scratch has room for: also the split that fits with
-// whole blocks of bins, more parts at times, which the precision form may use.
+// Whether ray blocks may run on over classes (the plan takes what it estimates
+// faster).  Fewer than four channels, whose staging the estimate does not
+// cover, keep blocks of one class, and so do lines of more than 512 positions
+// (650^2 x 3, 1000 bins: 1083 us packed, 1079 not).
+static bool may_pack(const rt_geom &g)
+{
+    return g.Ns % 64 && g.K >= 4 && g.N <= 512;
+}
+
+// Line parts that a plan's scratch has room for, whichever way its ray blocks
+// are formed.
 static int line_parts_room(const rt_geom &g, int nz)
 {
-    return std::max(line_split(g, nz).NLP, line_split(g, nz, true).NLP);
+    return std::max(line_split(g, nz, false).NLP, may_pack(g) ? line_split(g, nz, true).NLP : 1);
 }
 
 size_t adjoint_scratch_bytes(const rt_geom &g)
@@ -198,16 +207,18 @@ static void ray_window(int N, int Ns, const RayDir *d, int n, int b0, int b1, Ra
 }
 
 // Ray groups of at most `blocks` blocks of 64 rays with windows of at most
-// wmax positions.  A group is a tile of bins (blocks of 64, the last one up to
-// the detector's end) over neighbouring classes; more classes and fewer bins
-// (or the reverse) widen the window by their fan-out (their spacing).  The
-// tile width is the power of two that costs least: per line the LDS cycles of
-// the taps and of the window's stores and a share of the barrier, as
-// k_project's comment has them.  At 512^2 over 180 classes two blocks of 16
-// classes: windows of 247 positions on average; whole lines (eight blocks of
-// four classes) took 12.8 ms against 9.85 there (128 slices of 16 channels)
-// and 8.45 against 5.76 at 1024^2 x 8.
-static std::vector<RayGroup> ray_groups(const rt_geom &g, const std::vector<RayDir> (&lists)[3], int blocks, int wmax)
+// wmax positions, the blocks of one class each or packed over the classes; and
+// the cost of the largest group and of all.  A group is a tile of bins (blocks
+// of 64, the last one up to the detector's end) over neighbouring classes;
+// more classes and fewer bins (or the reverse) widen the window by their fan-
+// out (their spacing).  The tile width is the power of two that costs least:
+// per line the LDS cycles of the taps and of the window's stores and a share
+// of the barrier, as k_project's comment has them.  At 512^2 over 180 classes
+// two blocks of 16 classes: windows of 247 positions on average; whole lines
+// (eight blocks of four classes) took 12.8 ms against 9.85 there (128 slices
+// of 16 channels) and 8.45 against 5.76 at 1024^2 x 8.
+static std::vector<RayGroup> ray_groups(const rt_geom &g, const std::vector<RayDir> (&lists)[3], bool packed,
+                                        int blocks, int wmax, double &worst, double &total)
 {
     const int nbb = (g.Ns + 63) / 64, N = g.N, Ns = g.Ns;
     std::vector<RayGroup> best;
@@ -215,7 +226,7 @@ static std::vector<RayGroup> ray_groups(const rt_geom &g, const std::vector<RayD
     for (int tile = 1; tile <= blocks; tile *= 2) {
         const int nt = (nbb + tile - 1) / tile;   // tiles of nearly equal width
         std::vector<RayGroup> v;
-        double cost = 0.0;
+        double cost = 0.0, most = 0.0;
         bool fits = true;
         int cls0 = 0;
         for (int s = 0; s < 3; ++s) {
@@ -228,32 +239,27 @@ static std::vector<RayGroup> ray_groups(const rt_geom &g, const std::vector<RayD
                 G.nb = std::min(64 * bbt, Ns - G.b0);
                 const int b1 = G.b0 + G.nb - 1;
                 for (int i = 0; i < (int)L.size(); i += G.ncls) {
-                    // classes of whole blocks or, at the detector's end, as many
-                    // as fit the rays: what costs less per ray
-                    RayGroup best_g{};
-                    double best_c = 1e300;
-                    for (int ncls : {blocks / bbt, blocks * 64 / G.nb}) {
-                        G.cls0 = cls0 + i;
-                        G.ncls = std::min(ncls, (int)L.size() - i);
-                        ray_window(N, Ns, L.data() + i, G.ncls, G.b0, b1, G);
-                        while (G.W > wmax && G.ncls > 1) ray_window(N, Ns, L.data() + i, --G.ncls, G.b0, b1, G);
-                        if (G.W > wmax) fits = false;
-                        const int lines = std::max(1, wmax / G.W >= 4 ? 4 : wmax / G.W >= 2 ? 2 : 1);
-                        const double c = (G.ncls * G.nb + 63) / 64 * 40.0 + G.W * 0.5 + 500.0 / lines;
-                        if (c / G.ncls < best_c) {
-                            best_c = c / G.ncls;
-                            best_g = G;
-                        }
-                    }
-                    G = best_g;
-                    cost += best_c * G.ncls;
+                    G.stride = packed ? G.nb : 64 * bbt;
+                    G.cls0 = cls0 + i;
+                    G.ncls = std::min(blocks * 64 / G.stride, (int)L.size() - i);
+                    ray_window(N, Ns, L.data() + i, G.ncls, G.b0, b1, G);
+                    while (G.W > wmax && G.ncls > 1) ray_window(N, Ns, L.data() + i, --G.ncls, G.b0, b1, G);
+                    if (G.W > wmax) fits = false;
+                    const int lines = std::max(1, wmax / G.W >= 4 ? 4 : wmax / G.W >= 2 ? 2 : 1);
+                    // a block of two classes costs a little more: its lanes are in the
+                    // order of the first alone
+                    const int nblk = (G.ncls * G.stride + 63) / 64, mixed = G.stride % 64 ? std::min(G.ncls - 1, nblk) : 0;
+                    const double c = nblk * 40.0 + mixed * 3.0 + G.W * 0.5 + 500.0 / lines;
+                    cost += c;
+                    most = std::max(most, c);
                     v.push_back(G);
                 }
             }
             cls0 += (int)L.size();
         }
         if (fits && cost < best_cost) {
-            best_cost = cost;
+            best_cost = total = cost;
+            worst = most;
             best = v;
         }
         if (tile >= nbb) break;
@@ -264,7 +270,7 @@ static std::vector<RayGroup> ray_groups(const rt_geom &g, const std::vector<RayD
 RayCfg ray_cfg(const Plan &p)
 {
     const rt_geom &g = p.g;
-    const LineSplit L = line_split(g, p.nz_ref);
+    const LineSplit L = line_split(g, p.nz_ref, p.packed);
     RayCfg R;
     R.K4 = (g.K + 3) / 4;
     const int tq = g.Nz * R.K4;   // channel quads of all slices
@@ -272,7 +278,7 @@ RayCfg ray_cfg(const Plan &p)
     R.ncg = (tq + R.NQ - 1) / R.NQ;
     R.tl = g.N > 512;
     R.NLP = L.NLP;
-    const bool small = small_workgroups(g, p.nz_ref, p.ngroups);
+    const bool small = small_workgroups(g, p.nz_ref, p.packed, p.ngroups);
     R.nth = small ? RAY_NTH_SMALL : RAY_NTH;
     R.group0 = small ? p.ngroups : 0;
     R.ngroups = small ? (int)p.groups.size() - p.ngroups : p.ngroups;
@@ -387,13 +393,47 @@ static int configure(Plan &p, TableUpload &up)
     }
     std::vector<int> wcls;
     for (const std::vector<int> &L : by_dir) wcls.insert(wcls.end(), L.begin(), L.end());
-    if (!p.adjoint_only) p.groups = ray_groups(g, lists, RAY_BLOCKS, RAY_WMAX);
-    p.ngroups = (int)p.groups.size();
-    if (!p.adjoint_only && !p.ngroups) return fail(RT_E_SHAPE, "no ray groups of the projector for N=%d Ns=%d", g.N, g.Ns);
-    if (!p.adjoint_only && (small_workgroups(g, p.nz_ref, p.ngroups) || small_workgroups(g, 1, p.ngroups))) {
-        const std::vector<RayGroup> v = ray_groups(g, lists, RAY_BLOCKS_SMALL, RAY_WMAX_SMALL);
-        p.groups.insert(p.groups.end(), v.begin(), v.end());
+    // Ray blocks of one class, or packed over the classes: the set of groups
+    // whose launch takes less.  The workgroups are alike, so up to six rounds of
+    // them count as whole ones, each of the largest group and of 30 us of setup
+    // and epilogue (3 us where the workgroups are small).  100^2 x 40, 16
+    // channels, 200 classes, 78% of the lanes in use: 600 workgroups of one
+    // class, three rounds, 305 us, 480 packed in two 220; 390^2 x 13, 32
+    // channels, 13 classes (one round either way) 217 and 243.
+    double best_t = 1e300;
+    for (int packed = 0; packed < (may_pack(g) ? 2 : 1) && !p.adjoint_only; ++packed) {
+        double worst = 0.0, total = 0.0;
+        std::vector<RayGroup> v = ray_groups(g, lists, packed, RAY_BLOCKS, RAY_WMAX, worst, total);
+        const int ngroups = (int)v.size();
+        if (!ngroups) continue;
+        const int NQ = quads_per_row(g, p.nz_ref);
+        const long ncg = ((long)p.nz_ref * ((g.K + 3) / 4) + NQ - 1) / NQ;
+        const LineSplit L = line_split(g, p.nz_ref, packed);
+        const bool small = small_workgroups(g, p.nz_ref, packed, ngroups);
+        if (small || small_workgroups(g, 1, packed, ngroups)) {
+            double w = 0.0, t = 0.0;
+            const std::vector<RayGroup> vs = ray_groups(g, lists, packed, RAY_BLOCKS_SMALL, RAY_WMAX_SMALL, w, t);
+            v.insert(v.end(), vs.begin(), vs.end());
+            if (small) {
+                worst = w;
+                total = t;
+            }
+        }
+        const int ngr = small ? (int)v.size() - ngroups : ngroups;
+        const double W = (double)ncg * ngr * L.NLP;
+        const double occ = small ? (NQ == 4 ? 2 : 4) : 1, share = std::min(occ, std::max(1.0, W / 256));
+        const double rounds = W / (256 * occ), setup = small ? 3.0 : 30.0, us = (double)g.N / L.NLP / 2400;
+        const double t = share * (rounds <= 6 ? std::ceil(rounds) * (worst * us + setup)
+                                              : total / ngr * (rounds + 0.5) * us + rounds * setup) +
+                         (L.NLP > 1 ? 8.0 + 2.0e-6 * L.NLP * n0 * p.nz_ref * g.Ns * ((g.K + 3) / 4 * 16) : 0.0);
+        if (t < best_t) {
+            best_t = t;
+            p.packed = packed;
+            p.groups = v;
+            p.ngroups = ngroups;
+        }
     }
+    if (!p.adjoint_only && !p.ngroups) return fail(RT_E_SHAPE, "no ray groups of the projector for N=%d Ns=%d", g.N, g.Ns);
 
     // Lane order of the forward waves.  A wave's 64 rays are 64 consecutive
     // bins of one class, or of neighbours in the order of the first; their

@@ -70,9 +70,8 @@ __device__ inline float dot4(float4 w, v4 x)
 // and K = 8 two, and a position of a staged line is NQ * 16 bytes in LDS.
 // Rays.  A workgroup takes one RayGroup: a tile of bins of neighbouring
 // classes of one walk direction, as blocks of 64 rays, PPT blocks per wave.
-// Where the detector is no multiple of 64 a block runs on into the next class
-// (with a block per class and 64 bins, 100 bins left 22% of the lanes idle:
-// 100^2 x 40, 8 channels, 200 classes 205 us, packed 115).  Lines no
+// Where the detector is no multiple of 64 a block may run on into the next
+// class (as the plan finds faster).  Lines no
 // ray of a block crosses are skipped (a wave-uniform interval per block): 9%
 // of the tap work at Ns = N, more where the detector is wider than the slice.
 // Lines.  Only the window of W positions that the group's rays reach on a
@@ -156,7 +155,7 @@ __global__ __launch_bounds__(NTH) void k_project(
     long long U[PPT], S[PPT];
     float invc[PPT], sfr[PPT];
     int cl[PPT], bin[PPT], jb[PPT], je[PPT];   // class (-1: none) and bin of a lane, lines [jb, je) of the block
-    const int nrays = G.ncls * G.nb;
+    const int nrays = G.ncls * G.stride;
 #pragma unroll
     for (int j = 0; j < PPT; ++j) {
         // block n: rays 64 n .. of the list of classes times bins, in the lane
@@ -164,10 +163,11 @@ __global__ __launch_bounds__(NTH) void k_project(
         const int first = (j * NW + wave) * 64;
         int a = -1, b = Ns;
         if (first < nrays) {
-            const int ray = first + (int)rlane[wcls[G.cls0 + first / G.nb] * 64 + lane], c = ray / G.nb;
-            if (ray < nrays) {
+            const int ray = first + (int)rlane[wcls[G.cls0 + first / G.stride] * 64 + lane], c = ray / G.stride;
+            const int off = ray - c * G.stride;
+            if (ray < nrays && off < G.nb) {
                 a = wcls[G.cls0 + c];
-                b = G.b0 + ray - c * G.nb;
+                b = G.b0 + off;
             }
         }
         cl[j] = a;
