@@ -243,9 +243,9 @@ int rt_fbp_filter(const rt_plan *plan, const float *g, float *q, void *stream);
  *   sum_k B[m][k] f_k = F_m,  B[m][k] = mean of Phi[i][k] over half-turn m,
  * for the plan's basis (FP64 pseudo-inverse on the host; a rank-deficient B
  * is RT_E_ARG).  Device g [Ntheta][Nz][Ns], f_out [Nz][N][N][K].  Needs
- * Npi <= 64.  Allocates (Ntheta Nz Ns + 2 Nz N^2 Npi + Ntheta0 Nz Ns Npi)
- * floats of temporaries for the call and blocks on `stream` before it
- * returns. */
+ * Npi <= 64.  With Npi' = Npi rounded up to 4, allocates about (Ntheta Nz Ns +
+ * Nz N^2 Npi + Ntheta0 Nz Ns Npi' + Ntheta Npi') floats of temporaries for the
+ * call and blocks on `stream` before it returns. */
 int rt_fbp(const rt_plan *plan, const float *g, float *f_out, void *stream);
 
 /* ---- resumable job/step form of solve, for serving ---------------------

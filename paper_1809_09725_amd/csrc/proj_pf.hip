@@ -85,12 +85,14 @@ __device__ inline float dot4(float4 w, v4 x)
 // workgroup walks one of NLP parts of the lines and stores partial sums
 // that k_contract adds in part order.
 //
-// What bounds it: the tap reads of LDS, 8 bytes per channel sample, 5.1 cycles
-// each where 4.3 would be free of conflicts, with the FMAs close behind; at
-// 512^2 x 128, K = 16, 180 classes 9.85 ms, of which 8.0 remain without the
+// What bounds it: no unit alone.  At 512^2 x 128, K = 16, 180 classes (9.9 ms)
+// LDS is active 58% of the time, with the tap reads at 8 bytes per channel
+// sample and 5.1 cycles each where 4.3 would be free of conflicts, and the
+// vector units issue half of it; the 16 waves of a CU, one workgroup, meet at
+// each stage's barrier and leave both idle there.  8.0 ms remain without the
 // staging and its barriers.  With whole lines staged for all bins of four
-// classes, rows padded to 80 bytes and lanes ordered modulo 16 it was 13.1 ms
-// there, and 8.4 ms against 5.4 at 1024^2 x 8 over 300 classes, where whole
+// classes, rows padded to 80 bytes and lanes ordered modulo 16 it was 12.9 ms
+// there, and 8.4 ms against 5.6 at 1024^2 x 8 over 300 classes, where whole
 // lines allowed 8 channels at a time.
 //
 // LDS.  A ds_read_b128 is served in four groups of 16 lanes ({0-3, 12-15,
@@ -509,8 +511,8 @@ __global__ __launch_bounds__(NTH) void k_project(
 // NLP partial sums once, keeps the KQ channel quads in registers and takes
 // every half-turn from them (the Phi rows are uniform over the workgroup).  The
 // order of the FP64 partials is fixed by the grid.  Bound by HBM: P, g and h1
-// once each; 1024^2 x 8, 300 classes, 12 half-turns with the prox: 437 us with
-// a thread per (half-turn, slice, bin) reading P each time, 113 as it is.
+// once each; 1024^2 x 8, 300 classes, 12 half-turns with the prox: 466 us with
+// a thread per (half-turn, slice, bin) reading P each time, 116 as it is.
 template <int KQ>
 __global__ __launch_bounds__(NT) void k_contract(
     const float *__restrict__ P, const float *__restrict__ phi, float *__restrict__ out,

@@ -66,9 +66,9 @@ __device__ inline int sf_bin(int tid, int a, const unsigned char *__restrict__ l
 // E.out + lp * E.pstride for k_sf_finish).  Consecutive workgroups take the
 // class groups of one part, so the part's BF16 lines are read while they are
 // still cached.  A thread owns the rays (slot, bin) of its half of the A slots
-// (of all of them with one slot or 512 threads) at UT bins each.  NPP: frame columns
-// per class (Npi rounded up to 4, the padding columns are zero); KB: MFMA
-// k-steps of 16 channels.
+// (of all of them with one slot or fewer than 1024 threads) at UT bins each.
+// NPP: frame columns per class (Npi rounded up to 4, the padding columns are
+// zero); KB: MFMA k-steps of 16 channels.
 //
 // The frames F[c][pos] = sum_k Phi[i(c)][k] f_k(pos) of a chunk of PCH
 // positions are one v_mfma_f32_32x32x16_bf16 product per 32-position tile,
@@ -79,21 +79,21 @@ __device__ inline int sf_bin(int tid, int a, const unsigned char *__restrict__ l
 //
 // What bounds it: per line of 1024 positions and 4 classes of 8 half-turns the
 // LDS takes about 2100 cycles (1024 for the frames' stores, 1100 for the
-// taps' reads), the vector units 1300 and the matrix cores 1024, of 5300 in
+// taps' reads), the vector units 1300 and the matrix cores 1024, of 5200 in
 // all; the operand loads (128-byte lines, of which a column walk uses half)
 // are hidden.  Two frame buffers let one barrier per step do, with the
 // products of the next step running under the taps of this one; 16 waves of
 // half the rays each (ST = 1024; ST = 512 where these would lack rays: two
-// workgroups per CU) keep more of the LDS reads in flight than 8.  Measured,
-// 1024^2 x 8, 256 classes, 8 half-turns, K = 32: 7.25 ms with one buffer and
-// two barriers per chunk, 5.58 with two buffers and 8 waves, 4.66 as it is;
-// 512^2 x 16, 180 classes, K = 16: 2.22 -> 1.50 ms; 2048^2 x 2, K = 32:
-// 12.7 -> 7.4 ms.
+// workgroups per CU; 640 and 768 where a line then is one chunk) keep more of the
+// LDS reads in flight than 8.  Measured, 1024^2 x 8, 256 classes, 8 half-turns,
+// K = 32: 7.4 ms with one buffer and two barriers per chunk, 5.6 with two
+// buffers and 8 waves, 4.5 as it is; 512^2 x 16, 180 classes, K = 16: 2.24 ->
+// 1.47 ms; 2048^2 x 2, 64 classes, 12 half-turns, K = 32: 3.42 -> 2.20 ms.
 // Waves per SIMD asked for: with 33..48 channels and two bins or slots of up
 // to 20 half-turns a thread, 512 threads are held to 128 registers (a few more
-// otherwise), so that two workgroups do fit a CU: 512^2 x
-// 16, 16 half-turns, K = 48: 5.40 -> 4.67 ms.  More sums, or more channels, would
-// spill tens of registers (256^2 x 16, 16 half-turns, K = 64: 1.13 -> 1.85 ms).
+// otherwise), so that two workgroups do fit a CU: 512^2 x 16, 16 half-turns, K =
+// 48: 5.40 -> 4.67 ms.  More sums, or more channels, would spill tens of
+// registers (256^2 x 16, 16 half-turns, K = 64: 1.13 -> 1.85 ms).
 constexpr int sf_waves(int npp, int kb, int as, int ub, int st)
 {
     return st == 512 && kb == 3 && as * ub == 2 && npp <= 20 ? 4 : (st + 255) / 256;

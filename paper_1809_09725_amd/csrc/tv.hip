@@ -23,8 +23,8 @@ namespace {
 // Consecutive slices per work item of the gradient and divergence (the
 // z-neighbours are then still at hand): 4, fewer where that leaves less than 8
 // workgroups of NT per CU.  At 256^2 x 8 and 8 frames one slice per item,
-// with the loads of four frames in flight, took the gradient from 78 to 28 us and
-// the divergence from 56 to 34.
+// with the loads of four frames in flight, took the gradient from 81 to 31 us and
+// the divergence from 58 to 35.
 int z_chunk(size_t plane, int nz)
 {
     for (int zc = 4; zc > 1; zc /= 2)
@@ -183,7 +183,7 @@ __global__ __launch_bounds__(NT) void k_frames(const float *__restrict__ f,
 // a long chain of loads.  The loads of UF frames are issued together: they are
 // unconditional, from clamped addresses, and the differences at the last index
 // of an axis are selected to zero.  Measured with the shrink: 256^2 x 8, 8
-// frames 80 -> 33 us; 512^2 x 32, 10 frames 606 -> 587 us (5.2 TB/s).
+// frames 81 -> 31 us; 512^2 x 32, 10 frames 614 -> 589 us (5.2 TB/s).
 // h2 of a voxel is read and written once here and next read after the
 // back-projection has streamed through L2: streaming (non-temporal) accesses
 // leave L2 to the frames' neighbour reads (STREAM, for planes of a multiple of
