@@ -49,8 +49,9 @@ struct Tables {
 // of the classes [cls0, cls0 + ncls) of the class list, which share one walk
 // direction (0: rows, |cos| >= |sin|; 1: columns) and neighbour each other in
 // angle; a wave's block of 64 is 64 rays of the list of classes times `stride`
-// bins: nb (blocks then run on into the next class) or nb rounded up to 64.  On line l their taps lie in the W
-// positions from floor(wl0 + l sw) on (32.32 fixed point).
+// bins: nb (blocks then run on into the next class) or nb rounded up to 64.  On
+// line l their taps lie in the W positions from floor(wl0 + l sw) on (32.32
+// fixed point).
 struct RayGroup {
     int walk, cls0, ncls, b0, nb, stride, W;
     long long wl0, sw;
@@ -107,7 +108,6 @@ struct Plan {
     Tables T;
     int nz_ref = 0;       // slices the order of the ray sums is planned for (see ray_cfg)
     bool adjoint_only = false;
-    bool packed = false;   // the plain projector's ray blocks run on over classes
     std::vector<RayGroup> groups;   // full workgroups, then small ones
     int ngroups = 0;      // full workgroups
     RayCfg ray;           // of this plan's slices (ray_cfg)

@@ -89,16 +89,15 @@ struct LineSplit {
 // of at most 256 positions, of workgroups of 4 ray blocks (several per CU).
 // Measured: one 512^2 slice of 16 channels over 180 classes, 46 full
 // workgroups, 462 us in one part, 119 in five.
-static LineSplit line_split(const rt_geom &g, int nz, bool packed)
+static LineSplit line_split(const rt_geom &g, int nz)
 {
     LineSplit best;
     if (nz < 1) return best;
     const long n0 = g.Ntheta / g.Npi;
-    const long K4 = (g.K + 3) / 4;
+    const long K4 = (g.K + 3) / 4, nbb = (g.Ns + 63) / 64;
     const int NQ = quads_per_row(g, nz);
     const long ncg = (nz * K4 + NQ - 1) / NQ;
-    const long per = packed ? g.Ns : (g.Ns + 63) / 64 * 64;
-    const long half = ((n0 + 1) / 2 * per + 63) / 64;   // ray blocks of a walk, about
+    const long half = (n0 + 1) / 2 * nbb;   // ray blocks of a walk, about
     const bool fusable = g.N <= 512 && K4 <= NQ && NQ % K4 == 0;
     double cost = 1e300;
     for (int small = 0; small < (g.N <= 256 ? 2 : 1); ++small) {
@@ -131,29 +130,24 @@ static LineSplit line_split(const rt_geom &g, int nz, bool packed)
 // the rounds that they take (128^2 x 40, 8 channels, 200 classes, 1.2 rounds:
 // 239 and 176).  In fuller rounds small ones lose there: 70^2 x 120, 8
 // channels, 90 classes: 88 and 122.
-static bool small_workgroups(const rt_geom &g, int nz, bool packed, int ngroups)
+static bool small_workgroups(const rt_geom &g, int nz, int ngroups)
 {
-    const LineSplit L = line_split(g, nz, packed);
+    const LineSplit L = line_split(g, nz);
     if (L.small || L.NLP > 1 || nz < 1) return L.small;
     const int NQ = quads_per_row(g, nz);
     const long W = ((long)nz * ((g.K + 3) / 4) + NQ - 1) / NQ * ngroups, slots = (W + 255) / 256 * 256;
     return g.N <= 64 || (g.N <= 128 && W * 10 < slots * 7);
 }
 
-// Whether ray blocks may run on over classes (the plan takes what it estimates
-// faster).  Fewer than four channels, whose staging the estimate does not
-// cover, keep blocks of one class, and so do lines of more than 512 positions
-// (650^2 x 3, 1000 bins: 1083 us packed, 1079 not).
-static bool may_pack(const rt_geom &g)
+// Whether the ray blocks of nz slices may run on over classes (the plan takes
+// what it estimates faster).  Line parts already even out launches of few
+// workgroups (339^2 x 2, 11 channels, 147 classes, four parts: 125 us, packed
+// 134; 196^2, 25 channels, 122 classes, six parts: 83 and 97); the staging of
+// fewer than four channels is not in the estimate; and lines of more than 512
+// positions gained nothing (650^2 x 3, 1000 bins: 1079 and 1083 us).
+static bool may_pack(const rt_geom &g, int nz)
 {
-    return g.Ns % 64 && g.K >= 4 && g.N <= 512;
-}
-
-// Line parts that a plan's scratch has room for, whichever way its ray blocks
-// are formed.
-static int line_parts_room(const rt_geom &g, int nz)
-{
-    return std::max(line_split(g, nz, false).NLP, may_pack(g) ? line_split(g, nz, true).NLP : 1);
+    return g.Ns % 64 && g.K >= 4 && g.N <= 512 && line_split(g, nz).NLP == 1;
 }
 
 size_t adjoint_scratch_bytes(const rt_geom &g)
@@ -165,8 +159,8 @@ size_t plan_scratch_bytes(const rt_geom &g, int nz_ref)
 {
     const size_t n0 = (size_t)(g.Ntheta / g.Npi), Kp = (size_t)(g.K + 3) / 4 * 4;
     // partial ray sums of the whole volume, or of the one slice of the power iteration
-    const size_t slices = std::max((size_t)g.Nz * line_parts_room(g, nz_ref),
-                                   g.Nz > 0 ? (size_t)line_parts_room(g, 1) : 0);
+    const size_t slices = std::max((size_t)g.Nz * line_split(g, nz_ref).NLP,
+                                   g.Nz > 0 ? (size_t)line_split(g, 1).NLP : 0);
     return n0 * slices * g.Ns * Kp * sizeof(float);
 }
 
@@ -270,7 +264,7 @@ static std::vector<RayGroup> ray_groups(const rt_geom &g, const std::vector<RayD
 RayCfg ray_cfg(const Plan &p)
 {
     const rt_geom &g = p.g;
-    const LineSplit L = line_split(g, p.nz_ref, p.packed);
+    const LineSplit L = line_split(g, p.nz_ref);
     RayCfg R;
     R.K4 = (g.K + 3) / 4;
     const int tq = g.Nz * R.K4;   // channel quads of all slices
@@ -278,7 +272,7 @@ RayCfg ray_cfg(const Plan &p)
     R.ncg = (tq + R.NQ - 1) / R.NQ;
     R.tl = g.N > 512;
     R.NLP = L.NLP;
-    const bool small = small_workgroups(g, p.nz_ref, p.packed, p.ngroups);
+    const bool small = small_workgroups(g, p.nz_ref, p.ngroups);
     R.nth = small ? RAY_NTH_SMALL : RAY_NTH;
     R.group0 = small ? p.ngroups : 0;
     R.ngroups = small ? (int)p.groups.size() - p.ngroups : p.ngroups;
@@ -398,19 +392,18 @@ static int configure(Plan &p, TableUpload &up)
     // them count as whole ones, each of the largest group and of 30 us of setup
     // and epilogue (3 us where the workgroups are small).  100^2 x 40, 16
     // channels, 200 classes, 78% of the lanes in use: 600 workgroups of one
-    // class, three rounds, 305 us, 480 packed in two 220; 390^2 x 13, 32
-    // channels, 13 classes (one round either way) 217 and 243.
+    // class, three rounds, 305 us, 480 packed in two 213; 198^2 x 31, 305 bins,
+    // 32 channels, 37 classes (two rounds either way) 340 and 389 us.
     double best_t = 1e300;
-    for (int packed = 0; packed < (may_pack(g) ? 2 : 1) && !p.adjoint_only; ++packed) {
+    for (int packed = 0; packed < (may_pack(g, p.nz_ref) ? 2 : 1) && !p.adjoint_only; ++packed) {
         double worst = 0.0, total = 0.0;
         std::vector<RayGroup> v = ray_groups(g, lists, packed, RAY_BLOCKS, RAY_WMAX, worst, total);
         const int ngroups = (int)v.size();
         if (!ngroups) continue;
         const int NQ = quads_per_row(g, p.nz_ref);
         const long ncg = ((long)p.nz_ref * ((g.K + 3) / 4) + NQ - 1) / NQ;
-        const LineSplit L = line_split(g, p.nz_ref, packed);
-        const bool small = small_workgroups(g, p.nz_ref, packed, ngroups);
-        if (small || small_workgroups(g, 1, packed, ngroups)) {
+        const bool small = small_workgroups(g, p.nz_ref, ngroups);
+        if (small || small_workgroups(g, 1, ngroups)) {
             double w = 0.0, t = 0.0;
             const std::vector<RayGroup> vs = ray_groups(g, lists, packed, RAY_BLOCKS_SMALL, RAY_WMAX_SMALL, w, t);
             v.insert(v.end(), vs.begin(), vs.end());
@@ -420,15 +413,13 @@ static int configure(Plan &p, TableUpload &up)
             }
         }
         const int ngr = small ? (int)v.size() - ngroups : ngroups;
-        const double W = (double)ncg * ngr * L.NLP;
-        const double occ = small ? (NQ == 4 ? 2 : 4) : 1, share = std::min(occ, std::max(1.0, W / 256));
-        const double rounds = W / (256 * occ), setup = small ? 3.0 : 30.0, us = (double)g.N / L.NLP / 2400;
+        const double W = (double)ncg * ngr, occ = small ? (NQ == 4 ? 2 : 4) : 1;
+        const double share = std::min(occ, std::max(1.0, W / 256)), rounds = W / (256 * occ);
+        const double setup = small ? 3.0 : 30.0, us = g.N / 2400.0;
         const double t = share * (rounds <= 6 ? std::ceil(rounds) * (worst * us + setup)
-                                              : total / ngr * (rounds + 0.5) * us + rounds * setup) +
-                         (L.NLP > 1 ? 8.0 + 2.0e-6 * L.NLP * n0 * p.nz_ref * g.Ns * ((g.K + 3) / 4 * 16) : 0.0);
+                                              : total / ngr * (rounds + 0.5) * us + rounds * setup);
         if (t < best_t) {
             best_t = t;
-            p.packed = packed;
             p.groups = v;
             p.ngroups = ngroups;
         }
@@ -555,7 +546,7 @@ static int configure(Plan &p, TableUpload &up)
         C.NLP = sf_line_parts(g);
         if (C.NLP == 1) {
             const long wg = (long)p.nz_ref * C.ngroups * C.nbt;
-            const long room = (long)line_parts_room(g, p.nz_ref) * ((g.K + 3) / 4 * 4) / g.Npi;
+            const long room = (long)line_split(g, p.nz_ref).NLP * ((g.K + 3) / 4 * 4) / g.Npi;
             const long fit = C.ST == 512 ? 512 : 256;
             auto cost = [&](long n) { return (wg * n + fit - 1) / fit * ((g.N + n - 1) / n + 24); };
             for (long n = 2; n <= std::min<long>({room, 32, g.N}); ++n)
